@@ -152,6 +152,14 @@ struct DevPlan {
   };
   bool vpath = false;
   std::vector<VPass> vpasses;
+  // genus 2: the image that counts level 2 by norms (norm_impl.h), in place of
+  // the level tables wherever every level of a tile is counted in one launch
+  bool npath = false;
+  hwc::PlanDesc ndesc{};
+  hwc::PlanDesc* d_ndesc = nullptr;
+  void* d_nimage = nullptr;
+  uint32_t* d_tmat = nullptr;
+  uint32_t nblock = 1024, ngrid = 0;
   uint64_t dev_bytes = 0;
   uint64_t last_use = 0;
   uint32_t block = 256, grid = 0, wpe = 1;
@@ -425,6 +433,13 @@ void free_plan(hwc_ctx* c, DevPlan* P) {
     defer_free(c, v.d_image, 0);
     defer_free(c, v.d_desc, 0);
   }
+  defer_free(c, P->d_nimage, 0);
+  defer_free(c, P->d_ndesc, 0);
+  defer_free(c, P->d_tmat, 0);
+  P->d_nimage = nullptr;
+  P->d_ndesc = nullptr;
+  P->d_tmat = nullptr;
+  P->npath = false;
   c->grave_bytes += P->dev_bytes;
   P->d_shift = nullptr;
   P->vpasses.clear();
@@ -707,6 +722,135 @@ int build_vplan(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, uint32_t g, uint
   return HWC_OK;
 }
 
+// Least field that counts level 2 by norms (genus 2, orbit sweep, split
+// evaluation on, no level in device memory).  Every field from 67 on gained
+// (count kernel on 2^18 curves: 67 0.62 -> 0.44 ms, 81 0.81 -> 0.78, 101 1.31
+// -> 0.84, 293 19.2 -> 5.6); below, a translate's setup is spread over fewer
+// than 32 points, and the quotient constant of the integer translates,
+// 2^30 / q, no longer fits 24 bits.
+constexpr uint32_t kNormMinQ = 65;
+
+// The image of norm_impl.h for (q, 2), or an empty one when it does not fit.
+// Fills the offsets of D and the level descriptors' table offsets.
+std::vector<uint8_t> norm_image(const hwc::Field& F1, uint32_t q, bool fold, hwc::NormDesc* D, uint32_t* tab1,
+                                uint32_t* emb1) {
+  const uint32_t M = q - 1, H = M / 2, zrow = fold ? 2 * M : 3 * M, rows = zrow + 2 * M + 1;
+  uint32_t srow = 1;
+  while (srow < 4 * M) srow *= 2;
+  const uint32_t S = srow * hwc::kNormRow, nfin = 2 * srow + 2 * M;
+  const uint64_t need = (uint64_t)rows * hwc::kNormRow + align16(10 * M) + align16(4 * q) + align16(nfin);
+  if (need > kLdsLimit) return {};
+  std::vector<uint8_t> img((size_t)need, 0);
+  auto put32 = [&](size_t off, uint32_t v) { std::memcpy(img.data() + off, &v, 4); };
+  auto put16 = [&](size_t off, uint32_t v) { const uint16_t h = (uint16_t)v; std::memcpy(img.data() + off, &h, 2); };
+  for (uint32_t r = 0; r < rows; ++r) {
+    uint32_t v = 0;
+    if (r < zrow) {
+      const uint32_t z = F1.zech[r % M];
+      v = z == M ? S : z * hwc::kNormRow;
+    } else if (r > zrow) {
+      const uint32_t k = r - zrow - 1;
+      v = k == 2 * M - 1 ? S : k % M * hwc::kNormRow;
+    }
+    for (uint32_t b = 0; b < hwc::kNormRow; b += 4) put32((size_t)r * hwc::kNormRow + b, v);
+  }
+  size_t off = (size_t)rows * hwc::kNormRow;
+  *tab1 = (uint32_t)off;
+  for (uint32_t i = 0; i < 3 * M; ++i) {   // form A
+    const uint32_t z = F1.zech[i % M];
+    put16(off + 2 * i, z == M ? 6 * M : 2 * z);
+  }
+  off += align16(10 * M);
+  *emb1 = (uint32_t)off;
+  for (uint32_t k = 0; k < q; ++k) put32(off + 4 * k, (uint32_t)F1.emb[k]);
+  off += align16(4 * q);
+  D->kind = fold ? hwc::kNormFold : hwc::kNormPlain;
+  D->M = M;
+  D->srow = srow;
+  D->emb_off = *emb1;
+  D->tab1_off = *tab1;
+  D->fin_off = (uint32_t)off;
+  const uint32_t par = H % 2 ? 0u : 1u;    // parity of log(-v), v a nonsquare
+  for (uint32_t i = 0; i < nfin; ++i) {
+    const int64_t d = (int64_t)i - (int64_t)srow;
+    uint32_t v;
+    if (d < -(int64_t)M) v = par;                               // E = 0: -v O^2
+    else if (d >= (int64_t)(5 * M) / 2) v = 0;                  // O = 0: E^2
+    else v = F1.zech[(2 * (uint32_t)((d + 2 * M) % H) + par) % M] & 1u;
+    img[off + i] = (uint8_t)v;
+  }
+  return img;
+}
+
+// The norm tables of a genus 2 plan, where the rule above takes them and they
+// fit LDS and what is left of the table budget; leaves npath unset otherwise.
+int build_norm(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, const Tuning& T, uint64_t plan_bytes) {
+  const uint32_t q = P->q, M = q - 1;
+  const hwc::LevelDesc& top = P->desc.lv[1];
+  if (q < kNormMinQ || !T.split || top.M < T.split_min_m || (T.device_tables & 3u)) return HWC_OK;
+  const hwc::Field& F1 = P->fields[0]->F;
+  hwc::NormDesc D{};
+  uint32_t tab1 = 0, emb1 = 0;
+  std::vector<uint8_t> img = norm_image(F1, q, false, &D, &tab1, &emb1);
+  if (img.empty()) img = norm_image(F1, q, true, &D, &tab1, &emb1);
+  if (img.empty()) return HWC_OK;
+  std::vector<uint32_t> tm;
+  if (e == 1) {
+    // rows i < 6 of t: binom(j, i) t^(j-i) mod q, times 4, pairs j = 2k, 2k + 1
+    const uint64_t m = ((1ull << 32) + 4 * q - 1) / (4 * q), vmax = 4ull * 7 * M * M;
+    if (m >= (1u << 24) || vmax >= (1u << 24) || vmax * (m * 4 * q - (1ull << 32)) >= (1ull << 32)) return HWC_OK;
+    D.qm = (uint32_t)m;
+    uint32_t binom[7][7] = {};
+    for (uint32_t j = 0; j < 7; ++j)
+      for (uint32_t i = 0; i <= j; ++i)
+        binom[j][i] = (i == 0 || i == j) ? 1u : binom[j - 1][i - 1] + binom[j - 1][i];
+    for (uint32_t t = 0; t < q; ++t)
+      for (uint32_t i = 0; i < 6; ++i) {
+        uint32_t row[8] = {};
+        for (uint32_t j = i, tp = 1; j < 7; ++j, tp = tp * t % q) row[j] = 4 * (binom[j][i] * tp % q);
+        for (uint32_t k = i / 2; k < 4; ++k) tm.push_back(row[2 * k] | row[2 * k + 1] << 16);
+      }
+  }
+  const uint64_t bytes = img.size() + tm.size() * 4 + sizeof(hwc::PlanDesc);
+  if (c->budget && plan_bytes + bytes > c->budget) return HWC_OK;   // the level tables alone fit
+  // launch shape: as for the level tables
+  uint32_t block = T.block;
+  int best = -1;
+  for (uint32_t b : {256u, 512u, 1024u}) {
+    if (T.block && b != T.block) continue;
+    int n = 0;
+    HIPX(c, hwc::occupancy_count(2, 1, b, (uint32_t)img.size(), P->wpe, &n));
+    if (n * (int)(b / hwc::kWave) > best) {
+      best = n * (int)(b / hwc::kWave);
+      block = b;
+      P->ngrid = (uint32_t)(c->cus * (T.wg_per_cu && (int)T.wg_per_cu < n ? (int)T.wg_per_cu : n));
+    }
+  }
+  if (best < 1) return HWC_OK;
+  P->nblock = block;
+  HIPX(c, hipMalloc(&P->d_nimage, img.size()));
+  HIPX(c, hipMemcpy(P->d_nimage, img.data(), img.size(), hipMemcpyHostToDevice));
+  if (!tm.empty()) {
+    HIPX(c, hipMalloc(&P->d_tmat, tm.size() * 4));
+    HIPX(c, hipMemcpy(P->d_tmat, tm.data(), tm.size() * 4, hipMemcpyHostToDevice));
+    D.tmat = P->d_tmat;
+  }
+  hwc::PlanDesc& N = P->ndesc;
+  N = P->desc;
+  N.image = static_cast<const uint32_t*>(P->d_nimage);
+  N.image_bytes = (uint32_t)img.size();
+  N.norm = D;
+  N.lv[0].form = hwc::kFormA;
+  N.lv[0].tab_off = tab1;
+  N.lv[0].emb_off = emb1;
+  HIPX(c, hipMalloc(&P->d_ndesc, sizeof(N)));
+  HIPX(c, hipMemcpy(P->d_ndesc, &N, sizeof(N), hipMemcpyHostToDevice));
+  P->dev_bytes += bytes;
+  c->table_bytes += bytes;
+  P->npath = true;
+  return HWC_OK;
+}
+
 // Build (or fetch) the device plan for (q, g, orbit).
 int get_plan(hwc_ctx* c, uint32_t q, uint32_t g, uint32_t orbit, DevPlan** out) {
   auto key = std::make_tuple(q, g, orbit);
@@ -961,6 +1105,10 @@ int get_plan(hwc_ctx* c, uint32_t q, uint32_t g, uint32_t orbit, DevPlan** out) 
   if (bpc < 1) bpc = 1;
   if (T.wg_per_cu && (int)T.wg_per_cu < bpc) bpc = (int)T.wg_per_cu;
   P->grid = (uint32_t)(c->cus * bpc);
+  if (g == 2 && orbit) {
+    const int rv = build_norm(c, P.get(), p, e, T, P->dev_bytes);
+    if (rv) return rv;
+  }
   if (T.mfma) {
     bool ok = false;
     int rv = build_vplan(c, P.get(), p, e, g, orbit, T.block, &ok);
@@ -1193,12 +1341,13 @@ int enqueue(hwc_ctx* c, DevPlan* P, const Scratch& S, const void* codes, int cb,
     } else {
       // a tile per bucket's ragged end besides the full ones (translated rows
       // fall in a few buckets; more tiles are still all counted)
-      const uint32_t grid = persistent_grid(P->grid, P->block, (n + hwc::kWave - 1) / hwc::kWave + 4);
+      const uint32_t block = P->npath ? P->nblock : P->block;
+      const uint32_t grid = persistent_grid(P->npath ? P->ngrid : P->grid, block, (n + hwc::kWave - 1) / hwc::kWave + 4);
       const uint32_t plog = S.acc ? part_log(P, flags) : 0u;
       if (plog) HIPX(c, hwc::launch_fill(S.acc, 0, n * g + S.max_tiles, s));
-      HIPX(c, hwc::launch_count(P->desc, P->d_desc, cb, codes, S.perm, S.tiles, S.ntiles, S.queue, 0, g - 1, N,
-                                lam ? S.lv : nullptr, plog, plog ? S.acc : nullptr, plog ? S.acc + n * g : nullptr,
-                                grid, P->block, P->wpe, s));
+      HIPX(c, hwc::launch_count(P->npath ? P->ndesc : P->desc, P->npath ? P->d_ndesc : P->d_desc, cb, codes, S.perm,
+                                S.tiles, S.ntiles, S.queue, 0, g - 1, N, lam ? S.lv : nullptr, plog,
+                                plog ? S.acc : nullptr, plog ? S.acc + n * g : nullptr, grid, block, P->wpe, s));
     }
     if (lam) HIPX(c, hwc::launch_lambda(P->desc, P->d_desc, cb, codes, n, S.lv, lam, (flags & kFlagSqf) ? 1u : 0u, s));
   }
@@ -1491,7 +1640,7 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     G.end = nz;
     for (size_t r = 0; r < nz; ++r) {
       const DevPlan* P = B.plans[B.order[r]];
-      G.lds = std::max(G.lds, P->desc.image_bytes);
+      G.lds = std::max(G.lds, P->npath ? P->ndesc.image_bytes : P->desc.image_bytes);
       G.gmax = std::max(G.gmax, P->g);
     }
     uint64_t tiles = 0;
@@ -1544,7 +1693,8 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
   std::vector<hwc::JobDesc> hj(std::max<size_t>(nz, 1));
   for (size_t r = 0; r < nz; ++r) {
     const hwc_job& J = jobs[B.order[r]];
-    hj[r].plan = B.plans[B.order[r]]->d_desc;
+    const DevPlan* P = B.plans[B.order[r]];
+    hj[r].plan = P->npath ? P->d_ndesc : P->d_desc;
     hj[r].codes = batch_rows(st, J, B, r);
     hj[r].perm = static_cast<uint32_t*>(st.bperm.p) + B.off[r];
     hj[r].tiles = static_cast<uint64_t*>(st.btiles.p) + B.toff[r];

@@ -27,38 +27,11 @@
 
 #include <algorithm>
 
+#include "count_core.h"
+#include "norm_impl.h"
 #include "plan.h"
 
 namespace hwc {
-
-// LDS reads at absolute LDS byte addresses.  The count and batch kernels
-// declare no static LDS, so their dynamic block -- the table image -- starts
-// at address 0 (prepare_kernels checks this on the host), and a table step is
-// one add and one read with no base to add.
-typedef const __attribute__((address_space(3))) uint16_t* lds16_ptr;
-typedef const __attribute__((address_space(3))) uint32_t* lds32_ptr;
-__device__ __forceinline__ uint32_t lds_u16(uint32_t addr) { return *(lds16_ptr)(size_t)addr; }
-__device__ __forceinline__ uint32_t lds_u32(uint32_t addr) { return *(lds32_ptr)(size_t)addr; }
-constexpr uint32_t kImageBase = 0;   // LDS address of the dynamic block
-
-__device__ __forceinline__ uint32_t uniform(uint32_t v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Uniform reads of data no kernel writes while it runs (x lists, tile words):
-// through the constant address space they become scalar loads instead of
-// vector loads that stall the wave on a full memory round trip.
-typedef const __attribute__((address_space(4))) uint32_t* const_u32_ptr;
-typedef const __attribute__((address_space(4))) uint64_t* const_u64_ptr;
-__device__ __forceinline__ uint32_t sload(const uint32_t* p, uint32_t i) { return ((const_u32_ptr)p)[i]; }
-__device__ __forceinline__ uint64_t sload64(const uint64_t* p, uint32_t i) { return ((const_u64_ptr)p)[i]; }
-__device__ __forceinline__ LevelDesc load_level(const PlanDesc& P, uint32_t j) {
-  static_assert(sizeof(LevelDesc) % 4 == 0, "LevelDesc is copied in dwords");
-  LevelDesc L;
-  const uint32_t* src = reinterpret_cast<const uint32_t*>(&P.lv[j]);
-  uint32_t* dst = reinterpret_cast<uint32_t*>(&L);
-#pragma unroll
-  for (uint32_t i = 0; i < sizeof(LevelDesc) / 4; ++i) dst[i] = sload(src, i);
-  return L;
-}
 
 // ----------------------------------------------------------------------------
 // the count
@@ -1060,7 +1033,22 @@ __device__ __forceinline__ void process_tile(const PlanDesc& P, uint32_t lb, con
   for (uint32_t j = lvl_lo; j <= lvl_hi; ++j) {
     const bool shared = j + 1 == (uint32_t)G;
     if (part && !shared) continue;
-    const uint32_t v = count_level<G>(load_level(P, j), lb, code, top, mask, shared ? part : 0u, shared ? plog : 0u);
+    uint32_t v = 0;
+    bool norm = false;
+    if constexpr (G == 2) {
+      if (shared) {
+        const NormDesc D = load_norm(P);
+        if (D.kind) {
+          norm = true;
+          if (D.kind == kNormFold)
+            v = top ? norm_level<true, true>(D, code, part, plog) : norm_level<true, false>(D, code, part, plog);
+          else
+            v = top ? norm_level<false, true>(D, code, part, plog) : norm_level<false, false>(D, code, part, plog);
+        }
+      }
+    }
+    if (!norm)
+      v = count_level<G>(load_level(P, j), lb, code, top, mask, shared ? part : 0u, shared ? plog : 0u);
 #pragma unroll
     for (int k = 0; k < G; ++k) lv[k] = (uint32_t)k == j ? v : lv[k];
   }
@@ -1110,7 +1098,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))) voi
   const PlanDesc& P = *Pd;
   extern __shared__ uint32_t lds32[];
   constexpr uint32_t lb = kImageBase;
-  for (uint32_t i = threadIdx.x; i < P.image_bytes / 4; i += blockDim.x) lds32[i] = P.image[i];
+  stage_image(lds32, P.image, P.image_bytes);
   __syncthreads();
   const uint32_t lane = threadIdx.x & (kWave - 1);
   // queue entries: tiles, or (plog > 0, levels 0..G-1 through the queue) the
@@ -1195,9 +1183,7 @@ __global__ __launch_bounds__(1024) void batch_kernel(const JobDesc* __restrict__
       if (threadIdx.x == 0) sh_open = atomicAdd(J.queue, 0u) < nt ? 1u : 0u;
       __syncthreads();
       if (!sh_open) continue;   // nothing left here: no restaging
-      const uint32_t* img = P->image;
-      const uint32_t nwords = P->image_bytes / 4;
-      for (uint32_t w = threadIdx.x; w < nwords; w += blockDim.x) lds32[w] = img[w];
+      stage_image(lds32, P->image, P->image_bytes);
       __syncthreads();
       staged = P;
     }

@@ -1,0 +1,244 @@
+#pragma once
+// Genus 2, level 2 by norms: the quadratic character of F_{q^2} read in F_q.
+//
+// Let delta be a nonsquare of F_q and F_{q^2} = F_q(sqrt delta).  Every
+// Frobenius orbit of size 2 is {t + s sqrt delta, t - s sqrt delta}, so the
+// orbits are the pairs (t, v) with t in F_q and v = s^2 delta a nonsquare of
+// F_q.  With f(t + y) = sum_i b_i y^i,
+//   f(t + s sqrt delta) = E + s sqrt delta O,
+//   E = b_0 + b_2 v + b_4 v^2 + b_6 v^3,   O = b_1 + b_3 v + b_5 v^2,
+// and chi(z) over F_{q^2} is chi of the norm N z = E^2 - v O^2 over F_q
+// (z^((q^2-1)/2) = (z^(q+1))^((q-1)/2)).  So one point costs six Zech steps in
+// F_q (three for E, two for O, one for the norm) instead of about three in
+// F_{q^2}; but F_q's table has q - 1 entries instead of q^2 - 1, so each lane
+// gets a copy of its own in its own LDS bank, and a read takes the 2 CU-clocks
+// of a conflict-free one, not the 6.3 of a random gather, with no folding of
+// half tables.  Count kernel on 2^18 curves against the level's own table:
+// q = 293 (85 848 elements) 19.2 -> 5.6 ms, 241 5.7 -> 3.4, 169 3.2 -> 2.0,
+// 101 1.31 -> 0.84, 67 0.62 -> 0.44.  Bound at q = 241: LDS 16.3 CU-clocks a
+// point (five conflict-free reads and one of the byte table), 13.5 vector
+// instructions, 17.7 measured; with the extra subtraction (q = 293) 17
+// instructions and 19.9.
+//
+// One lane holds one curve, as everywhere in the count; t and v are uniform.
+// Rows of the image (kNormRow bytes: one u32 per bank, all alike; M = q - 1):
+//   0 .. Z - 1   128 Z(r mod M), or the marker S where 1 + gamma^r = 0
+//   Z            0 (a vanished partial sum restarts from the next coefficient)
+//   Z + 1 ..     2M rows that return their own index mod M (128 (r mod M)),
+//                the last one the marker: the step of a zero coefficient,
+//                which only multiplies by v
+// (S: a power of two, at least 4M rows) with Z = 3M, or Z = 2M where 3M does not fit (fold: one more subtraction per
+// step).  A step is a + delta + L, clamped to the row that a marker must
+// reach (Z for a Zech step, the last row for a multiplication), and one read.
+// A step's delta, clamp and fold are per lane, so the zero coefficients that
+// some lane of nearly every translate has cost nothing.
+//
+// The last step needs the parity of log(1 - v O^2 / E^2) only:
+// w = log(-v) + 2 (log O - log E) mod M, so the sum d of the halves counts mod
+// M / 2.  As it is taken, -M < d < 5M / 2, or past 3M when O = 0 (N = E^2, a
+// square), or below -3M / 2 when E = 0 (N = -v O^2, of -v's parity): a byte
+// table over -S <= d < S + 2M holds the answer for each.  Both zero is a root,
+// found by a comparison.
+#include "count_core.h"
+
+namespace hwc {
+
+constexpr uint32_t kNormUnroll = 8;   // nonsquares v per pass of the inner loop
+
+typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
+
+__device__ __forceinline__ uint32_t lds_u8(uint32_t addr) {
+  return *(const __attribute__((address_space(3))) uint8_t*)(size_t)addr;
+}
+
+// floor(v m / 2^32) on 24-bit operands (v_mul_hi_u32_u24)
+__device__ __forceinline__ uint32_t norm_mulhi24(uint32_t v, uint32_t m) {
+  return (uint32_t)(((uint64_t)(v & 0xFFFFFFu) * (m & 0xFFFFFFu)) >> 32);
+}
+
+// One step's per-lane constants.
+struct NormStep {
+  uint32_t del, cap, fold;
+};
+
+// Links coefficient b (log, M = zero) below the chain whose last nonzero
+// coefficient has log beta: the step's constants (rows scaled to bytes, the
+// lane's bank included), and beta for the next one.
+__device__ __forceinline__ NormStep norm_link(uint32_t& beta, uint32_t b, uint32_t M, uint32_t zrow, uint32_t lane4) {
+  const bool z = b == M;
+  const uint32_t d = beta >= b ? beta - b : beta + M - b;
+  NormStep s;
+  s.del = (z ? zrow + 1u : d) * kNormRow + lane4;
+  s.cap = (z ? zrow + 2u * M : zrow) * kNormRow + lane4;
+  s.fold = z ? 0u : M * kNormRow;
+  beta = z ? beta : b;
+  return s;
+}
+
+template <bool FOLD>
+__device__ __forceinline__ uint32_t norm_step(uint32_t a, const NormStep& s, uint32_t L) {
+  const uint32_t v = a + s.del + L;
+  return lds_u32(FOLD ? min(min(v, v - s.fold), s.cap) : min(v, s.cap));
+}
+
+// U consecutive nonsquares v (logs L, L + 2, ..) at one t: odd logs of the
+// norms into odd, roots into z.  kl: the lane's and the first v's terms of the
+// last index, with the byte table's offset.
+template <bool FOLD, bool TOP, int U>
+__device__ __forceinline__ void norm_group(uint32_t L, uint32_t kl, const NormStep& e4, const NormStep& e2,
+                                           const NormStep& e0, const NormStep& o3, const NormStep& o1, uint32_t S,
+                                           uint32_t& odd, uint32_t& z) {
+  uint32_t aE[U], aO[U], r[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t Lu = L + 2u * kNormRow * u;
+    // the leading b_6 (degree 6) never vanishes, so its step cannot meet a
+    // marker; the chains that start at b_5 or b_4 carry a vanished start in
+    // their first delta
+    if (TOP) aE[u] = norm_step<FOLD>(lds_u32(e4.del + Lu), e2, Lu);
+    else aE[u] = lds_u32(min(e2.del + Lu, e2.cap));
+    aO[u] = lds_u32(min(o3.del + Lu, o3.cap));
+  }
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const uint32_t Lu = L + 2u * kNormRow * u;
+    aE[u] = norm_step<FOLD>(aE[u], e0, Lu);
+    aO[u] = norm_step<FOLD>(aO[u], o1, Lu);
+  }
+  uint32_t both = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    uint32_t x = aO[u] - aE[u] + kl;
+    asm("" : "+v"(x));                 // one shift of the sum, not one per term
+    r[u] = lds_u8(x / kNormRow + u);   // log(-v) / 2 grows by one per v
+    odd += r[u];
+    both |= aE[u] & aO[u];             // the marker is one bit above every row
+  }
+  if (__ballot(both >= S)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool root = (aE[u] & aO[u]) >= S;
+      z += root;
+      odd -= root ? r[u] : 0u;
+    }
+  }
+}
+
+// Every nonsquare v at one t: the chains of the translate's coefficients
+// b[0..6] (logs, M = zero; b[6] = M in degree 5).
+template <bool FOLD, bool TOP>
+__device__ __forceinline__ void norm_sweep_v(const uint32_t (&b)[7], const NormDesc& D, uint32_t lane4,
+                                             uint32_t& odd, uint32_t& z) {
+  const uint32_t M = D.M, H = M / 2, S = D.srow * kNormRow, zrow = FOLD ? 2u * M : 3u * M;
+  NormStep e4{}, e2, e0, o3, o1;
+  uint32_t bE, bO;
+  if (TOP) {
+    bE = b[6];
+    e4 = norm_link(bE, b[4], M, zrow, lane4);
+    e2 = norm_link(bE, b[2], M, zrow, lane4);
+  } else {
+    bE = b[4] == M ? 0u : b[4];
+    e2 = norm_link(bE, b[2], M, zrow, lane4);
+    e2.del += b[4] == M ? S : 0u;
+  }
+  e0 = norm_link(bE, b[0], M, zrow, lane4);
+  bO = b[5] == M ? 0u : b[5];
+  o3 = norm_link(bO, b[3], M, zrow, lane4);
+  o3.del += b[5] == M ? S : 0u;
+  o1 = norm_link(bO, b[1], M, zrow, lane4);
+  // v = gamma^(2k+1), k < H: log(-v) = H + 2k + 1, halved (its parity is
+  // fixed); with log O - log E of the chains' bases, mod H
+  uint32_t K = bO >= bE ? bO - bE : bO + M - bE;
+  K = K >= H ? K - H : K;
+  uint32_t L = kNormRow, kl = (K + (H + 1u) / 2u + D.fin_off + D.srow) * kNormRow, k = 0;
+  for (; k + kNormUnroll <= H; k += kNormUnroll) {
+    norm_group<FOLD, TOP, kNormUnroll>(L, kl, e4, e2, e0, o3, o1, S, odd, z);
+    L += 2u * kNormUnroll * kNormRow;
+    kl += kNormUnroll * kNormRow;
+  }
+  const uint32_t rest = H - k;
+  if (kNormUnroll > 4 && (rest & 4u)) {
+    norm_group<FOLD, TOP, 4>(L, kl, e4, e2, e0, o3, o1, S, odd, z);
+    L += 8u * kNormRow;
+    kl += 4u * kNormRow;
+  }
+  if (rest & 2u) {
+    norm_group<FOLD, TOP, 2>(L, kl, e4, e2, e0, o3, o1, S, odd, z);
+    L += 4u * kNormRow;
+    kl += 2u * kNormRow;
+  }
+  if (rest & 1u) norm_group<FOLD, TOP, 1>(L, kl, e4, e2, e0, o3, o1, S, odd, z);
+}
+
+// Sum of two elements of F_q given as logs (M = zero), by the form A table of
+// level 1 (entries 2 Z, 6M where 1 + gamma^d = 0); no branches, so the reads
+// of one translate overlap.
+__device__ __forceinline__ uint32_t norm_add(uint32_t tab, uint32_t M, uint32_t a, uint32_t b) {
+  const bool az = a == M, bz = b == M;
+  uint32_t d = b >= a ? b - a : b + M - a;
+  d = (az || bz) ? 0u : d;
+  const uint32_t v = lds_u16(tab + 2u * d);
+  uint32_t s = a + (v >> 1);
+  s = s >= M ? s - M : s;
+  s = v == 6u * M ? M : s;
+  return az ? b : (bz ? a : s);
+}
+
+// The counts of level 2 over the orbits (t, v), t in part `part` of 2^plog
+// shares of F_q: roots | nonsquares << 8, as count_level returns them.
+template <bool FOLD, bool TOP>
+__device__ __forceinline__ uint32_t norm_level(const NormDesc& D, const uint32_t (&code)[7], uint32_t part,
+                                               uint32_t plog) {
+  const uint32_t M = D.M, q = M + 1u;
+  const uint32_t lane4 = (threadIdx.x & 31u) * 4u;
+  const uint32_t t0 = (q * part) >> plog, t1 = (q * (part + 1u)) >> plog;
+  uint32_t odd = 0, z = 0;
+  uint32_t w[7];
+#pragma unroll
+  for (int i = 0; i < 7; ++i) w[i] = lds_u32(D.emb_off + 4u * code[i]);
+  uint32_t pk[4];   // coefficient pairs for the integer translates
+#pragma unroll
+  for (int k = 0; k < 4; ++k) pk[k] = code[2 * k] | (k < 3 ? code[2 * k + 1 < 7 ? 2 * k + 1 : 6] << 16 : 0u);
+#pragma unroll 1
+  for (uint32_t t = t0; t < t1; ++t) {
+    uint32_t b[7];
+    b[6] = w[6];
+    if (D.tmat) {
+      // prime q: b_i = sum_j binom(j, i) t^(j-i) c_j mod q by 2 x 16-bit dot
+      // products with the uniform rows of t, whose entries come times 4, so
+      // the residue times 4 is a byte offset into the logs
+      uint32_t at = t * kNormTmatWords;
+#pragma unroll
+      for (int i = 0; i < 6; ++i) {
+        uint32_t acc = 0;
+#pragma unroll
+        for (int k = i / 2; k < 4; ++k) {
+          const uint32_t row = sload(D.tmat, at++);
+          acc = __builtin_amdgcn_udot2(__builtin_bit_cast(ushort2_t, row), __builtin_bit_cast(ushort2_t, pk[k]), acc,
+                                       false);
+        }
+        b[i] = lds_u32(D.emb_off + acc - __umul24(norm_mulhi24(acc, D.qm), 4u * q));
+      }
+    } else {
+      // prime powers: repeated synthetic division by X - t in logs; t runs
+      // over 0, 1, gamma, gamma^2, ..
+#pragma unroll
+      for (int i = 0; i < 6; ++i) b[i] = w[i];
+      if (t) {
+        const uint32_t lt = t - 1u;
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+#pragma unroll
+          for (int i = 5; i >= k; --i) {
+            uint32_t m = b[i + 1] + lt;
+            m = m >= M ? m - M : m;
+            b[i] = norm_add(D.tab1_off, M, b[i], b[i + 1] == M ? M : m);
+          }
+      }
+    }
+    norm_sweep_v<FOLD, TOP>(b, D, lane4, odd, z);
+  }
+  return z | (odd << 8);
+}
+
+}  // namespace hwc

@@ -74,12 +74,30 @@ struct LevelDesc {
   const uint32_t* xs_s;
 };
 
+// Genus 2 with the norm tables (norm_impl.h) in place of level 2's Zech table.
+// Image: the rows at offset 0, level 1's form A table and logs, the byte table
+// of the last step.
+constexpr uint32_t kNormRow = 128;         // bytes of a row: one u32 per LDS bank
+constexpr uint32_t kNormTmatWords = 18;    // words per t of the translates of degree 6
+constexpr uint32_t kNormPlain = 1, kNormFold = 2;
+struct NormDesc {
+  uint32_t kind;          // 0: none, kNormPlain, kNormFold
+  uint32_t M;             // q - 1
+  uint32_t srow;          // row a vanished sum reads as: a power of two, at least 4M
+  uint32_t emb_off;       // logs of the codes in F_q (u32)
+  uint32_t tab1_off;      // F_q's form A table
+  uint32_t fin_off;       // byte table of the last step
+  uint32_t qm, pad;       // floor(v / 4q) = (v * qm) >> 32 for the integer translates
+  const uint32_t* tmat;   // prime q: [q][kNormTmatWords] translate rows; nullptr: log arithmetic
+};
+
 struct PlanDesc {
   uint32_t q, p, g, ncoef;   // q = p^e; ncoef = 2g+3
   uint32_t orbit;         // 1: level j sweeps primitive Frobenius orbits of F_{q^j}
   uint32_t image_bytes;   // LDS image size (multiple of 16)
   const uint32_t* image;  // device copy of the image (dwords)
   LevelDesc lv[kMaxG];
+  NormDesc norm;          // kind != 0: level 2 is counted by norms
 };
 
 // Factorization partition code (eq. 1.2): the multiplicity of part j
