@@ -53,6 +53,9 @@ uint64_t hist_scratch_bytes(uint64_t n);
 hipError_t hist_run(const int32_t* N, const uint32_t* lam, uint64_t n, uint32_t g, uint32_t q, void* scratch,
                     int32_t* out_keys, uint64_t* out_counts, uint64_t cap, uint64_t* out_len, uint32_t* err,
                     hipStream_t s);
+bool hist_is_small(uint64_t n, uint32_t g, uint32_t q, bool lam);
+hipError_t launch_hist_small_batch(const HistJob* jobs, uint32_t njobs, uint32_t* err, hipStream_t s);
+hipError_t prepare_hist_small();
 hipError_t launch_lambda(const PlanDesc& P, const PlanDesc* dP, int coeff_bytes, const void* codes, uint64_t n,
                          const uint32_t* lv, uint32_t* lam, uint32_t sqf, hipStream_t s);
 hipError_t launch_gen_reps(int coeff_bytes, uint32_t q, uint32_t ncoef, uint32_t d, uint32_t i, int32_t j,
@@ -1508,6 +1511,7 @@ struct BatchPlan {
   std::vector<BatchSeg> segs;       // launches over `order`
   std::vector<uint32_t> plog;       // tile parts (log2) per sorted job
   std::vector<uint64_t> aoff;       // word offset of the job's part counts in bacc
+  std::vector<hwc::HistJob> hjobs;  // histograms of one workgroup each (after the job descriptors in memory)
   uint64_t ntot = 0, tiles_tot = 0, nhist = 0, tbytes = 0, nlv = 0, acc_words = 0;
 };
 
@@ -1524,8 +1528,8 @@ const void* batch_rows(const ScratchSet& st, const hwc_job& J, const BatchPlan& 
 // multi-plan launch (after their bucketing), their histograms, then each
 // matrix-product job as its own launches (ordered on the same stream; in a
 // captured graph they are nodes of the same graph).
-int enqueue_batch(hwc_ctx* c, const hwc_job* jobs, const BatchPlan& B, const hwc::JobDesc* d_jobs, int set,
-                  uint32_t flags, hipStream_t s) {
+int enqueue_batch(hwc_ctx* c, const hwc_job* jobs, const BatchPlan& B, const hwc::JobDesc* d_jobs,
+                  const hwc::HistJob* d_hjobs, int set, uint32_t flags, hipStream_t s) {
   const ScratchSet& st = c->sets[set];
   const size_t nz = B.order.size();
   if (nz) {
@@ -1553,9 +1557,10 @@ int enqueue_batch(hwc_ctx* c, const hwc_job* jobs, const BatchPlan& B, const hwc
     if (B.acc_words) HIPX(c, hwc::launch_fill(static_cast<uint32_t*>(st.bacc.p), 0, B.acc_words, s));
     for (const BatchSeg& G : B.segs)
       HIPX(c, hwc::launch_batch(d_jobs + G.begin, (uint32_t)(G.end - G.begin), G.gmax, G.lds, G.grid, G.block, s));
+    HIPX(c, hwc::launch_hist_small_batch(d_hjobs, (uint32_t)B.hjobs.size(), c->d_err, s));
     for (size_t r = 0; r < nz; ++r) {
       const hwc_job& J = jobs[B.order[r]];
-      if (!J.d_hist_keys) continue;
+      if (!J.d_hist_keys || hwc::hist_is_small(J.n, J.g, J.q, false)) continue;
       HIPX(c, hwc::hist_run(J.d_out_N, nullptr, J.n, J.g, J.q, st.hist.p, J.d_hist_keys, J.d_hist_counts,
                             J.hist_capacity, J.d_hist_len, c->d_err, s));
     }
@@ -1678,7 +1683,10 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     } else {
       B.tco.push_back(kNoShift);
     }
-    if (J.d_hist_keys) B.nhist = std::max<uint64_t>(B.nhist, J.n);
+    if (J.d_hist_keys && hwc::hist_is_small(J.n, J.g, J.q, false))
+      B.hjobs.push_back({J.d_out_N, nullptr, J.d_hist_keys, J.d_hist_counts, J.d_hist_len, J.hist_capacity,
+                         (uint32_t)J.n, J.g, J.q, 0});
+    else if (J.d_hist_keys) B.nhist = std::max<uint64_t>(B.nhist, J.n);
   }
   if (nz) {
     if ((rc = ensure(c, set, st.bpid, std::max<uint64_t>(B.ntot, 1) * 2))) return rc;
@@ -1709,7 +1717,13 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     hj[r].acc = B.plog[r] ? static_cast<uint32_t*>(st.bacc.p) + B.aoff[r] : nullptr;
     hj[r].done = B.plog[r] ? hj[r].acc + J.n * J.g : nullptr;
   }
-  const size_t jbytes = std::max<size_t>(nz, 1) * sizeof(hwc::JobDesc);
+  // the job descriptors, then those of the histograms
+  const size_t jobs_bytes = (std::max<size_t>(nz, 1) * sizeof(hwc::JobDesc) + 15) / 16 * 16;
+  const size_t jbytes = jobs_bytes + B.hjobs.size() * sizeof(hwc::HistJob);
+  std::vector<uint8_t> desc(jbytes, 0);
+  std::memcpy(desc.data(), hj.data(), hj.size() * sizeof(hwc::JobDesc));
+  if (!B.hjobs.empty())
+    std::memcpy(desc.data() + jobs_bytes, B.hjobs.data(), B.hjobs.size() * sizeof(hwc::HistJob));
   if ((rc = order_begin(c, set, s))) return rc;
   const bool use_graph = !(flags & HWC_NO_GRAPH) && !c->profile;
   if (!use_graph) {
@@ -1723,14 +1737,15 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
       if (sl.h) HIPX(c, hipHostFree(sl.h));
       sl.p = sl.h = nullptr;
       sl.bytes = 0;
-      const size_t want = std::max<size_t>(jbytes, 64 * sizeof(hwc::JobDesc));
+      const size_t want = std::max<size_t>(jbytes, 64 * (sizeof(hwc::JobDesc) + sizeof(hwc::HistJob)));
       HIPX(c, hipMalloc(&sl.p, want));
       HIPX(c, hipHostMalloc(&sl.h, want, hipHostMallocDefault));
       sl.bytes = want;
     }
-    std::memcpy(sl.h, hj.data(), jbytes);
+    std::memcpy(sl.h, desc.data(), jbytes);
     HIPX(c, hipMemcpyAsync(sl.p, sl.h, jbytes, hipMemcpyHostToDevice, s));
-    rc = enqueue_batch(c, jobs, B, static_cast<const hwc::JobDesc*>(sl.p), set, flags, s);
+    rc = enqueue_batch(c, jobs, B, static_cast<const hwc::JobDesc*>(sl.p),
+                       reinterpret_cast<const hwc::HistJob*>(static_cast<uint8_t*>(sl.p) + jobs_bytes), set, flags, s);
     if (rc) return rc;
     HIPX(c, hipEventRecord(sl.done, s));
     sl.used = true;
@@ -1758,13 +1773,15 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
   ge.set = set;
   ge.plans.assign(B.plans.begin(), B.plans.end());
   HIPX(c, hipMalloc(&ge.jobs, jbytes));
-  hipError_t me = hipMemcpy(ge.jobs, hj.data(), jbytes, hipMemcpyHostToDevice);
+  hipError_t me = hipMemcpy(ge.jobs, desc.data(), jbytes, hipMemcpyHostToDevice);
   if (me != hipSuccess) {
     (void)hipFree(ge.jobs);
     return fail(c, HWC_ERR_DEVICE, std::string("job copy: ") + hipGetErrorString(me));
   }
   HIPX(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-  rc = enqueue_batch(c, jobs, B, static_cast<const hwc::JobDesc*>(ge.jobs), set, flags, c->stream);
+  rc = enqueue_batch(c, jobs, B, static_cast<const hwc::JobDesc*>(ge.jobs),
+                     reinterpret_cast<const hwc::HistJob*>(static_cast<uint8_t*>(ge.jobs) + jobs_bytes), set, flags,
+                     c->stream);
   hipGraph_t graph = nullptr;
   hipError_t ee = hipStreamEndCapture(c->stream, &graph);
   ge.graph = graph;
@@ -2210,6 +2227,7 @@ int hwc_ctx_create(int device, uint64_t hbm_budget_bytes, hwc_ctx** out) {
     c->cus = prop.multiProcessorCount;
     if ((e = hwc::prepare_kernels()) != hipSuccess) return create_fail(e, "kernel attributes");
     if ((e = hwc::prepare_vcount()) != hipSuccess) return create_fail(e, "kernel attributes");
+    if ((e = hwc::prepare_hist_small()) != hipSuccess) return create_fail(e, "kernel attributes");
     if ((e = hipMalloc(reinterpret_cast<void**>(&c->d_err), 256)) != hipSuccess) return create_fail(e, "hipMalloc");
     for (auto& st : c->sets)
       if ((e = hipEventCreateWithFlags(&st.ev, hipEventDisableTiming)) != hipSuccess)

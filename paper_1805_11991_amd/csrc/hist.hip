@@ -26,11 +26,12 @@ struct KeyRadix {
   uint32_t g;          // columns taken from N
   uint32_t width;      // g, or g + 1 with the factorization code as last column
   uint64_t radix[5];   // R_k, then the number of partition codes
-  uint32_t nlam;       // partition codes (ascending): the code's digit is its rank
-  uint32_t lam_codes[kLamCodesMax];
-  uint32_t lam_mul;    // slot (c * lam_mul) >> 24 is distinct for every code c
-  uint8_t lam_slot[256];   // rank + 1 of the code in that slot, 0 for none
+  LamCodes lc;         // with the code as last column: its digit is its rank
 };
+
+// hist_small.hip
+bool hist_is_small(uint64_t n, uint32_t g, uint32_t q, bool lam);
+hipError_t launch_hist_small(const HistJob& J, const LamCodes* lc, uint32_t* err, hipStream_t s);
 
 // ---- device-wide exclusive scan of u32 (chunks of kScanTile) ----
 
@@ -195,8 +196,8 @@ __global__ __launch_bounds__(kSortThreads) void make_keys_kernel(const int32_t* 
   __shared__ uint32_t codes[kLamCodesMax];
   __shared__ uint8_t slots[256];
   __shared__ uint32_t cnt[kRadixBins];
-  for (uint32_t t = threadIdx.x; t < kr.nlam; t += blockDim.x) codes[t] = kr.lam_codes[t];
-  for (uint32_t t = threadIdx.x; t < 256; t += blockDim.x) slots[t] = kr.lam_slot[t];
+  for (uint32_t t = threadIdx.x; t < kr.lc.n; t += blockDim.x) codes[t] = kr.lc.code[t];
+  for (uint32_t t = threadIdx.x; t < 256; t += blockDim.x) slots[t] = kr.lc.slot[t];
   for (uint32_t t = threadIdx.x; t < kRadixBins; t += blockDim.x) cnt[t] = 0;
   __syncthreads();
   const uint32_t tile = xcd_tile(blockIdx.x, nblocks);
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kSortThreads) void make_keys_kernel(const int32_t* 
       }
       if (lam) {
         const uint32_t v = lam[i];
-        uint32_t rk = slots[(v * kr.lam_mul) >> 24];  // rank + 1 of the code in v's slot
+        uint32_t rk = slots[(v * kr.lc.mul) >> 24];  // rank + 1 of the code in v's slot
         if (rk == 0 || codes[rk - 1] != v) { bad = 1; rk = 1; }
         key = key * (K)kr.radix[kr.g] + (K)(rk - 1);
       }
@@ -420,7 +421,7 @@ __global__ __launch_bounds__(256) void runs_kernel(const K* __restrict__ keys, u
       for (int k = (int)kr.width - 1; k >= 0; --k) {
         const K r = (K)kr.radix[k];
         const uint32_t d = (uint32_t)(key % r);
-        out_keys[j * kr.width + k] = (int32_t)(k == (int)kr.g ? kr.lam_codes[d] : d);
+        out_keys[j * kr.width + k] = (int32_t)(k == (int)kr.g ? kr.lc.code[d] : d);
         key /= r;
       }
     }
@@ -533,30 +534,34 @@ hipError_t hist_run(const int32_t* N, const uint32_t* lam, uint64_t n, uint32_t 
     kr.radix[k] = (k < g) ? 2 * qk + 3 : 1;
     if (k < g) bits += __builtin_log2((double)kr.radix[k]);
   }
-  kr.nlam = lam ? lam_code_list(g, kr.lam_codes) : 0u;
-  kr.lam_mul = 0;
-  for (uint32_t t = 0; t < 256; ++t) kr.lam_slot[t] = 0;
+  kr.lc.n = lam ? lam_code_list(g, kr.lc.code) : 0u;
+  kr.lc.mul = 0;
+  for (uint32_t t = 0; t < 256; ++t) kr.lc.slot[t] = 0;
   if (lam) {   // an odd multiplier that puts the codes in distinct slots (the first one tried does for g <= 4)
-    for (uint32_t m = 0x9E3779B1u, tries = 0; kr.lam_mul == 0; m += 2) {
+    for (uint32_t m = 0x9E3779B1u, tries = 0; kr.lc.mul == 0; m += 2) {
       if (++tries > (1u << 16)) return hipErrorInvalidValue;
       bool clash = false;
-      for (uint32_t t = 0; t < 256; ++t) kr.lam_slot[t] = 0;
-      for (uint32_t r = 0; r < kr.nlam && !clash; ++r) {
-        uint8_t& sl = kr.lam_slot[(kr.lam_codes[r] * m) >> 24];
+      for (uint32_t t = 0; t < 256; ++t) kr.lc.slot[t] = 0;
+      for (uint32_t r = 0; r < kr.lc.n && !clash; ++r) {
+        uint8_t& sl = kr.lc.slot[(kr.lc.code[r] * m) >> 24];
         clash = sl != 0;
         sl = (uint8_t)(r + 1);
       }
       if (!clash) {
-        kr.lam_mul = m;
+        kr.lc.mul = m;
         break;
       }
     }
   }
   if (lam) {
-    kr.radix[g] = kr.nlam;
-    bits += __builtin_log2((double)kr.nlam);
+    kr.radix[g] = kr.lc.n;
+    bits += __builtin_log2((double)kr.lc.n);
   }
   if (bits > 63.0) return hipErrorInvalidValue;
+  if (hist_is_small(n, g, q, lam != nullptr)) {
+    const HistJob J = {N, lam, out_keys, out_counts, out_len, cap, (uint32_t)n, g, q, 0};
+    return launch_hist_small(J, lam ? &kr.lc : nullptr, err, s);
+  }
   const uint32_t nbits = (uint32_t)bits + 1;
   // 9-bit digits when they save a pass over 8-bit ones
   const uint32_t p8 = (nbits + 7) / 8, p9 = (nbits + 8) / 9;

@@ -144,6 +144,27 @@ inline uint32_t lam_code_list(uint32_t g, uint32_t* out) {
   return n;
 }
 
+// The partition codes as histogram digits: a code's rank, found through a
+// multiplicative hash with a slot per code.
+struct LamCodes {
+  uint32_t n;                       // codes (ascending)
+  uint32_t code[kLamCodesMax];
+  uint32_t mul;                     // slot (c * mul) >> 24 is distinct for every code c
+  uint8_t slot[256];                // rank + 1 of the code in that slot, 0 for none
+};
+
+// One request of the one-workgroup histogram (hist_small.hip).
+constexpr uint32_t kHistSmallMax = 8192;
+struct HistJob {
+  const int32_t* N;        // [n][g]
+  const uint32_t* lam;     // [n] partition codes, or nullptr
+  int32_t* keys;           // [cap][g, or g + 1 with lam]
+  uint64_t* counts;        // [cap]
+  uint64_t* len;           // number of distinct tuples, or nullptr
+  uint64_t cap;
+  uint32_t n, g, q, pad;
+};
+
 // One curve for the lane-per-x kernel: coefficient logs in F_{q^k} (M where
 // the coefficient is zero), degree d, M = q^k - 1.
 struct SingleDesc {

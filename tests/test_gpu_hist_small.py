@@ -1,0 +1,82 @@
+"""The one-workgroup histogram (requests of up to 8192 rows): sorted tuples and
+multiplicities equal numpy's over the counts themselves, at the edges of its
+waves, of its keys per thread and of its range; few and many distinct tuples;
+a capacity below the need; the partition column; several jobs in one launch."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+SIZES = [1, 63, 64, 65, 1023, 1024, 1025, 2048, 2049, 4096, 4097, 8191, 8192, 8193]
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1805_11991_amd import hwcount
+    c = hwcount.Context(device=0)
+    yield c
+    c.close()
+
+
+def _request(curvegen_mod, q, g, n, cap, cols):
+    import torch
+    d = torch.from_numpy(curvegen_mod.sample(q, g, n, seed=10 * q + g)).cuda()
+    return {"q": q, "g": g, "d_coeffs": d, "d_out_N": torch.zeros((n, g), dtype=torch.int32, device="cuda"),
+            "d_hist_keys": torch.full((cap, cols), -7, dtype=torch.int32, device="cuda"),
+            "d_hist_counts": torch.full((cap,), -7, dtype=torch.int64, device="cuda"),
+            "d_hist_len": torch.zeros(1, dtype=torch.int64, device="cuda")}
+
+
+def _check(j, columns):
+    keys, counts = np.unique(columns, axis=0, return_counts=True)
+    cap = j["d_hist_keys"].shape[0]
+    assert int(j["d_hist_len"].item()) == len(keys)
+    m = min(cap, len(keys))
+    hk, hc = j["d_hist_keys"].cpu().numpy(), j["d_hist_counts"].cpu().numpy()
+    assert np.array_equal(hk[:m], keys[:m]) and np.array_equal(hc[:m], counts[:m])
+    assert (hk[m:] == -7).all() and (hc[m:] == -7).all()      # nothing past the end
+
+
+@pytest.mark.parametrize("n", SIZES)
+@pytest.mark.parametrize("q,g", [(3, 1), (3, 2), (13, 3), (101, 2), (5, 4)])
+def test_small_histogram(ctx, curvegen_mod, q, g, n):
+    j = _request(curvegen_mod, q, g, n, n, g)
+    ctx.count_curves_dev(q, g, j["d_coeffs"], j["d_out_N"], j["d_hist_keys"], j["d_hist_counts"], j["d_hist_len"])
+    ctx.status()
+    _check(j, j["d_out_N"].cpu().numpy())
+
+
+@pytest.mark.parametrize("cap", [1, 37])
+def test_short_capacity(ctx, curvegen_mod, cap):
+    j = _request(curvegen_mod, 13, 4, 1500, cap, 4)
+    ctx.count_curves_dev(13, 4, j["d_coeffs"], j["d_out_N"], j["d_hist_keys"], j["d_hist_counts"], j["d_hist_len"])
+    ctx.status()
+    assert int(j["d_hist_len"].item()) > cap
+    _check(j, j["d_out_N"].cpu().numpy())
+
+
+@pytest.mark.parametrize("q,g,n", [(13, 3, 700), (7, 2, 8192), (5, 4, 3000)])
+def test_partition_column(ctx, curvegen_mod, q, g, n):
+    import torch
+    j = _request(curvegen_mod, q, g, n, n, g + 1)
+    lam = torch.zeros(n, dtype=torch.int32, device="cuda")
+    ctx.count_lambda_dev(q, g, j["d_coeffs"], j["d_out_N"], lam, j["d_hist_keys"], j["d_hist_counts"],
+                         j["d_hist_len"])
+    ctx.status()
+    _check(j, np.concatenate([j["d_out_N"].cpu().numpy(), lam.cpu().numpy()[:, None]], axis=1))
+
+
+@pytest.mark.parametrize("flags", [0, 8])
+def test_batch_of_small_and_large(ctx, curvegen_mod, flags):
+    jobs = [_request(curvegen_mod, q, g, n, n, g)
+            for q, g, n in [(5, 2, 10), (13, 3, 8193), (9, 3, 1), (67, 2, 2000), (3, 4, 8192), (7, 1, 4100)]]
+    for _ in range(2):
+        ctx.count_batch(jobs, flags=flags)
+        ctx.status()
+    for j in jobs:
+        _check(j, j["d_out_N"].cpu().numpy())
