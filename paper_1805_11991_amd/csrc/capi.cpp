@@ -56,6 +56,10 @@ hipError_t hist_run(const int32_t* N, const uint32_t* lam, uint64_t n, uint32_t 
 bool hist_is_small(uint64_t n, uint32_t g, uint32_t q, bool lam);
 hipError_t launch_hist_small_batch(const HistJob* jobs, uint32_t njobs, uint32_t* err, hipStream_t s);
 hipError_t prepare_hist_small();
+hipError_t launch_bucket_small(const BucketJob& J, uint32_t* err, hipStream_t s);
+hipError_t launch_bucket_small_batch(const BucketJob* hjobs, const BucketJob* jobs, uint32_t njobs, uint32_t* err,
+                                     hipStream_t s);
+hipError_t prepare_bucket_small();
 hipError_t launch_lambda(const PlanDesc& P, const PlanDesc* dP, int coeff_bytes, const void* codes, uint64_t n,
                          const uint32_t* lv, uint32_t* lam, uint32_t sqf, hipStream_t s);
 hipError_t launch_gen_reps(int coeff_bytes, uint32_t q, uint32_t ncoef, uint32_t d, uint32_t i, int32_t j,
@@ -1272,6 +1276,27 @@ uint32_t part_log(const DevPlan* P, uint32_t flags) {
   return top.xs && top.nx >= kPartMinPoints ? kPartLog : 0;
 }
 
+// The one-workgroup bucketing of n rows (out: their dense translates, or null).
+hwc::BucketJob bucket_job(const DevPlan* P, const void* codes, void* out, int cb, uint64_t n, uint32_t* perm,
+                          uint64_t* tiles, uint32_t* ntiles, uint32_t* queue, uint32_t* acc, uint64_t acc_words) {
+  hwc::BucketJob J{};
+  J.codes = codes;
+  J.out = out;
+  J.step = P->d_shift;
+  J.perm = perm;
+  J.tiles = tiles;
+  J.ntiles = ntiles;
+  J.queue = queue;
+  J.acc = acc;
+  J.acc_words = (uint32_t)acc_words;
+  J.n = (uint32_t)n;
+  J.q = P->q;
+  J.g = P->g;
+  J.cb = (uint32_t)cb;
+  J.mode = !out ? 0u : P->desc.p == P->q ? 1u : 2u;
+  return J;
+}
+
 // Enqueue the whole count of one request on stream s.
 int take_event(hwc_ctx* c, hipEvent_t* ev) {
   if (!c->event_pool.empty()) {
@@ -1327,13 +1352,23 @@ int enqueue(hwc_ctx* c, DevPlan* P, const Scratch& S, const void* codes, int cb,
     return HWC_OK;
   }
   const bool shifted = P->d_shift && n > 0;
-  if (shifted) {   // translate and classify in one pass
-    HIPX(c, hwc::launch_fill(S.counts, 0, hwc::pattern_count(g), s));
-    HIPX(c, hwc::launch_shift(cb, g, codes, n, P->q, P->d_shift, S.tcodes, S.pid, S.counts, c->d_err, s));
-    codes = S.tcodes;
+  const uint32_t plog = S.acc && n > 0 ? part_log(P, flags) : 0u;
+  const uint64_t acc_words = plog ? n * g + S.max_tiles : 0;
+  if (n <= hwc::kBucketSmallMax) {
+    HIPX(c, hwc::launch_bucket_small(bucket_job(P, codes, shifted ? S.tcodes : nullptr, cb, n, S.perm, S.tiles, S.ntiles,
+                                                S.queue, S.acc, acc_words),
+                                     c->d_err, s));
+    if (shifted) codes = S.tcodes;
+  } else {
+    if (shifted) {   // translate and classify in one pass
+      HIPX(c, hwc::launch_fill(S.counts, 0, hwc::pattern_count(g), s));
+      HIPX(c, hwc::launch_shift(cb, g, codes, n, P->q, P->d_shift, S.tcodes, S.pid, S.counts, c->d_err, s));
+      codes = S.tcodes;
+    }
+    HIPX(c, hwc::launch_bucket(cb, codes, n, P->q, g, S.pid, S.counts, c->d_err, S.bucket_start, S.tile_start,
+                               S.cursor, S.ntiles, S.queue, S.tiles, S.perm, S.max_tiles, shifted, s));
+    HIPX(c, hwc::launch_fill(S.acc, 0, acc_words, s));
   }
-  HIPX(c, hwc::launch_bucket(cb, codes, n, P->q, g, S.pid, S.counts, c->d_err, S.bucket_start, S.tile_start,
-                             S.cursor, S.ntiles, S.queue, S.tiles, S.perm, S.max_tiles, shifted, s));
   if (record) HIPX(c, hipEventRecord(ev[1], s));
   if (n > 0) {
     if (flags & HWC_PLAIN) {
@@ -1346,8 +1381,6 @@ int enqueue(hwc_ctx* c, DevPlan* P, const Scratch& S, const void* codes, int cb,
       // fall in a few buckets; more tiles are still all counted)
       const uint32_t block = P->npath ? P->nblock : P->block;
       const uint32_t grid = persistent_grid(P->npath ? P->ngrid : P->grid, block, (n + hwc::kWave - 1) / hwc::kWave + 4);
-      const uint32_t plog = S.acc ? part_log(P, flags) : 0u;
-      if (plog) HIPX(c, hwc::launch_fill(S.acc, 0, n * g + S.max_tiles, s));
       HIPX(c, hwc::launch_count(P->npath ? P->ndesc : P->desc, P->npath ? P->d_ndesc : P->d_desc, cb, codes, S.perm,
                                 S.tiles, S.ntiles, S.queue, 0, g - 1, N, lam ? S.lv : nullptr, plog,
                                 plog ? S.acc : nullptr, plog ? S.acc + n * g : nullptr, grid, block, P->wpe, s));
@@ -1512,6 +1545,7 @@ struct BatchPlan {
   std::vector<uint32_t> plog;       // tile parts (log2) per sorted job
   std::vector<uint64_t> aoff;       // word offset of the job's part counts in bacc
   std::vector<hwc::HistJob> hjobs;  // histograms of one workgroup each (after the job descriptors in memory)
+  std::vector<hwc::BucketJob> bjobs;  // bucketings of one workgroup each (after those)
   uint64_t ntot = 0, tiles_tot = 0, nhist = 0, tbytes = 0, nlv = 0, acc_words = 0;
 };
 
@@ -1529,7 +1563,8 @@ const void* batch_rows(const ScratchSet& st, const hwc_job& J, const BatchPlan& 
 // matrix-product job as its own launches (ordered on the same stream; in a
 // captured graph they are nodes of the same graph).
 int enqueue_batch(hwc_ctx* c, const hwc_job* jobs, const BatchPlan& B, const hwc::JobDesc* d_jobs,
-                  const hwc::HistJob* d_hjobs, int set, uint32_t flags, hipStream_t s) {
+                  const hwc::HistJob* d_hjobs, const hwc::BucketJob* d_bjobs, int set, uint32_t flags,
+                  hipStream_t s) {
   const ScratchSet& st = c->sets[set];
   const size_t nz = B.order.size();
   if (nz) {
@@ -1537,8 +1572,10 @@ int enqueue_batch(hwc_ctx* c, const hwc_job* jobs, const BatchPlan& B, const hwc
     uint32_t* perm = static_cast<uint32_t*>(st.bperm.p);
     uint64_t* tiles = static_cast<uint64_t*>(st.btiles.p);
     uint32_t* small = static_cast<uint32_t*>(st.bsmall.p);
+    HIPX(c, hwc::launch_bucket_small_batch(B.bjobs.data(), d_bjobs, (uint32_t)B.bjobs.size(), c->d_err, s));
     for (size_t r = 0; r < nz; ++r) {
       const hwc_job& J = jobs[B.order[r]];
+      if (J.n <= hwc::kBucketSmallMax) continue;
       const DevPlan* P = B.plans[B.order[r]];
       uint32_t* sm = small + r * kSmallStride;
       const void* rows = batch_rows(st, J, B, r);
@@ -1551,10 +1588,11 @@ int enqueue_batch(hwc_ctx* c, const hwc_job* jobs, const BatchPlan& B, const hwc
       HIPX(c, hwc::launch_bucket(J.coeff_bytes, rows, J.n, P->q, P->g, pid + B.off[r], sm, c->d_err, sm + 2048,
                                  sm + 4096, sm + 6144, sm + 8192, sm + 8196, tiles + B.toff[r], perm + B.off[r],
                                  B.max_tiles[r], shifted, s));
+      // the part counts and finished-part counters start at zero (a fill
+      // kernel, which graph capture records as an ordinary kernel node)
+      if (B.plog[r])
+        HIPX(c, hwc::launch_fill(static_cast<uint32_t*>(st.bacc.p) + B.aoff[r], 0, J.n * J.g + B.max_tiles[r], s));
     }
-    // the part counts and finished-part counters start at zero (a fill
-    // kernel, which graph capture records as an ordinary kernel node)
-    if (B.acc_words) HIPX(c, hwc::launch_fill(static_cast<uint32_t*>(st.bacc.p), 0, B.acc_words, s));
     for (const BatchSeg& G : B.segs)
       HIPX(c, hwc::launch_batch(d_jobs + G.begin, (uint32_t)(G.end - G.begin), G.gmax, G.lds, G.grid, G.block, s));
     HIPX(c, hwc::launch_hist_small_batch(d_hjobs, (uint32_t)B.hjobs.size(), c->d_err, s));
@@ -1716,14 +1754,32 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     hj[r].plog = B.plog[r];
     hj[r].acc = B.plog[r] ? static_cast<uint32_t*>(st.bacc.p) + B.aoff[r] : nullptr;
     hj[r].done = B.plog[r] ? hj[r].acc + J.n * J.g : nullptr;
+    if (J.n <= hwc::kBucketSmallMax) {
+      const bool shifted = hj[r].codes != J.d_coeffs;
+      B.bjobs.push_back(bucket_job(P, J.d_coeffs, shifted ? const_cast<void*>(hj[r].codes) : nullptr, J.coeff_bytes,
+                                   J.n, const_cast<uint32_t*>(hj[r].perm), const_cast<uint64_t*>(hj[r].tiles),
+                                   const_cast<uint32_t*>(hj[r].ntiles), hj[r].queue, hj[r].acc,
+                                   B.plog[r] ? J.n * J.g + B.max_tiles[r] : 0));
+    }
   }
-  // the job descriptors, then those of the histograms
-  const size_t jobs_bytes = (std::max<size_t>(nz, 1) * sizeof(hwc::JobDesc) + 15) / 16 * 16;
-  const size_t jbytes = jobs_bytes + B.hjobs.size() * sizeof(hwc::HistJob);
-  std::vector<uint8_t> desc(jbytes, 0);
-  std::memcpy(desc.data(), hj.data(), hj.size() * sizeof(hwc::JobDesc));
-  if (!B.hjobs.empty())
-    std::memcpy(desc.data() + jobs_bytes, B.hjobs.data(), B.hjobs.size() * sizeof(hwc::HistJob));
+  // the job descriptors, then those of the histograms and of the bucketings
+  std::vector<uint8_t> desc;
+  auto append = [&](const void* p, size_t bytes) {
+    const size_t at = desc.size();
+    desc.resize(at + (bytes + 15) / 16 * 16, 0);
+    if (bytes) std::memcpy(desc.data() + at, p, bytes);
+    return at;
+  };
+  append(hj.data(), hj.size() * sizeof(hwc::JobDesc));
+  const size_t hist_at = append(B.hjobs.data(), B.hjobs.size() * sizeof(hwc::HistJob));
+  const size_t bucket_at = append(B.bjobs.data(), B.bjobs.size() * sizeof(hwc::BucketJob));
+  const size_t jbytes = desc.size();
+  auto enqueue_at = [&](void* base, hipStream_t on) {
+    uint8_t* p = static_cast<uint8_t*>(base);
+    return enqueue_batch(c, jobs, B, reinterpret_cast<const hwc::JobDesc*>(p),
+                         reinterpret_cast<const hwc::HistJob*>(p + hist_at),
+                         reinterpret_cast<const hwc::BucketJob*>(p + bucket_at), set, flags, on);
+  };
   if ((rc = order_begin(c, set, s))) return rc;
   const bool use_graph = !(flags & HWC_NO_GRAPH) && !c->profile;
   if (!use_graph) {
@@ -1737,15 +1793,14 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
       if (sl.h) HIPX(c, hipHostFree(sl.h));
       sl.p = sl.h = nullptr;
       sl.bytes = 0;
-      const size_t want = std::max<size_t>(jbytes, 64 * (sizeof(hwc::JobDesc) + sizeof(hwc::HistJob)));
+      const size_t want = std::max<size_t>(jbytes, 64 * (sizeof(hwc::JobDesc) + sizeof(hwc::HistJob) + sizeof(hwc::BucketJob)));
       HIPX(c, hipMalloc(&sl.p, want));
       HIPX(c, hipHostMalloc(&sl.h, want, hipHostMallocDefault));
       sl.bytes = want;
     }
     std::memcpy(sl.h, desc.data(), jbytes);
     HIPX(c, hipMemcpyAsync(sl.p, sl.h, jbytes, hipMemcpyHostToDevice, s));
-    rc = enqueue_batch(c, jobs, B, static_cast<const hwc::JobDesc*>(sl.p),
-                       reinterpret_cast<const hwc::HistJob*>(static_cast<uint8_t*>(sl.p) + jobs_bytes), set, flags, s);
+    rc = enqueue_at(sl.p, s);
     if (rc) return rc;
     HIPX(c, hipEventRecord(sl.done, s));
     sl.used = true;
@@ -1779,9 +1834,7 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     return fail(c, HWC_ERR_DEVICE, std::string("job copy: ") + hipGetErrorString(me));
   }
   HIPX(c, hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-  rc = enqueue_batch(c, jobs, B, static_cast<const hwc::JobDesc*>(ge.jobs),
-                     reinterpret_cast<const hwc::HistJob*>(static_cast<uint8_t*>(ge.jobs) + jobs_bytes), set, flags,
-                     c->stream);
+  rc = enqueue_at(ge.jobs, c->stream);
   hipGraph_t graph = nullptr;
   hipError_t ee = hipStreamEndCapture(c->stream, &graph);
   ge.graph = graph;
@@ -2228,6 +2281,7 @@ int hwc_ctx_create(int device, uint64_t hbm_budget_bytes, hwc_ctx** out) {
     if ((e = hwc::prepare_kernels()) != hipSuccess) return create_fail(e, "kernel attributes");
     if ((e = hwc::prepare_vcount()) != hipSuccess) return create_fail(e, "kernel attributes");
     if ((e = hwc::prepare_hist_small()) != hipSuccess) return create_fail(e, "kernel attributes");
+    if ((e = hwc::prepare_bucket_small()) != hipSuccess) return create_fail(e, "kernel attributes");
     if ((e = hipMalloc(reinterpret_cast<void**>(&c->d_err), 256)) != hipSuccess) return create_fail(e, "hipMalloc");
     for (auto& st : c->sets)
       if ((e = hipEventCreateWithFlags(&st.ev, hipEventDisableTiming)) != hipSuccess)

@@ -10,6 +10,7 @@
 #include "count_entry.h"
 #include "count_impl.h"
 #include "plan.h"
+#include "rows.h"
 
 namespace hwc {
 
@@ -24,19 +25,6 @@ __global__ void fill_u32_kernel(uint32_t* p, uint32_t v, uint64_t n) {
 // ----------------------------------------------------------------------------
 // classification: validate rows, compute the pattern of each row and the
 // number of rows per pattern.
-
-// hist[pat] += 1 for every active lane, one LDS atomic per distinct pattern in
-// the wave (rows of a wave mostly share one or two patterns, so per-lane
-// atomics would serialize on the same address).
-__device__ __forceinline__ void wave_count(uint32_t* hist, uint32_t pat, bool active) {
-  uint64_t left = __ballot(active);
-  while (left) {
-    const uint32_t leader = uniform((uint32_t)__builtin_amdgcn_readlane((int)pat, (int)__builtin_ctzll(left)));
-    const uint64_t same = __ballot(active && pat == leader);
-    if ((threadIdx.x & (kWave - 1)) == (uint32_t)__builtin_ctzll(left)) atomicAdd(&hist[leader], (uint32_t)__popcll(same));
-    left &= ~same;
-  }
-}
 
 template <typename CT>
 __global__ __launch_bounds__(256) void classify_kernel(const CT* __restrict__ codes, uint64_t n, uint32_t q,
@@ -109,7 +97,6 @@ __global__ __launch_bounds__(256) void shift_kernel(const CT* __restrict__ in, u
                                                     uint32_t* __restrict__ err, uint32_t qm) {
   extern __shared__ uint32_t sh32[];
   constexpr uint32_t npat = 1u << NC;
-  constexpr uint32_t NW = shift_tmat_row_words(NC);
   const uint32_t qq = q * q, words = DOT ? 0u : (qq * q + 3) / 4;
   uint32_t* hist = sh32 + (words + 3) / 4 * 4;     // after the step table
   for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) sh32[i] = step[i];
@@ -126,86 +113,20 @@ __global__ __launch_bounds__(256) void shift_kernel(const CT* __restrict__ in, u
     const uint64_t r = w0 + (threadIdx.x & (kWave - 1));
     const bool live = r < n;
     CT raw[NC];
-    uint32_t c[NC];
-    bool valid = live;
 #pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      raw[i] = live ? in[r * NC + i] : (CT)0;
-      const int v = (int)raw[i];
-      valid = valid && v >= 0 && v < (int)q;
-      c[i] = (v >= 0 && v < (int)q) ? (uint32_t)v : 0u;
-    }
-    const uint32_t d = c[NC - 1] ? NC - 1 : NC - 2;
-    bool need = false;
-#pragma unroll
-    for (int i = 0; i < NC - 1; ++i) need = need || ((uint32_t)i < d && c[i] == 0);
-    need = need && valid && c[d] != 0;
-    bool done = false;
+    for (int i = 0; i < NC; ++i) raw[i] = live ? in[r * NC + i] : (CT)0;
     uint32_t w[NC];
-#pragma unroll
-    for (int i = 0; i < NC; ++i) w[i] = c[i];
-    uint32_t cp[NW];
-    if constexpr (DOT) {
-#pragma unroll
-      for (uint32_t w = 0; w < NW; ++w) {
-        uint32_t word = 0;
-#pragma unroll
-        for (uint32_t b = 0; b < 4; ++b)
-          if (4 * w + b < (uint32_t)NC) word |= c[4 * w + b] << (8 * b);
-        cp[w] = word;
-      }
-    }
-    for (uint32_t t = 1; t < q && t <= kShiftTries; ++t) {
-      if (!__ballot(need && !done)) break;
-      uint32_t v[NC];
-      if constexpr (DOT) {
-        const uint32_t* Tt = tmat + t * shift_tmat_words(NC);
-#pragma unroll
-        for (int i = 0; i < NC - 1; ++i) {
-          uint32_t acc = 0;
-#pragma unroll
-          for (uint32_t w = (uint32_t)i / 4; w < NW; ++w)
-            acc = __builtin_amdgcn_udot4(Tt[i * NW + w], cp[w], acc, false);
-          v[i] = acc - __umul24(q, __umul24(acc, qm) >> 20);   // 24-bit products, full rate
-        }
-        v[NC - 1] = c[NC - 1];
-      } else {
-        const uint32_t base = t * qq;
-#pragma unroll
-        for (int i = 0; i < NC; ++i) v[i] = c[i];
-#pragma unroll
-        for (int k = 0; k < NC - 1; ++k) {
-#pragma unroll
-          for (int i = NC - 2; i >= k; --i) v[i] = tab[base + v[i] * q + v[i + 1]];
-        }
-      }
-      bool dense = true;
-#pragma unroll
-      for (int i = 0; i < NC - 1; ++i) dense = dense && ((uint32_t)i >= d || v[i] != 0);
-      if (need && !done && dense) {
-#pragma unroll
-        for (int i = 0; i < NC; ++i) w[i] = v[i];
-        done = true;
-      }
-    }
+    const bool done = translate_row<NC, CT, DOT>(raw, live, q, qm, tmat, tab, w);
     if (live) {
 #pragma unroll
       for (int i = 0; i < NC; ++i) out[r * NC + i] = done ? (CT)w[i] : raw[i];
     }
     if (pid) {
       // the pattern of the row as written (classify_kernel's rule)
-      uint32_t mask = 0;
       int o[NC];
 #pragma unroll
       for (int i = 0; i < NC; ++i) o[i] = done ? (int)w[i] : (int)raw[i];
-      const uint32_t dd = o[NC - 1] ? NC - 1 : NC - 2;
-#pragma unroll
-      for (int i = 0; i < NC; ++i) {
-        if (live && (o[i] < 0 || o[i] >= (int)q)) bad |= 1u;
-        if ((uint32_t)i < dd && o[i] != 0) mask |= 1u << i;
-      }
-      if (live && o[NC - 1] == 0 && o[NC - 2] == 0) bad |= 2u;
-      const uint32_t pat = (o[NC - 1] ? (1u << (NC - 1)) : 0u) | mask;
+      const uint32_t pat = row_pattern<NC>(o, q, live, bad);
       if (live) pid[r] = (uint16_t)pat;
       wave_count(hist, pat, live);
     }

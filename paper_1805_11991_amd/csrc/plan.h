@@ -165,6 +165,22 @@ struct HistJob {
   uint32_t n, g, q, pad;
 };
 
+// One request of the one-workgroup bucketing (bucket_small.hip).
+constexpr uint32_t kBucketSmallMax = 8192;
+struct BucketJob {
+  const void* codes;       // [n][2g+3] int8 or int16
+  void* out;               // dense translates of the rows (mode 1, 2)
+  const uint32_t* step;    // the plan's shift buffer (mode 1, 2)
+  uint32_t* perm;          // [n]
+  uint64_t* tiles;
+  uint32_t* ntiles;
+  uint32_t* queue;
+  uint32_t* acc;           // words to clear for tile parts
+  uint32_t acc_words;
+  uint32_t n, q, g, cb;
+  uint32_t mode;           // 0: rows as given; 1: translates, prime q; 2: translates by the step table
+};
+
 // One curve for the lane-per-x kernel: coefficient logs in F_{q^k} (M where
 // the coefficient is zero), degree d, M = q^k - 1.
 struct SingleDesc {
