@@ -46,8 +46,8 @@ hipError_t launch_bucket(int coeff_bytes, const void* codes, uint64_t n, uint32_
                          uint32_t* counts, uint32_t* err, uint32_t* bucket_start, uint32_t* tile_start,
                          uint32_t* cursor, uint32_t* ntiles, uint32_t* queue, uint64_t* tiles, uint32_t* perm,
                          uint64_t max_tiles, bool classified, hipStream_t s);
-hipError_t launch_batch(const JobDesc* jobs, uint32_t njobs, uint32_t gmax, uint32_t lds_bytes, uint32_t grid,
-                        uint32_t block, hipStream_t s);
+hipError_t launch_batch(const JobDesc* jobs, uint32_t njobs, const uint32_t* first, uint32_t gmax, uint32_t lds_bytes,
+                        uint32_t grid, uint32_t block, hipStream_t s);
 hipError_t occupancy_batch(uint32_t gmax, uint32_t block, uint32_t lds_bytes, int* blocks_per_cu);
 uint64_t hist_scratch_bytes(uint64_t n);
 hipError_t hist_run(const int32_t* N, const uint32_t* lam, uint64_t n, uint32_t g, uint32_t q, void* scratch,
@@ -205,13 +205,16 @@ struct JobSlot {          // job descriptors of a direct multi-plan launch
 };
 
 constexpr uint32_t kSmallStride = 4 * 2048 + 16;   // per-job bucketing words (u32)
-// Tile parts: a request whose top level sweeps at least this many points by
-// orbits has each tile's top-level sweep cut into 2^kPartLog parts, so that
-// the last tiles of a launch do not hold a few waves long after the rest of
-// the GPU has run dry (one 2^20-curve request at q = 293, g = 2: 80 -> 72 ms)
-// and a job of few tiles spreads over the waves in flight
+// Tile parts.  A request whose top level sweeps at least kPartMinPoints points
+// by orbits has every tile cut into 2^kPartLog parts, so that the last tiles of
+// a launch do not hold a few waves long after the rest of the GPU has run dry
+// (one 2^20-curve request at q = 293, g = 2: 80 -> 72 ms).  A request (or batch)
+// of fewer entries than the waves in flight want is cut further, down to
+// kPartPoints top-level points a part: there a wave's serial sweep is the time
+// (500 curves at g = 3, q = 13: 8 tiles of 112 us, now 128 parts in 37 us).
 constexpr uint32_t kPartMinPoints = 8192;
 constexpr uint32_t kPartLog = 3;
+constexpr uint32_t kPartMaxLog = 8;
 constexpr int kJobSlots = 4;
 
 // Scratch of the work enqueued on one stream.  Calls on different streams
@@ -1151,12 +1154,13 @@ int get_plan(hwc_ctx* c, uint32_t q, uint32_t g, uint32_t orbit, DevPlan** out) 
   P->tile_cost = 0;
   for (uint32_t j = 0; j < g; ++j)
     P->tile_cost += (double)D.lv[j].nx * (2 * g + 2) *
-                    (form[j] == hwc::kFormA   ? 1.0
-                     : form[j] == hwc::kFormC ? 1.5
-                     : form[j] == hwc::kFormE ? 2.0
-                     : form[j] == hwc::kFormF ? 3.0
-                     : form[j] == hwc::kFormG ? 2.5
-                                              : 6.0);
+                    (P->npath                 ? 0.9
+                     : form[j] == hwc::kFormA ? 1.0
+                     : form[j] == hwc::kFormC ? 1.3
+                     : form[j] == hwc::kFormE ? 2.5
+                     : form[j] == hwc::kFormG ? 4.0
+                     : form[j] == hwc::kFormF ? 6.0
+                                              : 12.0);
   P->last_use = ++c->tick;
   *out = P.get();
   c->plans[key] = std::move(P);
@@ -1267,14 +1271,36 @@ uint32_t persistent_grid(uint32_t resident, uint32_t block, uint64_t tiles) {
   return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(resident, need));
 }
 
-// log2 of the parts each tile's top-level sweep is cut into (kPartMinPoints):
-// orbit sweeps of the Zech path only (the point lists are explicit), not the
-// plain form (one launch per level, whole tiles)
-uint32_t part_log(const DevPlan* P, uint32_t flags) {
+// log2 of the parts each tile of a request is cut into (kPartMinPoints), when
+// an entry costing `cost` should cost at most `target`: orbit sweeps of the
+// Zech path only (the point lists are explicit), not the plain form (one launch
+// per level, whole tiles)
+uint32_t part_log(const DevPlan* P, uint32_t flags, double cost, double target) {
   if (P->vpath || !P->orbit || (flags & HWC_PLAIN)) return 0;
   const hwc::LevelDesc& top = P->desc.lv[P->g - 1];
-  return top.xs && top.nx >= kPartMinPoints ? kPartLog : 0;
+  if (!top.xs) return 0;
+  uint32_t pl = top.nx >= kPartMinPoints ? kPartLog : 0;
+  while (pl < kPartMaxLog && (top.nx >> pl) >= 2 * hwc::kPartPoints && cost > target * (double)(1u << pl)) ++pl;
+  return pl;
 }
+
+// ... of a single request of n rows: one entry for each of 16 waves a CU, two
+// where the top level sweeps thousands of points and a part's setup is small
+// beside its share (count kernel, one against two entries a wave: g = 4, q = 13,
+// 7098 points, 2^16 curves 1015 / 627 us; g = 3, q = 13, 728 points, 2^17 curves
+// 164 / 186 us).
+uint32_t part_log_single(const hwc_ctx* c, const DevPlan* P, uint32_t flags, uint64_t n) {
+  const double tiles = (double)((n + hwc::kWave - 1) / hwc::kWave);
+  const double entries = (P->desc.lv[P->g - 1].nx >= 6000 ? 32.0 : 16.0) * c->cus;
+  return part_log(P, flags, 1.0, tiles / entries);
+}
+
+// Rows up to which one workgroup buckets a request alone (bucket_small.hip: 9 us
+// at 500 rows, 110 us at 8192, against about 22 us for the five launches of the
+// many-workgroup kernels), and jobs of up to kBucketSmallMax rows from which on
+// a batch buckets them all in one launch instead of five launches each.
+constexpr uint32_t kBucketAlone = 1024;
+constexpr size_t kBucketTogether = 6;
 
 // The one-workgroup bucketing of n rows (out: their dense translates, or null).
 hwc::BucketJob bucket_job(const DevPlan* P, const void* codes, void* out, int cb, uint64_t n, uint32_t* perm,
@@ -1352,9 +1378,9 @@ int enqueue(hwc_ctx* c, DevPlan* P, const Scratch& S, const void* codes, int cb,
     return HWC_OK;
   }
   const bool shifted = P->d_shift && n > 0;
-  const uint32_t plog = S.acc && n > 0 ? part_log(P, flags) : 0u;
+  const uint32_t plog = S.acc && n > 0 ? part_log_single(c, P, flags, n) : 0u;
   const uint64_t acc_words = plog ? n * g + S.max_tiles : 0;
-  if (n <= hwc::kBucketSmallMax) {
+  if (n <= kBucketAlone) {
     HIPX(c, hwc::launch_bucket_small(bucket_job(P, codes, shifted ? S.tcodes : nullptr, cb, n, S.perm, S.tiles, S.ntiles,
                                                 S.queue, S.acc, acc_words),
                                      c->d_err, s));
@@ -1380,7 +1406,8 @@ int enqueue(hwc_ctx* c, DevPlan* P, const Scratch& S, const void* codes, int cb,
       // a tile per bucket's ragged end besides the full ones (translated rows
       // fall in a few buckets; more tiles are still all counted)
       const uint32_t block = P->npath ? P->nblock : P->block;
-      const uint32_t grid = persistent_grid(P->npath ? P->ngrid : P->grid, block, (n + hwc::kWave - 1) / hwc::kWave + 4);
+      const uint32_t grid = persistent_grid(P->npath ? P->ngrid : P->grid, block,
+                                            ((n + hwc::kWave - 1) / hwc::kWave + 4) << plog);
       HIPX(c, hwc::launch_count(P->npath ? P->ndesc : P->desc, P->npath ? P->d_ndesc : P->d_desc, cb, codes, S.perm,
                                 S.tiles, S.ntiles, S.queue, 0, g - 1, N, lam ? S.lv : nullptr, plog,
                                 plog ? S.acc : nullptr, plog ? S.acc + n * g : nullptr, grid, block, P->wpe, s));
@@ -1456,7 +1483,7 @@ int run_dev(hwc_ctx* c, uint32_t q, uint32_t g, const void* codes, int cb, uint6
   (void)reap(c, false);
   Scratch S;
   if ((rc = get_scratch(c, set, n, g, cb, needs_lv(P, flags, lam), hk != nullptr, needs_tcodes(P),
-                        part_log(P, flags) > 0, &S)))
+                        part_log_single(c, P, flags, n) > 0, &S)))
     return rc;
   const bool use_graph = !(flags & (HWC_PLAIN | HWC_NO_GRAPH)) && n > 0 && !c->profile;
   if ((rc = order_begin(c, set, s))) return rc;
@@ -1545,12 +1572,21 @@ struct BatchPlan {
   std::vector<uint32_t> plog;       // tile parts (log2) per sorted job
   std::vector<uint64_t> aoff;       // word offset of the job's part counts in bacc
   std::vector<hwc::HistJob> hjobs;  // histograms of one workgroup each (after the job descriptors in memory)
+  std::vector<uint32_t> first;        // first job of each workgroup (after those)
   std::vector<hwc::BucketJob> bjobs;  // bucketings of one workgroup each (after those)
+  uint32_t bucket_max = 0;          // most rows of a job that one workgroup buckets
   uint64_t ntot = 0, tiles_tot = 0, nhist = 0, tbytes = 0, nlv = 0, acc_words = 0;
 };
 
 
 constexpr uint64_t kNoShift = ~0ull;
+
+// Upper bound of a batch's descriptors: the jobs, their histograms and
+// bucketings, and the first job of each workgroup (at most 32 waves a CU, a
+// workgroup has at least four), each part padded to 16 bytes.
+size_t batch_desc_bytes(const hwc_ctx* c, size_t njobs) {
+  return njobs * (sizeof(hwc::JobDesc) + sizeof(hwc::HistJob) + sizeof(hwc::BucketJob)) + (size_t)c->cus * 8 * 4 + 64;
+}
 
 // Rows the batch kernel reads for sorted job r: the dense translates when its
 // plan has a step table, else the caller's rows.
@@ -1563,8 +1599,8 @@ const void* batch_rows(const ScratchSet& st, const hwc_job& J, const BatchPlan& 
 // matrix-product job as its own launches (ordered on the same stream; in a
 // captured graph they are nodes of the same graph).
 int enqueue_batch(hwc_ctx* c, const hwc_job* jobs, const BatchPlan& B, const hwc::JobDesc* d_jobs,
-                  const hwc::HistJob* d_hjobs, const hwc::BucketJob* d_bjobs, int set, uint32_t flags,
-                  hipStream_t s) {
+                  const hwc::HistJob* d_hjobs, const hwc::BucketJob* d_bjobs, const uint32_t* d_first, int set,
+                  uint32_t flags, hipStream_t s) {
   const ScratchSet& st = c->sets[set];
   const size_t nz = B.order.size();
   if (nz) {
@@ -1575,7 +1611,7 @@ int enqueue_batch(hwc_ctx* c, const hwc_job* jobs, const BatchPlan& B, const hwc
     HIPX(c, hwc::launch_bucket_small_batch(B.bjobs.data(), d_bjobs, (uint32_t)B.bjobs.size(), c->d_err, s));
     for (size_t r = 0; r < nz; ++r) {
       const hwc_job& J = jobs[B.order[r]];
-      if (J.n <= hwc::kBucketSmallMax) continue;
+      if (J.n <= B.bucket_max) continue;
       const DevPlan* P = B.plans[B.order[r]];
       uint32_t* sm = small + r * kSmallStride;
       const void* rows = batch_rows(st, J, B, r);
@@ -1594,7 +1630,7 @@ int enqueue_batch(hwc_ctx* c, const hwc_job* jobs, const BatchPlan& B, const hwc
         HIPX(c, hwc::launch_fill(static_cast<uint32_t*>(st.bacc.p) + B.aoff[r], 0, J.n * J.g + B.max_tiles[r], s));
     }
     for (const BatchSeg& G : B.segs)
-      HIPX(c, hwc::launch_batch(d_jobs + G.begin, (uint32_t)(G.end - G.begin), G.gmax, G.lds, G.grid, G.block, s));
+      HIPX(c, hwc::launch_batch(d_jobs + G.begin, (uint32_t)(G.end - G.begin), d_first, G.gmax, G.lds, G.grid, G.block, s));
     HIPX(c, hwc::launch_hist_small_batch(d_hjobs, (uint32_t)B.hjobs.size(), c->d_err, s));
     for (size_t r = 0; r < nz; ++r) {
       const hwc_job& J = jobs[B.order[r]];
@@ -1669,6 +1705,15 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
   std::stable_sort(B.order.begin(), B.order.end(),
                    [&](size_t a, size_t b) { return B.plans[a]->tile_cost > B.plans[b]->tile_cost; });
   const size_t nz = B.order.size();
+  // tile parts: eight entries of about equal work for each of 16 waves a CU,
+  // where the jobs have the points
+  double work = 0;
+  auto job_tiles = [&](size_t r) { return (jobs[B.order[r]].n + hwc::kWave - 1) / hwc::kWave; };
+  for (size_t r = 0; r < nz; ++r) work += B.plans[B.order[r]]->tile_cost * (double)job_tiles(r);
+  for (size_t r = 0; r < nz; ++r) {
+    const DevPlan* P = B.plans[B.order[r]];
+    B.plog.push_back(jobs[B.order[r]].n ? part_log(P, flags, P->tile_cost, work / (128.0 * c->cus)) : 0u);
+  }
   // one launch over every job: the workgroup holds the largest image, the
   // kernel the largest genus, and the block size is the one that keeps the
   // most waves busy -- resident, and no more than there are tiles -- the
@@ -1687,7 +1732,7 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
       G.gmax = std::max(G.gmax, P->g);
     }
     uint64_t tiles = 0;
-    for (size_t k = G.begin; k < G.end; ++k) tiles += (jobs[B.order[k]].n + hwc::kWave - 1) / hwc::kWave + 4;
+    for (size_t k = G.begin; k < G.end; ++k) tiles += (job_tiles(k) + 4) << B.plog[k];
     int64_t best = -1;
     int bpc_best = 1;
     for (uint32_t b : {256u, 512u, 1024u}) {
@@ -1702,6 +1747,17 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     }
     G.grid = persistent_grid((uint32_t)(c->cus * bpc_best), G.block, tiles);
     B.segs.push_back(G);
+    // each workgroup's first job: workgroups in proportion to the jobs' work
+    double upto = 0;
+    size_t at = 0;
+    for (uint32_t w = 0; w < G.grid; ++w) {
+      const double want = (w + 0.5) * work / G.grid;
+      while (at + 1 < nz && upto + B.plans[B.order[at]]->tile_cost * (double)job_tiles(at) <= want) {
+        upto += B.plans[B.order[at]]->tile_cost * (double)job_tiles(at);
+        ++at;
+      }
+      B.first.push_back((uint32_t)at);
+    }
   }
   for (size_t r = 0; r < nz; ++r) {
     const hwc_job& J = jobs[B.order[r]];
@@ -1711,8 +1767,7 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     B.max_tiles.push_back(mt);
     B.ntot += J.n;
     B.tiles_tot += mt;
-    const uint32_t pl = part_log(B.plans[B.order[r]], flags);
-    B.plog.push_back(pl);
+    const uint32_t pl = B.plog[r];
     B.aoff.push_back(B.acc_words);
     if (pl) B.acc_words += J.n * J.g + mt;
     if (B.plans[B.order[r]]->d_shift && J.n > 0) {
@@ -1736,6 +1791,9 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
   if (B.nhist && (rc = ensure(c, set, st.hist, hwc::hist_scratch_bytes(B.nhist)))) return rc;
   if (B.nlv && (rc = ensure(c, set, st.lv, B.nlv * 4))) return rc;
   if (B.acc_words && (rc = ensure(c, set, st.bacc, B.acc_words * 4))) return rc;
+  size_t nsmall = 0;
+  for (size_t r = 0; r < nz; ++r) nsmall += jobs[B.order[r]].n <= hwc::kBucketSmallMax;
+  B.bucket_max = nsmall >= kBucketTogether ? hwc::kBucketSmallMax : kBucketAlone;
   std::vector<hwc::JobDesc> hj(std::max<size_t>(nz, 1));
   for (size_t r = 0; r < nz; ++r) {
     const hwc_job& J = jobs[B.order[r]];
@@ -1752,9 +1810,10 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     hj[r].cb = (uint32_t)J.coeff_bytes;
     hj[r].g = J.g;
     hj[r].plog = B.plog[r];
+    hj[r].cost = (float)(P->tile_cost / (double)(1u << B.plog[r]));
     hj[r].acc = B.plog[r] ? static_cast<uint32_t*>(st.bacc.p) + B.aoff[r] : nullptr;
     hj[r].done = B.plog[r] ? hj[r].acc + J.n * J.g : nullptr;
-    if (J.n <= hwc::kBucketSmallMax) {
+    if (J.n <= B.bucket_max) {
       const bool shifted = hj[r].codes != J.d_coeffs;
       B.bjobs.push_back(bucket_job(P, J.d_coeffs, shifted ? const_cast<void*>(hj[r].codes) : nullptr, J.coeff_bytes,
                                    J.n, const_cast<uint32_t*>(hj[r].perm), const_cast<uint64_t*>(hj[r].tiles),
@@ -1773,12 +1832,14 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
   append(hj.data(), hj.size() * sizeof(hwc::JobDesc));
   const size_t hist_at = append(B.hjobs.data(), B.hjobs.size() * sizeof(hwc::HistJob));
   const size_t bucket_at = append(B.bjobs.data(), B.bjobs.size() * sizeof(hwc::BucketJob));
+  const size_t first_at = append(B.first.data(), B.first.size() * 4);
   const size_t jbytes = desc.size();
   auto enqueue_at = [&](void* base, hipStream_t on) {
     uint8_t* p = static_cast<uint8_t*>(base);
     return enqueue_batch(c, jobs, B, reinterpret_cast<const hwc::JobDesc*>(p),
                          reinterpret_cast<const hwc::HistJob*>(p + hist_at),
-                         reinterpret_cast<const hwc::BucketJob*>(p + bucket_at), set, flags, on);
+                         reinterpret_cast<const hwc::BucketJob*>(p + bucket_at),
+                         reinterpret_cast<const uint32_t*>(p + first_at), set, flags, on);
   };
   if ((rc = order_begin(c, set, s))) return rc;
   const bool use_graph = !(flags & HWC_NO_GRAPH) && !c->profile;
@@ -1793,7 +1854,7 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
       if (sl.h) HIPX(c, hipHostFree(sl.h));
       sl.p = sl.h = nullptr;
       sl.bytes = 0;
-      const size_t want = std::max<size_t>(jbytes, 64 * (sizeof(hwc::JobDesc) + sizeof(hwc::HistJob) + sizeof(hwc::BucketJob)));
+      const size_t want = std::max<size_t>(jbytes, batch_desc_bytes(c, 64));
       HIPX(c, hipMalloc(&sl.p, want));
       HIPX(c, hipHostMalloc(&sl.h, want, hipHostMallocDefault));
       sl.bytes = want;
@@ -2782,7 +2843,7 @@ int hwc_ctx_reserve(hwc_ctx* c, uint64_t max_curves, uint32_t max_jobs, void* st
   if ((rc = ensure(c, set, st.bsmall, J * kSmallStride * 4))) return rc;
   if ((rc = ensure(c, set, st.btcodes, N * (2 * hwc::kMaxG + 3) * 2 + J * 256))) return rc;
   if ((rc = ensure(c, set, st.bacc, (N * hwc::kMaxG + tiles) * 4))) return rc;
-  const size_t jbytes = std::max<size_t>(J, 64) * sizeof(hwc::JobDesc);
+  const size_t jbytes = batch_desc_bytes(c, std::max<size_t>(J, 64));
   for (auto& sl : st.slots) {
     if (sl.bytes >= jbytes) continue;
     if (sl.used) HIPX(c, hipEventSynchronize(sl.done));

@@ -22,9 +22,9 @@ struct CountEntry {
                            const uint32_t* perm, const uint64_t* tiles, const uint32_t* ntiles, uint32_t* queue,
                            uint32_t lo, uint32_t hi, int32_t* outN, uint32_t* outLv, uint32_t plog, uint32_t* acc,
                            uint32_t* done, uint32_t grid, uint32_t block, uint32_t wpe, hipStream_t s);
-  // batch_kernel<G> over njobs jobs, image slot of `slot` bytes
-  static hipError_t batch(const JobDesc* jobs, uint32_t njobs, uint32_t slot, uint32_t grid, uint32_t block,
-                          hipStream_t s);
+  // batch_kernel<G> over njobs jobs, image slot of `slot` bytes; first: each workgroup's first job
+  static hipError_t batch(const JobDesc* jobs, uint32_t njobs, const uint32_t* first, uint32_t slot, uint32_t grid,
+                          uint32_t block, hipStream_t s);
   static hipError_t occupancy(int coeff_bytes, uint32_t block, uint32_t lds_bytes, uint32_t wpe, int* blocks_per_cu);
   static hipError_t occupancy_batch(uint32_t block, size_t lds_bytes, int* blocks_per_cu);
   // lets the kernels use the whole LDS image budget and checks that they

@@ -994,10 +994,10 @@ __device__ __forceinline__ void assemble(const PlanDesc& P, const uint32_t (&lv)
 }
 
 // One tile (up to 64 curves of one pattern) through levels lvl_lo..lvl_hi.
-// With plog > 0 this is part `part` of tile `tile`: the levels below the top
-// belong to part 0, the top level's points are shared out (count_level); the
-// part adds its counts into acc, and the tile's last part to finish reads the
-// sums back and assembles N.
+// With plog > 0 this is part `part` of tile `tile`: the levels' points are shared
+// out over the parts (count_level), each share of at least kPartPoints points;
+// the part adds its counts into acc, and the tile's last part to finish reads
+// the sums back and assembles N.
 template <int G, typename CT>
 __device__ __forceinline__ void process_tile(const PlanDesc& P, uint32_t lb, const CT* __restrict__ codes,
                                              const uint32_t* __restrict__ perm, uint64_t w, uint32_t lvl_lo,
@@ -1031,12 +1031,21 @@ __device__ __forceinline__ void process_tile(const PlanDesc& P, uint32_t lb, con
   for (int j = 0; j < G; ++j) lv[j] = 0;
 #pragma unroll 1
   for (uint32_t j = lvl_lo; j <= lvl_hi; ++j) {
-    const bool shared = j + 1 == (uint32_t)G;
-    if (part && !shared) continue;
+    // with parts: every part takes its share of the top level's points; a level
+    // below is shared out over 2^slog of them, the first of which is another
+    // for each level
+    const bool is_top = j + 1 == (uint32_t)G;
+    uint32_t share = part, slog = plog;
+    if (plog && !is_top) {
+      const uint32_t pts = sload(&P.lv[j].nx, 0) / kPartPoints;
+      slog = pts < 2u ? 0u : min(plog, 31u - (uint32_t)__builtin_clz(pts));
+      share = (part + ((uint32_t)G - 1u - j) * kPartStep) & ((1u << plog) - 1u);
+      if (share >> slog) continue;
+    }
     uint32_t v = 0;
     bool norm = false;
     if constexpr (G == 2) {
-      if (shared) {
+      if (is_top) {
         const NormDesc D = load_norm(P);
         if (D.kind) {
           norm = true;
@@ -1048,7 +1057,7 @@ __device__ __forceinline__ void process_tile(const PlanDesc& P, uint32_t lb, con
       }
     }
     if (!norm)
-      v = count_level<G>(load_level(P, j), lb, code, top, mask, shared ? part : 0u, shared ? plog : 0u);
+      v = count_level<G>(load_level(P, j), lb, code, top, mask, share, slog);
 #pragma unroll
     for (int k = 0; k < G; ++k) lv[k] = (uint32_t)k == j ? v : lv[k];
   }
@@ -1059,11 +1068,16 @@ __device__ __forceinline__ void process_tile(const PlanDesc& P, uint32_t lb, con
       for (int k = 0; k < G; ++k)
         if (lv[k]) atomicAdd(acc + (uint64_t)curve * G + k, lv[k]);
     }
-    __threadfence();
+    // Parts of a tile meet through device-scope atomics only (adds above, the
+    // loads below), which no L2 holds back, so it is enough that this wave's
+    // adds are done before it counts itself: a wait, not a fence, which
+    // writes back the L2 for every part (g = 3, q = 13, 2^16 curves: 261 us
+    // with the fences, 191 without)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     uint32_t prior = 0;
     if (lane == 0) prior = atomicAdd(done + tile, 1u);
     if (uniform(prior) != (1u << plog) - 1u) return;
-    __threadfence();
+    asm volatile("" ::: "memory");
 #pragma unroll
     for (int k = 0; k < G; ++k)
       lv[k] = __hip_atomic_load(acc + (uint64_t)curve * G + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1159,30 +1173,58 @@ __device__ __forceinline__ void process_job_tile(const JobDesc& J, uint32_t lb, 
 #undef HWC_JOB
 }
 
-// One persistent launch over the jobs of a batch, taken in the order given
-// (most expensive tiles first).  Every wave pops tiles of the current job from
-// the job's own queue and moves to the next job when that queue is empty; a
-// workgroup restages its LDS image only when the next job that still has
-// tiles uses another plan, and only there waits at barriers.  slot: byte
-// offset, past every image, of the word that broadcasts whether a job still
-// has tiles (inside the dynamic block, so the kernel has no static LDS).
+// The open job with the most work left (entries left times their cost), or ~0.
+// One wave; the factor between 1 and 2, different for every workgroup, keeps
+// workgroups that finish together from all choosing the same job.
+__device__ __forceinline__ uint32_t next_job(const JobDesc* __restrict__ jobs, uint32_t njobs) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  uint64_t best = 0;
+  for (uint32_t base = 0; base < njobs; base += kWave) {
+    const uint32_t k = base + lane;
+    if (k < njobs) {
+      const JobDesc& J = jobs[k];
+      const uint32_t nt = *J.ntiles << J.plog;
+      const uint32_t at = __hip_atomic_load(J.queue, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (at < nt) {
+        const uint32_t mix = ((blockIdx.x * 0x9E3779B1u + k * 0x85EBCA6Bu) >> 24) + 256u;
+        const float left = (float)(nt - at) * J.cost * (float)mix;
+        const uint64_t key = ((uint64_t)__float_as_uint(left) << 32) | (k + 1u);   // positive floats order as integers
+        best = key > best ? key : best;
+      }
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const uint64_t o = __shfl_xor(best, off);
+    best = o > best ? o : best;
+  }
+  return (uint32_t)best - 1u;
+}
+
+// One persistent launch over the jobs of a batch.  Each workgroup starts at the
+// job that the host gave it (workgroups in proportion to the jobs' work, so
+// that most stage one image only), its waves pop the job's tiles until its
+// queue is empty, and it goes on to the open job with the most work left,
+// restaging its LDS image where that one has another plan.  (Taking the jobs
+// one after another with every workgroup, each image was staged 256 times and
+// every wave popped every queue: 71 jobs of 8192 curves took 5.6 ms, now 4.3;
+// 32 mixed jobs of up to 8192 curves, their tiles in more parts, 4.0 and 0.6.)  slot: byte
+// offset, past every image, of the word that broadcasts the next job (inside
+// the dynamic block, so the kernel has no static LDS).
 template <int GMAX>
 __global__ __launch_bounds__(1024) void batch_kernel(const JobDesc* __restrict__ jobs, uint32_t njobs,
-                                                     uint32_t slot) {
+                                                     const uint32_t* __restrict__ first, uint32_t slot) {
   extern __shared__ uint32_t lds32[];
-  uint32_t& sh_open = *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(lds32) + slot);
+  uint32_t& sh_next = *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(lds32) + slot);
   constexpr uint32_t lb = kImageBase;
   const uint32_t lane = threadIdx.x & (kWave - 1);
   const PlanDesc* staged = nullptr;
-  for (uint32_t k = 0; k < njobs; ++k) {
+  uint32_t k = uniform(first[blockIdx.x]);
+  while (k < njobs) {
     const JobDesc& J = jobs[k];
     const uint32_t nt = *J.ntiles << J.plog;   // queue entries: tiles, or parts of tiles
     const PlanDesc* P = J.plan;
-    if (P != staged) {
-      __syncthreads();   // every wave is done with the image staged so far
-      if (threadIdx.x == 0) sh_open = atomicAdd(J.queue, 0u) < nt ? 1u : 0u;
-      __syncthreads();
-      if (!sh_open) continue;   // nothing left here: no restaging
+    if (P != staged) {   // every wave is done with the image staged so far (the barrier below)
       stage_image(lds32, P->image, P->image_bytes);
       __syncthreads();
       staged = P;
@@ -1194,6 +1236,14 @@ __global__ __launch_bounds__(1024) void batch_kernel(const JobDesc* __restrict__
       if (t >= nt) break;
       process_job_tile<GMAX>(J, lb, t);
     }
+    __syncthreads();
+    if (threadIdx.x < kWave) {
+      const uint32_t nx = next_job(jobs, njobs);
+      if (threadIdx.x == 0) sh_next = nx;
+    }
+    __syncthreads();
+    k = uniform(sh_next);
+    __syncthreads();   // the word is read before a later round writes it
   }
 }
 

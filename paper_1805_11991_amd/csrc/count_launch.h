@@ -29,9 +29,9 @@ hipError_t CountEntry<G>::launch(const PlanDesc& P, const PlanDesc* dP, int coef
 }
 
 template <int G>
-hipError_t CountEntry<G>::batch(const JobDesc* jobs, uint32_t njobs, uint32_t slot, uint32_t grid, uint32_t block,
-                                hipStream_t s) {
-  hipLaunchKernelGGL(batch_kernel<G>, dim3(grid), dim3(block), slot + 16, s, jobs, njobs, slot);
+hipError_t CountEntry<G>::batch(const JobDesc* jobs, uint32_t njobs, const uint32_t* first, uint32_t slot,
+                                uint32_t grid, uint32_t block, hipStream_t s) {
+  hipLaunchKernelGGL(batch_kernel<G>, dim3(grid), dim3(block), slot + 16, s, jobs, njobs, first, slot);
   return hipGetLastError();
 }
 

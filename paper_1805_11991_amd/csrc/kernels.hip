@@ -607,14 +607,14 @@ hipError_t launch_count(const PlanDesc& P, const PlanDesc* dP, int coeff_bytes, 
 #undef HWC_CASE
 }
 
-hipError_t launch_batch(const JobDesc* jobs, uint32_t njobs, uint32_t gmax, uint32_t lds_bytes, uint32_t grid,
-                        uint32_t block, hipStream_t s) {
+hipError_t launch_batch(const JobDesc* jobs, uint32_t njobs, const uint32_t* first, uint32_t gmax, uint32_t lds_bytes,
+                        uint32_t grid, uint32_t block, hipStream_t s) {
   const uint32_t slot = (lds_bytes + 15u) & ~15u;
   switch (gmax) {
-    case 1: return CountEntry<1>::batch(jobs, njobs, slot, grid, block, s);
-    case 2: return CountEntry<2>::batch(jobs, njobs, slot, grid, block, s);
-    case 3: return CountEntry<3>::batch(jobs, njobs, slot, grid, block, s);
-    case 4: return CountEntry<4>::batch(jobs, njobs, slot, grid, block, s);
+    case 1: return CountEntry<1>::batch(jobs, njobs, first, slot, grid, block, s);
+    case 2: return CountEntry<2>::batch(jobs, njobs, first, slot, grid, block, s);
+    case 3: return CountEntry<3>::batch(jobs, njobs, first, slot, grid, block, s);
+    case 4: return CountEntry<4>::batch(jobs, njobs, first, slot, grid, block, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -228,6 +228,11 @@ struct VPlanDesc {
   VLevel lv[kMaxG];
 };
 
+// Tile parts: least points of a part's share of a level, and the distance
+// between the first parts of neighbouring levels (odd: no two start alike).
+constexpr uint32_t kPartPoints = 48;
+constexpr uint32_t kPartStep = 5;
+
 // One request of a multi-plan launch (device memory).
 struct JobDesc {
   const PlanDesc* plan;   // device copy of the job's plan
@@ -238,11 +243,12 @@ struct JobDesc {
   uint32_t* queue;        // the job's tile queue (set to 0 by the bucketing)
   int32_t* outN;          // [n][g]
   uint32_t cb, g;         // code bytes, genus
-  // The top level's sweep of every tile cut into 2^plog parts (queue entry
-  // u: tile u >> plog, part u & (2^plog - 1)) when a job has few tiles for
-  // the waves in flight: the parts add their level counts into acc and the
-  // last part of a tile (counted in done) assembles N.  plog = 0: whole tiles.
+  // Every tile's sweep cut into 2^plog parts (queue entry u: tile u >> plog,
+  // part u & (2^plog - 1)) when a job has few tiles for the waves in flight:
+  // the parts add their level counts into acc and the last part of a tile
+  // (counted in done) assembles N.  plog = 0: whole tiles.
   uint32_t plog;
+  float cost;             // relative work of one queue entry
   uint32_t* acc;          // [n][g] packed level counts (zero before the launch)
   uint32_t* done;         // [tiles] parts finished (zero before the launch)
 };
