@@ -2184,6 +2184,8 @@ int run_map(hwc_ctx* c, uint32_t q, uint32_t g, int32_t* keys, uint64_t* counts,
 
 // ---- one curve over large fields (Table 1): lane-per-x ----
 
+constexpr size_t kMaxSingleFields = 8;
+
 int single_tables(hwc_ctx* c, uint32_t p, uint32_t e, uint32_t k, std::shared_ptr<FieldEntry>* fe_out,
                   SingleTabs** out, double* build_ms, double* upload_ms) {
   int rc = HWC_OK;
@@ -2201,7 +2203,6 @@ int single_tables(hwc_ctx* c, uint32_t p, uint32_t e, uint32_t k, std::shared_pt
     return HWC_OK;
   }
   // keep the tables of a few fields only (each can be tens of MB)
-  constexpr size_t kMaxSingleFields = 8;
   while (c->single.size() >= kMaxSingleFields) {
     HIPX(c, hipDeviceSynchronize());
     auto victim = c->single.begin();
@@ -2244,44 +2245,61 @@ int run_single(hwc_ctx* c, uint32_t q, uint32_t g, const int16_t* coeffs, uint32
   HIPX(c, hipSetDevice(c->device));
   const bool orbit = !(flags & HWC_FULL_SWEEP);
   const uint32_t d = coeffs[nc - 1] ? nc - 1 : nc - 2;
-  if ((rc = ensure_sync(c, c->hout, 64))) return rc;
-  unsigned long long* d_cnt = static_cast<unsigned long long*>(c->hout.p);
+  if ((rc = ensure_sync(c, c->hout, 8 * 24))) return rc;
+  unsigned long long* d_cnt = static_cast<unsigned long long*>(c->hout.p);   // zeros << 32 | nonsquares per level
   std::vector<uint64_t> z(kmax + 1), ns(kmax + 1), nx(kmax + 1);
   double build_ms = 0, upload_ms = 0, eval_ms = 0;
-  hipEvent_t ev0, ev1;
-  HIPX(c, hipEventCreate(&ev0));
-  HIPX(c, hipEventCreate(&ev1));
+  // every level's tables first, where they all stay resident together; then
+  // the levels are enqueued at once and waited for once
+  std::vector<std::shared_ptr<FieldEntry>> fe(kmax + 1);
+  std::vector<SingleTabs*> T(kmax + 1, nullptr);
+  const bool together = kmax <= kMaxSingleFields;
+  if (together)
+    for (uint32_t j = 1; j <= kmax; ++j)
+      if ((rc = single_tables(c, p, e, j, &fe[j], &T[j], &build_ms, &upload_ms))) return rc;
+  hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  if ((rc = take_event(c, &ev0))) return rc;
+  if ((rc = take_event(c, &ev1))) {
+    c->event_pool.push_back(ev0);
+    return rc;
+  }
+  unsigned long long host[24] = {};
+  auto wait = [&](uint32_t lo, uint32_t hi) {   // levels lo..hi are enqueued
+    if (hipEventRecord(ev1, c->stream) != hipSuccess ||
+        hipMemcpyAsync(host + lo - 1, d_cnt + lo - 1, 8 * (hi - lo + 1), hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
+        hipStreamSynchronize(c->stream) != hipSuccess)
+      return fail(c, HWC_ERR_DEVICE, "single-curve count failed");
+    float ms = 0;
+    (void)hipEventElapsedTime(&ms, ev0, ev1);
+    eval_ms += ms;
+    return HWC_OK;
+  };
   int out_rc = HWC_OK;
+  if (hwc::launch_fill(reinterpret_cast<uint32_t*>(d_cnt), 0, 2 * kmax, c->stream) != hipSuccess)
+    out_rc = fail(c, HWC_ERR_DEVICE, "single-curve count failed");
   for (uint32_t j = 1; j <= kmax && out_rc == HWC_OK; ++j) {
-    std::shared_ptr<FieldEntry> fe;
-    SingleTabs* T = nullptr;
-    if ((out_rc = single_tables(c, p, e, j, &fe, &T, &build_ms, &upload_ms))) break;
-    const hwc::Field& F = fe->F;
+    if (!together && (out_rc = single_tables(c, p, e, j, &fe[j], &T[j], &build_ms, &upload_ms))) break;
+    const hwc::Field& F = fe[j]->F;
     hwc::SingleDesc f{};
     f.M = (uint32_t)F.M;
     f.d = d;
     for (uint32_t i = 0; i < nc; ++i) f.lc[i] = F.emb[(uint32_t)coeffs[i]];
-    const uint64_t n = orbit ? T->nreps : F.M;
-    nx[j] = n;
-    unsigned long long host[2] = {0, 0};
-    if (hipMemsetAsync(d_cnt, 0, 16, c->stream) != hipSuccess ||
-        hipEventRecord(ev0, c->stream) != hipSuccess ||
-        hwc::launch_single(T->d_zech, orbit ? T->d_reps : nullptr, n, f, d_cnt, c->stream) != hipSuccess ||
-        hipEventRecord(ev1, c->stream) != hipSuccess ||
-        hipMemcpyAsync(host, d_cnt, 16, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
-        hipStreamSynchronize(c->stream) != hipSuccess) {
+    nx[j] = orbit ? T[j]->nreps : F.M;
+    if (((j == 1 || !together) && hipEventRecord(ev0, c->stream) != hipSuccess) ||
+        hwc::launch_single(T[j]->d_zech, orbit ? T[j]->d_reps : nullptr, nx[j], f, d_cnt + j - 1, c->stream) != hipSuccess) {
       out_rc = fail(c, HWC_ERR_DEVICE, "single-curve count failed");
       break;
     }
-    float ms = 0;
-    (void)hipEventElapsedTime(&ms, ev0, ev1);
-    eval_ms += ms;
-    z[j] = host[0];
-    ns[j] = host[1];
+    if (!together) out_rc = wait(j, j);
   }
-  (void)hipEventDestroy(ev0);
-  (void)hipEventDestroy(ev1);
+  if (together && out_rc == HWC_OK) out_rc = wait(1, kmax);
+  c->event_pool.push_back(ev0);
+  c->event_pool.push_back(ev1);
   if (out_rc) return out_rc;
+  for (uint32_t j = 1; j <= kmax; ++j) {
+    z[j] = host[j - 1] >> 32;
+    ns[j] = host[j - 1] & 0xFFFFFFFFu;
+  }
   // N_k (Sec. 1.1): affine points from the levels j | k (orbit sweep: weight j,
   // and a nonsquare of F_{q^j} is a square in F_{q^k} when k/j is even), plus
   // x = 0 and the points at infinity

@@ -183,6 +183,7 @@ struct BucketJob {
 
 // One curve for the lane-per-x kernel: coefficient logs in F_{q^k} (M where
 // the coefficient is zero), degree d, M = q^k - 1.
+constexpr uint32_t kSingleThreads = 512;
 struct SingleDesc {
   uint32_t lc[2 * kMaxG + 3];
   uint32_t d, M;
