@@ -1,4 +1,4 @@
-"""The one-workgroup histogram (requests of up to 8192 rows): sorted tuples and
+"""The one-workgroup and the dense histogram (the first for requests of up to 8192 rows): sorted tuples and
 multiplicities equal numpy's over the counts themselves, at the edges of its
 waves, of its keys per thread and of its range; few and many distinct tuples;
 a capacity below the need; the partition column; several jobs in one launch."""
@@ -69,6 +69,32 @@ def test_partition_column(ctx, curvegen_mod, q, g, n):
                          j["d_hist_len"])
     ctx.status()
     _check(j, np.concatenate([j["d_out_N"].cpu().numpy(), lam.cpu().numpy()[:, None]], axis=1))
+
+
+# past 8192 rows: dense cells where the keys are few (the largest key spaces that
+# fit and the smallest that do not), else the sort
+@pytest.mark.parametrize("q,g,n", [(5, 2, 8193), (13, 2, 70001), (3, 3, 40000), (7, 1, 9000), (5, 2, 300000),
+                                   (17, 2, 20000), (5, 3, 20000)])
+@pytest.mark.parametrize("partition", [False, True])
+def test_histogram_of_few_keys(ctx, curvegen_mod, q, g, n, partition):
+    import torch
+    j = _request(curvegen_mod, q, g, n, n, g + partition)
+    if partition:
+        lam = torch.zeros(n, dtype=torch.int32, device="cuda")
+        ctx.count_lambda_dev(q, g, j["d_coeffs"], j["d_out_N"], lam, j["d_hist_keys"], j["d_hist_counts"],
+                             j["d_hist_len"])
+    else:
+        ctx.count_curves_dev(q, g, j["d_coeffs"], j["d_out_N"], j["d_hist_keys"], j["d_hist_counts"], j["d_hist_len"])
+    ctx.status()
+    N = j["d_out_N"].cpu().numpy()
+    _check(j, np.concatenate([N, lam.cpu().numpy()[:, None]], axis=1) if partition else N)
+
+
+def test_few_keys_short_capacity(ctx, curvegen_mod):
+    j = _request(curvegen_mod, 5, 2, 9000, 17, 2)
+    ctx.count_curves_dev(5, 2, j["d_coeffs"], j["d_out_N"], j["d_hist_keys"], j["d_hist_counts"], j["d_hist_len"])
+    ctx.status()
+    _check(j, j["d_out_N"].cpu().numpy())
 
 
 @pytest.mark.parametrize("flags", [0, 8])
