@@ -253,7 +253,11 @@ struct hwc_ctx {
   Buf N, codes, hout;
   Buf mcodes, mN, mlam, mhk, mhc, mcj;   // map of eq. (1.2): one chunk of representatives
   std::map<std::tuple<uint32_t, uint32_t, uint32_t>, SingleTabs> single;   // one-curve tables
-  uint32_t* d_err = nullptr;
+  uint32_t* d_err = nullptr;        // row errors; 8 bytes in: the synchronous call's histogram length
+  // pinned staging of the synchronous host-buffer call: two upload buffers
+  // (double buffering), then the small results
+  uint8_t* h_stage = nullptr;
+  hipEvent_t stage_ev[2] = {nullptr, nullptr};
   std::list<GraphEntry> graphs;
   // scratch of the asynchronous calls, one set per stream (round robin past kSets)
   ScratchSet sets[kSets];
@@ -412,6 +416,52 @@ int ensure_sync(hwc_ctx* c, Buf& b, size_t bytes) {
   want = (want + 4095) & ~size_t(4095);
   HIPX(c, hipMalloc(&b.p, want));
   b.bytes = want;
+  return HWC_OK;
+}
+
+constexpr size_t kStageBytes = 1 << 20;    // one upload buffer
+constexpr uint64_t kStageHist = 4096;      // histogram entries returned with the error word
+
+int ensure_stage(hwc_ctx* c) {
+  if (!c->h_stage) {
+    const size_t bytes = 2 * kStageBytes + 64 + kStageHist * (8 + 4 * hwc::kMaxG);
+    HIPX(c, hipHostMalloc(reinterpret_cast<void**>(&c->h_stage), bytes, hipHostMallocDefault));
+  }
+  for (auto& e : c->stage_ev)
+    if (!e) HIPX(c, hipEventCreateWithFlags(&e, hipEventDisableTiming));
+  return HWC_OK;
+}
+
+// Every code in [0, q) and no row of degree below 2g + 1.
+bool rows_ok(const int16_t* coeffs, uint64_t n, uint32_t nc, uint32_t q) {
+  int16_t lo = 0, hi = 0;
+  for (uint64_t i = 0; i < n * nc; ++i) {
+    lo = std::min(lo, coeffs[i]);
+    hi = std::max(hi, coeffs[i]);
+  }
+  uint32_t low = 0;
+  for (uint64_t i = 0; i < n; ++i) low |= (uint32_t)((coeffs[i * nc + nc - 1] | coeffs[i * nc + nc - 2]) == 0);
+  return lo >= 0 && (uint32_t)hi < q && !low;
+}
+
+// Codes from the caller's memory to c->codes, as bytes when cb = 1, through the
+// two staging buffers: one is filled while the other is on its way.
+int upload_codes(hwc_ctx* c, const int16_t* coeffs, uint64_t count, int cb) {
+  const uint64_t per = kStageBytes / (uint64_t)cb;
+  uint8_t* dst = static_cast<uint8_t*>(c->codes.p);
+  for (uint64_t at = 0, k = 0; at < count; at += per, ++k) {
+    const uint64_t m = std::min(per, count - at);
+    uint8_t* buf = c->h_stage + (k & 1) * kStageBytes;
+    if (k >= 2) HIPX(c, hipEventSynchronize(c->stage_ev[k & 1]));
+    if (cb == 1) {
+      int8_t* o = reinterpret_cast<int8_t*>(buf);
+      for (uint64_t i = 0; i < m; ++i) o[i] = (int8_t)coeffs[at + i];
+    } else {
+      std::memcpy(buf, coeffs + at, m * 2);
+    }
+    HIPX(c, hipMemcpyAsync(dst + at * cb, buf, m * cb, hipMemcpyHostToDevice, c->stream));
+    HIPX(c, hipEventRecord(c->stage_ev[k & 1], c->stream));
+  }
   return HWC_OK;
 }
 
@@ -2402,6 +2452,9 @@ void hwc_ctx_destroy(hwc_ctx* c) {
       if (kv.second.d_reps) (void)hipFree(kv.second.d_reps);
     }
     if (c->d_err) (void)hipFree(c->d_err);
+    if (c->h_stage) (void)hipHostFree(c->h_stage);
+    for (auto e : c->stage_ev)
+      if (e) (void)hipEventDestroy(e);
     for (auto& ev : c->prof)
       for (auto e : ev) (void)hipEventDestroy(e);
     for (auto e : c->event_pool) (void)hipEventDestroy(e);
@@ -2466,12 +2519,16 @@ int hwc_count_curves(hwc_ctx* c, uint32_t q, uint32_t g, const int16_t* coeffs, 
   if (out_hist && (out_hist->g != g || (out_hist->capacity && (!out_hist->keys || !out_hist->counts))))
     return fail(c, HWC_ERR_ARG, "bad histogram descriptor");
   const uint32_t nc = 2 * g + 3;
-  // row checks on the host: range and degree
-  for (uint64_t i = 0; i < n; ++i) {
-    const int16_t* r = coeffs + i * nc;
-    for (uint32_t j = 0; j < nc; ++j)
-      if (r[j] < 0 || (uint32_t)r[j] >= q) return fail(c, HWC_ERR_COEFF_RANGE, "coefficient code out of range");
-    if (r[nc - 1] == 0 && r[nc - 2] == 0) return fail(c, HWC_ERR_DEGREE, "degree below 2g+1");
+  // row checks on the host: range and degree.  First over all rows at once (a
+  // loop the compiler vectorises); only a set that fails is looked at row by
+  // row for the first bad one.
+  if (!rows_ok(coeffs, n, nc, q)) {
+    for (uint64_t i = 0; i < n; ++i) {
+      const int16_t* r = coeffs + i * nc;
+      for (uint32_t j = 0; j < nc; ++j)
+        if (r[j] < 0 || (uint32_t)r[j] >= q) return fail(c, HWC_ERR_COEFF_RANGE, "coefficient code out of range");
+      if (r[nc - 1] == 0 && r[nc - 2] == 0) return fail(c, HWC_ERR_DEGREE, "degree below 2g+1");
+    }
   }
   HIPX(c, hipSetDevice(c->device));
   if (flags & HWC_VALIDATE) {
@@ -2491,33 +2548,48 @@ int hwc_count_curves(hwc_ctx* c, uint32_t q, uint32_t g, const int16_t* coeffs, 
     // device histogram sized to n (the most it can need), copied back up to cap
     if ((rc = ensure_sync(c, c->hout, std::max<uint64_t>(n, 1) * (g * 4 + 8) + 64))) return rc;
   }
-  if (n) HIPX(c, hipMemcpyAsync(c->codes.p, coeffs, n * nc * 2, hipMemcpyHostToDevice, c->stream));
-  HIPX(c, hwc::launch_fill(c->d_err, 0, 1, c->stream));
+  const int cb = q <= 127 ? 1 : 2;   // half the bytes over the bus and in the kernels
+  if ((rc = ensure_stage(c))) return rc;
+  if ((rc = upload_codes(c, coeffs, n * nc, cb))) return rc;
+  HIPX(c, hwc::launch_fill(c->d_err, 0, 4, c->stream));
   int32_t* dN = static_cast<int32_t*>(c->N.p);
   int32_t* dK = nullptr;
   uint64_t* dC = nullptr;
   if (want_hist) {
     uint8_t* base = static_cast<uint8_t*>(c->hout.p);
     dC = reinterpret_cast<uint64_t*>(base);
-    d_len = reinterpret_cast<uint64_t*>(base + std::max<uint64_t>(n, 1) * 8);
+    d_len = reinterpret_cast<uint64_t*>(c->d_err + 2);
     dK = reinterpret_cast<int32_t*>(base + std::max<uint64_t>(n, 1) * 8 + 64);
   }
-  rc = run_dev(c, q, g, c->codes.p, 2, n, dN, dK, dC, std::max<uint64_t>(n, 1), d_len, flags | HWC_NO_GRAPH,
+  rc = run_dev(c, q, g, c->codes.p, cb, n, dN, dK, dC, std::max<uint64_t>(n, 1), d_len, flags | HWC_NO_GRAPH,
                c->stream);
   if (rc) return rc;
-  uint32_t derr = 0;
-  HIPX(c, hipMemcpyAsync(&derr, c->d_err, 4, hipMemcpyDeviceToHost, c->stream));
+  // the error word, the length and the first entries of the histogram come
+  // back together: a short histogram needs no second wait
+  uint8_t* small = c->h_stage + 2 * kStageBytes;
+  uint8_t *hC = small + 64, *hK = hC + kStageHist * 8;
+  const uint64_t early = want_hist ? std::min<uint64_t>({cap, n, kStageHist}) : 0;
+  HIPX(c, hipMemcpyAsync(small, c->d_err, 16, hipMemcpyDeviceToHost, c->stream));
+  if (early) {
+    HIPX(c, hipMemcpyAsync(hC, dC, early * 8, hipMemcpyDeviceToHost, c->stream));
+    HIPX(c, hipMemcpyAsync(hK, dK, early * g * 4, hipMemcpyDeviceToHost, c->stream));
+  }
   if (out_N && n) HIPX(c, hipMemcpyAsync(out_N, dN, n * g * 4, hipMemcpyDeviceToHost, c->stream));
-  uint64_t len = 0;
-  if (want_hist) HIPX(c, hipMemcpyAsync(&len, d_len, 8, hipMemcpyDeviceToHost, c->stream));
   HIPX(c, hipStreamSynchronize(c->stream));
+  uint32_t derr = 0;
+  uint64_t len = 0;
+  std::memcpy(&derr, small, 4);
+  std::memcpy(&len, small + 8, 8);
   if (derr & 1u) return fail(c, HWC_ERR_COEFF_RANGE, "coefficient code out of range");
   if (derr & 2u) return fail(c, HWC_ERR_DEGREE, "degree below 2g+1");
   if (derr & 4u) return fail(c, HWC_ERR_DEVICE, "point count outside its histogram radix");
   if (want_hist) {
     out_hist->len = len;
     const uint64_t m = std::min(len, cap);
-    if (m) {
+    if (m <= early) {
+      if (m) std::memcpy(out_hist->counts, hC, m * 8);
+      if (m) std::memcpy(out_hist->keys, hK, m * g * 4);
+    } else {
       HIPX(c, hipMemcpyAsync(out_hist->keys, dK, m * g * 4, hipMemcpyDeviceToHost, c->stream));
       HIPX(c, hipMemcpyAsync(out_hist->counts, dC, m * 8, hipMemcpyDeviceToHost, c->stream));
       HIPX(c, hipStreamSynchronize(c->stream));
