@@ -342,11 +342,12 @@ int hwc_ctx_set_plan_option(hwc_ctx* ctx, uint32_t q, uint32_t g, uint32_t flags
  * x^m, plus ns single points), the LDS bytes of the plan, and mfma = 1 when
  * the plan counts by int8 matrix products (HWC_OPT_MFMA) instead of Zech
  * logarithms, 2 when it does so in the balanced form (p = 11, 13: one
- * 24-bit multiply-high per coordinate for the quotients).  At g = 2 and q >= 65 the orbit sweep's
- * persistent forms count level 2 by norms instead (f(x) as a pair over F_q,
- * the character of its norm read in F_q's Zech table) where that image fits
- * LDS and no option moves a level to device memory or turns the split off; the
- * description is that of the level's own table, which the plain form reads. */
+ * 24-bit multiply-high per coordinate for the quotients).  At g = 2 (primes
+ * q >= 37, prime powers q >= 81) the orbit sweep's persistent forms count by
+ * norms instead (f(x) in F_{q^2} as a pair over F_q, the character of its norm
+ * read in F_q's Zech table) where that image fits LDS and no option moves a
+ * level to device memory or turns the split off; the description is that of
+ * the level's own table, which the plain form reads. */
 typedef struct {
   uint32_t M, form, nx, weight, msplit, nt, ns, lds_bytes, mfma;
 } hwc_level_desc;

@@ -56,6 +56,11 @@ hipError_t hist_run(const int32_t* N, const uint32_t* lam, uint64_t n, uint32_t 
 bool hist_is_small(uint64_t n, uint32_t g, uint32_t q, bool lam);
 hipError_t launch_hist_small_batch(const HistJob* jobs, uint32_t njobs, uint32_t* err, hipStream_t s);
 hipError_t prepare_hist_small();
+hipError_t launch_norm(const PlanDesc& P, const PlanDesc* dP, int coeff_bytes, const void* codes, const uint32_t* perm,
+                       const uint64_t* tiles, const uint32_t* ntiles, uint32_t* queue, int32_t* outN, uint32_t* outLv,
+                       uint32_t plog, uint32_t* acc, uint32_t* done, uint32_t grid, uint32_t block, hipStream_t s);
+hipError_t occupancy_norm(uint32_t block, uint32_t lds_bytes, int* blocks_per_cu);
+hipError_t prepare_norm();
 hipError_t launch_bucket_small(const BucketJob& J, uint32_t* err, hipStream_t s);
 hipError_t launch_bucket_small_batch(const BucketJob* hjobs, const BucketJob* jobs, uint32_t njobs, uint32_t* err,
                                      hipStream_t s);
@@ -782,27 +787,28 @@ int build_vplan(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, uint32_t g, uint
   return HWC_OK;
 }
 
-// Least field that counts level 2 by norms (genus 2, orbit sweep, split
-// evaluation on, no level in device memory).  Every field from 67 on gained
-// (count kernel on 2^18 curves: 67 0.62 -> 0.44 ms, 81 0.81 -> 0.78, 101 1.31
-// -> 0.84, 293 19.2 -> 5.6); below, a translate's setup is spread over fewer
-// than 32 points, and the quotient constant of the integer translates,
-// 2^30 / q, no longer fits 24 bits.
-constexpr uint32_t kNormMinQ = 65;
+// Least fields that count level 2 by norms (genus 2, orbit sweep, split
+// evaluation on, no level in device memory): primes from 37 and prime powers
+// from 81 on, whose translates cost more.  Count kernel on 2^18 curves, level
+// table -> norms: 29 0.149 -> 0.195 ms, 37 0.238 -> 0.209, 61 0.540 -> 0.380,
+// 101 1.31 -> 0.80, 293 19.2 -> 5.7; 49 0.381 -> 0.399, 81 0.81 -> 0.72, 169
+// 3.15 -> 1.96.
+constexpr uint32_t kNormMinPrime = 37, kNormMinPower = 81;
 
 // The image of norm_impl.h for (q, 2), or an empty one when it does not fit.
-// Fills the offsets of D and the level descriptors' table offsets.
-std::vector<uint8_t> norm_image(const hwc::Field& F1, uint32_t q, bool fold, hwc::NormDesc* D, uint32_t* tab1,
-                                uint32_t* emb1) {
+// Fills the offsets of D.
+std::vector<uint8_t> norm_image(const hwc::Field& F1, uint32_t q, bool fold, hwc::NormDesc* D) {
   const uint32_t M = q - 1, H = M / 2, zrow = fold ? 2 * M : 3 * M, rows = zrow + 2 * M + 1;
+  // slots of 16 bytes below q = 65, where the quotient's constant, 2^32 / (q <<
+  // esh), would not fit 24 bits with 4
+  const uint32_t esh = q < 65 ? 4 : 2;
   uint32_t srow = 1;
   while (srow < 4 * M) srow *= 2;
   const uint32_t S = srow * hwc::kNormRow, nfin = 2 * srow + 2 * M;
-  const uint64_t need = (uint64_t)rows * hwc::kNormRow + align16(10 * M) + align16(4 * q) + align16(nfin);
+  const uint64_t need = (uint64_t)rows * hwc::kNormRow + align16(q << esh) + align16(nfin);
   if (need > kLdsLimit) return {};
   std::vector<uint8_t> img((size_t)need, 0);
   auto put32 = [&](size_t off, uint32_t v) { std::memcpy(img.data() + off, &v, 4); };
-  auto put16 = [&](size_t off, uint32_t v) { const uint16_t h = (uint16_t)v; std::memcpy(img.data() + off, &h, 2); };
   for (uint32_t r = 0; r < rows; ++r) {
     uint32_t v = 0;
     if (r < zrow) {
@@ -815,20 +821,13 @@ std::vector<uint8_t> norm_image(const hwc::Field& F1, uint32_t q, bool fold, hwc
     for (uint32_t b = 0; b < hwc::kNormRow; b += 4) put32((size_t)r * hwc::kNormRow + b, v);
   }
   size_t off = (size_t)rows * hwc::kNormRow;
-  *tab1 = (uint32_t)off;
-  for (uint32_t i = 0; i < 3 * M; ++i) {   // form A
-    const uint32_t z = F1.zech[i % M];
-    put16(off + 2 * i, z == M ? 6 * M : 2 * z);
-  }
-  off += align16(10 * M);
-  *emb1 = (uint32_t)off;
-  for (uint32_t k = 0; k < q; ++k) put32(off + 4 * k, (uint32_t)F1.emb[k]);
-  off += align16(4 * q);
+  D->emb_off = (uint32_t)off;
+  for (uint32_t k = 0; k < q; ++k) put32(off + ((size_t)k << esh), (uint32_t)F1.emb[k]);
+  off += align16(q << esh);
   D->kind = fold ? hwc::kNormFold : hwc::kNormPlain;
   D->M = M;
   D->srow = srow;
-  D->emb_off = *emb1;
-  D->tab1_off = *tab1;
+  D->esh = esh;
   D->fin_off = (uint32_t)off;
   const uint32_t par = H % 2 ? 0u : 1u;    // parity of log(-v), v a nonsquare
   for (uint32_t i = 0; i < nfin; ++i) {
@@ -847,18 +846,17 @@ std::vector<uint8_t> norm_image(const hwc::Field& F1, uint32_t q, bool fold, hwc
 int build_norm(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, const Tuning& T, uint64_t plan_bytes) {
   const uint32_t q = P->q, M = q - 1;
   const hwc::LevelDesc& top = P->desc.lv[1];
-  if (q < kNormMinQ || !T.split || top.M < T.split_min_m || (T.device_tables & 3u)) return HWC_OK;
+  if (q < (e == 1 ? kNormMinPrime : kNormMinPower) || !T.split || top.M < T.split_min_m || (T.device_tables & 3u)) return HWC_OK;
   const hwc::Field& F1 = P->fields[0]->F;
   hwc::NormDesc D{};
-  uint32_t tab1 = 0, emb1 = 0;
-  std::vector<uint8_t> img = norm_image(F1, q, false, &D, &tab1, &emb1);
-  if (img.empty()) img = norm_image(F1, q, true, &D, &tab1, &emb1);
+  std::vector<uint8_t> img = norm_image(F1, q, false, &D);
+  if (img.empty()) img = norm_image(F1, q, true, &D);
   if (img.empty()) return HWC_OK;
   std::vector<uint32_t> tm;
   if (e == 1) {
-    // rows i < 6 of t: binom(j, i) t^(j-i) mod q, times 4, pairs j = 2k, 2k + 1
-    const uint64_t m = ((1ull << 32) + 4 * q - 1) / (4 * q), vmax = 4ull * 7 * M * M;
-    if (m >= (1u << 24) || vmax >= (1u << 24) || vmax * (m * 4 * q - (1ull << 32)) >= (1ull << 32)) return HWC_OK;
+    // rows i < 6 of t: binom(j, i) t^(j-i) mod q, times 2^esh, pairs j = 2k, 2k + 1
+    const uint64_t qs = (uint64_t)q << D.esh, m = ((1ull << 32) + qs - 1) / qs, vmax = (7ull * M * M) << D.esh;
+    if (m >= (1u << 24) || vmax >= (1u << 24) || vmax * (m * qs - (1ull << 32)) >= (1ull << 32)) return HWC_OK;
     D.qm = (uint32_t)m;
     uint32_t binom[7][7] = {};
     for (uint32_t j = 0; j < 7; ++j)
@@ -867,7 +865,7 @@ int build_norm(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, const Tuning& T, 
     for (uint32_t t = 0; t < q; ++t)
       for (uint32_t i = 0; i < 6; ++i) {
         uint32_t row[8] = {};
-        for (uint32_t j = i, tp = 1; j < 7; ++j, tp = tp * t % q) row[j] = 4 * (binom[j][i] * tp % q);
+        for (uint32_t j = i, tp = 1; j < 7; ++j, tp = tp * t % q) row[j] = (binom[j][i] * tp % q) << D.esh;
         for (uint32_t k = i / 2; k < 4; ++k) tm.push_back(row[2 * k] | row[2 * k + 1] << 16);
       }
   }
@@ -879,7 +877,7 @@ int build_norm(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, const Tuning& T, 
   for (uint32_t b : {256u, 512u, 1024u}) {
     if (T.block && b != T.block) continue;
     int n = 0;
-    HIPX(c, hwc::occupancy_count(2, 1, b, (uint32_t)img.size(), P->wpe, &n));
+    HIPX(c, hwc::occupancy_norm(b, (uint32_t)img.size(), &n));
     if (n * (int)(b / hwc::kWave) > best) {
       best = n * (int)(b / hwc::kWave);
       block = b;
@@ -900,9 +898,6 @@ int build_norm(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, const Tuning& T, 
   N.image = static_cast<const uint32_t*>(P->d_nimage);
   N.image_bytes = (uint32_t)img.size();
   N.norm = D;
-  N.lv[0].form = hwc::kFormA;
-  N.lv[0].tab_off = tab1;
-  N.lv[0].emb_off = emb1;
   HIPX(c, hipMalloc(&P->d_ndesc, sizeof(N)));
   HIPX(c, hipMemcpy(P->d_ndesc, &N, sizeof(N), hipMemcpyHostToDevice));
   P->dev_bytes += bytes;
@@ -1334,15 +1329,15 @@ uint32_t part_log(const DevPlan* P, uint32_t flags, double cost, double target) 
   return pl;
 }
 
-// ... of a single request of n rows: one entry for each of 16 waves a CU, two
+// ... of a single request of n rows: one entry for each resident wave, two
 // where the top level sweeps thousands of points and a part's setup is small
 // beside its share (count kernel, one against two entries a wave: g = 4, q = 13,
 // 7098 points, 2^16 curves 1015 / 627 us; g = 3, q = 13, 728 points, 2^17 curves
 // 164 / 186 us).
-uint32_t part_log_single(const hwc_ctx* c, const DevPlan* P, uint32_t flags, uint64_t n) {
+uint32_t part_log_single(const DevPlan* P, uint32_t flags, uint64_t n) {
   const double tiles = (double)((n + hwc::kWave - 1) / hwc::kWave);
-  const double entries = (P->desc.lv[P->g - 1].nx >= 6000 ? 32.0 : 16.0) * c->cus;
-  return part_log(P, flags, 1.0, tiles / entries);
+  const double waves = P->npath ? (double)P->ngrid * P->nblock / hwc::kWave : (double)P->grid * P->block / hwc::kWave;
+  return part_log(P, flags, 1.0, tiles / (P->desc.lv[P->g - 1].nx >= 6000 ? 2.0 * waves : waves));
 }
 
 // Rows up to which one workgroup buckets a request alone (bucket_small.hip: 9 us
@@ -1428,7 +1423,7 @@ int enqueue(hwc_ctx* c, DevPlan* P, const Scratch& S, const void* codes, int cb,
     return HWC_OK;
   }
   const bool shifted = P->d_shift && n > 0;
-  const uint32_t plog = S.acc && n > 0 ? part_log_single(c, P, flags, n) : 0u;
+  const uint32_t plog = S.acc && n > 0 ? part_log_single(P, flags, n) : 0u;
   const uint64_t acc_words = plog ? n * g + S.max_tiles : 0;
   if (n <= kBucketAlone) {
     HIPX(c, hwc::launch_bucket_small(bucket_job(P, codes, shifted ? S.tcodes : nullptr, cb, n, S.perm, S.tiles, S.ntiles,
@@ -1458,9 +1453,14 @@ int enqueue(hwc_ctx* c, DevPlan* P, const Scratch& S, const void* codes, int cb,
       const uint32_t block = P->npath ? P->nblock : P->block;
       const uint32_t grid = persistent_grid(P->npath ? P->ngrid : P->grid, block,
                                             ((n + hwc::kWave - 1) / hwc::kWave + 4) << plog);
-      HIPX(c, hwc::launch_count(P->npath ? P->ndesc : P->desc, P->npath ? P->d_ndesc : P->d_desc, cb, codes, S.perm,
-                                S.tiles, S.ntiles, S.queue, 0, g - 1, N, lam ? S.lv : nullptr, plog,
-                                plog ? S.acc : nullptr, plog ? S.acc + n * g : nullptr, grid, block, P->wpe, s));
+      uint32_t* lv = lam ? S.lv : nullptr;
+      uint32_t *acc = plog ? S.acc : nullptr, *done = plog ? S.acc + n * g : nullptr;
+      if (P->npath)
+        HIPX(c, hwc::launch_norm(P->ndesc, P->d_ndesc, cb, codes, S.perm, S.tiles, S.ntiles, S.queue, N, lv, plog, acc,
+                                 done, grid, block, s));
+      else
+        HIPX(c, hwc::launch_count(P->desc, P->d_desc, cb, codes, S.perm, S.tiles, S.ntiles, S.queue, 0, g - 1, N, lv, plog,
+                                  acc, done, grid, block, P->wpe, s));
     }
     if (lam) HIPX(c, hwc::launch_lambda(P->desc, P->d_desc, cb, codes, n, S.lv, lam, (flags & kFlagSqf) ? 1u : 0u, s));
   }
@@ -1533,7 +1533,7 @@ int run_dev(hwc_ctx* c, uint32_t q, uint32_t g, const void* codes, int cb, uint6
   (void)reap(c, false);
   Scratch S;
   if ((rc = get_scratch(c, set, n, g, cb, needs_lv(P, flags, lam), hk != nullptr, needs_tcodes(P),
-                        part_log_single(c, P, flags, n) > 0, &S)))
+                        part_log_single(P, flags, n) > 0, &S)))
     return rc;
   const bool use_graph = !(flags & (HWC_PLAIN | HWC_NO_GRAPH)) && n > 0 && !c->profile;
   if ((rc = order_begin(c, set, s))) return rc;
@@ -1860,6 +1860,7 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     hj[r].cb = (uint32_t)J.coeff_bytes;
     hj[r].g = J.g;
     hj[r].plog = B.plog[r];
+    hj[r].norm = P->npath ? 1u : 0u;
     hj[r].cost = (float)(P->tile_cost / (double)(1u << B.plog[r]));
     hj[r].acc = B.plog[r] ? static_cast<uint32_t*>(st.bacc.p) + B.aoff[r] : nullptr;
     hj[r].done = B.plog[r] ? hj[r].acc + J.n * J.g : nullptr;
@@ -2410,6 +2411,7 @@ int hwc_ctx_create(int device, uint64_t hbm_budget_bytes, hwc_ctx** out) {
     if ((e = hwc::prepare_kernels()) != hipSuccess) return create_fail(e, "kernel attributes");
     if ((e = hwc::prepare_vcount()) != hipSuccess) return create_fail(e, "kernel attributes");
     if ((e = hwc::prepare_hist_small()) != hipSuccess) return create_fail(e, "kernel attributes");
+    if ((e = hwc::prepare_norm()) != hipSuccess) return create_fail(e, "kernel attributes");
     if ((e = hwc::prepare_bucket_small()) != hipSuccess) return create_fail(e, "kernel attributes");
     if ((e = hipMalloc(reinterpret_cast<void**>(&c->d_err), 256)) != hipSuccess) return create_fail(e, "hipMalloc");
     for (auto& st : c->sets)

@@ -965,34 +965,6 @@ __device__ __forceinline__ uint32_t count_level(const LevelDesc& Lp, uint32_t lb
   return z | ((ns0 + ns1) << 8);
 }
 
-// N_k from the per-level counts (Sec. 1.1 decomposition; x = 0 and the
-// points at infinity of the model in P(1, g+1, 1) added here).
-template <int G>
-__device__ __forceinline__ void assemble(const PlanDesc& P, const uint32_t (&lv)[G], uint32_t c0, uint32_t ctop,
-                                         uint32_t log0, uint32_t logtop, int32_t* out) {
-#pragma unroll
-  for (int k = 1; k <= G; ++k) {
-    const int chi0 = (k % 2 == 0) ? 1 : ((log0 & 1u) ? -1 : 1);
-    const int chit = (k % 2 == 0) ? 1 : ((logtop & 1u) ? -1 : 1);
-    int32_t n = (c0 == 0 ? 1 : 1 + chi0) + (ctop == 0 ? 1 : 1 + chit);
-    if (P.orbit) {
-#pragma unroll
-      for (int j = 1; j <= G; ++j) {
-        if (k % j) continue;
-        const uint32_t z = lv[j - 1] & 0xFFu, ns = lv[j - 1] >> 8;
-        const uint32_t s = P.lv[j - 1].nx - z - ns;
-        const uint32_t sq = ((k / j) % 2 == 0) ? s + ns : s;
-        n += (int32_t)(j * z + 2 * j * sq);
-      }
-    } else {
-      const uint32_t z = lv[k - 1] & 0xFFu, ns = lv[k - 1] >> 8;
-      const uint32_t s = P.lv[k - 1].nx - z - ns;
-      n += (int32_t)(z + 2 * s);
-    }
-    out[k - 1] = n;
-  }
-}
-
 // One tile (up to 64 curves of one pattern) through levels lvl_lo..lvl_hi.
 // With plog > 0 this is part `part` of tile `tile`: the levels' points are shared
 // out over the parts (count_level), each share of at least kPartPoints points;
@@ -1042,62 +1014,13 @@ __device__ __forceinline__ void process_tile(const PlanDesc& P, uint32_t lb, con
       share = (part + ((uint32_t)G - 1u - j) * kPartStep) & ((1u << plog) - 1u);
       if (share >> slog) continue;
     }
-    uint32_t v = 0;
-    bool norm = false;
-    if constexpr (G == 2) {
-      if (is_top) {
-        const NormDesc D = load_norm(P);
-        if (D.kind) {
-          norm = true;
-          if (D.kind == kNormFold)
-            v = top ? norm_level<true, true>(D, code, part, plog) : norm_level<true, false>(D, code, part, plog);
-          else
-            v = top ? norm_level<false, true>(D, code, part, plog) : norm_level<false, false>(D, code, part, plog);
-        }
-      }
-    }
-    if (!norm)
-      v = count_level<G>(load_level(P, j), lb, code, top, mask, share, slog);
+    const uint32_t v = count_level<G>(load_level(P, j), lb, code, top, mask, share, slog);
 #pragma unroll
     for (int k = 0; k < G; ++k) lv[k] = (uint32_t)k == j ? v : lv[k];
   }
-  if (plog) {
-    // packed counts add without carries: a level's zeros stay below 256
-    if (live) {
-#pragma unroll
-      for (int k = 0; k < G; ++k)
-        if (lv[k]) atomicAdd(acc + (uint64_t)curve * G + k, lv[k]);
-    }
-    // Parts of a tile meet through device-scope atomics only (adds above, the
-    // loads below), which no L2 holds back, so it is enough that this wave's
-    // adds are done before it counts itself: a wait, not a fence, which
-    // writes back the L2 for every part (g = 3, q = 13, 2^16 curves: 261 us
-    // with the fences, 191 without)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    uint32_t prior = 0;
-    if (lane == 0) prior = atomicAdd(done + tile, 1u);
-    if (uniform(prior) != (1u << plog) - 1u) return;
-    asm volatile("" ::: "memory");
-#pragma unroll
-    for (int k = 0; k < G; ++k)
-      lv[k] = __hip_atomic_load(acc + (uint64_t)curve * G + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
-
-  if (outN) {
-    const uint32_t log0 = lds_u32(lb + P.lv[0].emb_off + 4 * code[0]);
-    const uint32_t logt = lds_u32(lb + P.lv[0].emb_off + 4 * code[NC - 1]);
-    int32_t n[G];
-    assemble<G>(P, lv, code[0], code[NC - 1], log0, logt, n);
-    if (live) {
-#pragma unroll
-      for (int k = 0; k < G; ++k) outN[(uint64_t)curve * G + k] = n[k];
-    }
-  }
-  if (outLv && live) {
-#pragma unroll
-    for (int j = 0; j < G; ++j)
-      if ((uint32_t)j >= lvl_lo && (uint32_t)j <= lvl_hi) outLv[(uint64_t)curve * G + j] = lv[j];
-  }
+  const uint32_t emb = lb + P.lv[0].emb_off;
+  finish_tile<G>(P, code[0], code[NC - 1], lds_u32(emb + 4 * code[0]), lds_u32(emb + 4 * code[NC - 1]), lv, live, curve, lvl_lo, lvl_hi, outN, outLv, tile,
+                 plog, acc, done);
 }
 
 // WPE: minimum waves per SIMD the register allocation must allow (1: free)
@@ -1166,6 +1089,17 @@ __device__ __forceinline__ void process_job_tile(const JobDesc& J, uint32_t lb, 
                                   J.outN, nullptr, tile, part, plog, J.acc, J.done);                     \
     }                                                                                                    \
     break;
+  if constexpr (GMAX >= 2) {
+    if (J.norm) {   // genus 2, level 2 by norms
+      if (J.cb == 1)
+        norm_tile<int8_t, 8>(P, static_cast<const int8_t*>(J.codes), J.perm, w, J.outN, nullptr, tile, part, plog, J.acc,
+                          J.done);
+      else
+        norm_tile<int16_t, 8>(P, static_cast<const int16_t*>(J.codes), J.perm, w, J.outN, nullptr, tile, part, plog, J.acc,
+                           J.done);
+      return;
+    }
+  }
   switch (J.g) {
     HWC_JOB(1) HWC_JOB(2) HWC_JOB(3) HWC_JOB(4)
     default: break;

@@ -14,8 +14,8 @@
 // gets a copy of its own in its own LDS bank, and a read takes the 2 CU-clocks
 // of a conflict-free one, not the 6.3 of a random gather, with no folding of
 // half tables.  Count kernel on 2^18 curves against the level's own table:
-// q = 293 (85 848 elements) 19.2 -> 5.6 ms, 241 5.7 -> 3.4, 169 3.2 -> 2.0,
-// 101 1.31 -> 0.84, 67 0.62 -> 0.44.  Bound at q = 241: LDS 16.3 CU-clocks a
+// q = 293 (85 848 elements) 19.2 -> 5.7 ms, 241 5.7 -> 3.4, 169 3.2 -> 2.0,
+// 101 1.31 -> 0.80, 37 0.24 -> 0.21.  Bound at q = 241: LDS 16.3 CU-clocks a
 // point (five conflict-free reads and one of the byte table), 13.5 vector
 // instructions, 17.7 measured; with the extra subtraction (q = 293) 17
 // instructions and 19.9.
@@ -42,8 +42,6 @@
 #include "count_core.h"
 
 namespace hwc {
-
-constexpr uint32_t kNormUnroll = 8;   // nonsquares v per pass of the inner loop
 
 typedef unsigned short ushort2_t __attribute__((ext_vector_type(2)));
 
@@ -126,7 +124,8 @@ __device__ __forceinline__ void norm_group(uint32_t L, uint32_t kl, const NormSt
 
 // Every nonsquare v at one t: the chains of the translate's coefficients
 // b[0..6] (logs, M = zero; b[6] = M in degree 5).
-template <bool FOLD, bool TOP>
+// U: nonsquares per pass of the inner loop.
+template <bool FOLD, bool TOP, int U>
 __device__ __forceinline__ void norm_sweep_v(const uint32_t (&b)[7], const NormDesc& D, uint32_t lane4,
                                              uint32_t& odd, uint32_t& z) {
   const uint32_t M = D.M, H = M / 2, S = D.srow * kNormRow, zrow = FOLD ? 2u * M : 3u * M;
@@ -151,13 +150,13 @@ __device__ __forceinline__ void norm_sweep_v(const uint32_t (&b)[7], const NormD
   uint32_t K = bO >= bE ? bO - bE : bO + M - bE;
   K = K >= H ? K - H : K;
   uint32_t L = kNormRow, kl = (K + (H + 1u) / 2u + D.fin_off + D.srow) * kNormRow, k = 0;
-  for (; k + kNormUnroll <= H; k += kNormUnroll) {
-    norm_group<FOLD, TOP, kNormUnroll>(L, kl, e4, e2, e0, o3, o1, S, odd, z);
-    L += 2u * kNormUnroll * kNormRow;
-    kl += kNormUnroll * kNormRow;
+  for (; k + (uint32_t)U <= H; k += (uint32_t)U) {
+    norm_group<FOLD, TOP, U>(L, kl, e4, e2, e0, o3, o1, S, odd, z);
+    L += 2u * (uint32_t)U * kNormRow;
+    kl += (uint32_t)U * kNormRow;
   }
   const uint32_t rest = H - k;
-  if (kNormUnroll > 4 && (rest & 4u)) {
+  if (U > 4 && (rest & 4u)) {
     norm_group<FOLD, TOP, 4>(L, kl, e4, e2, e0, o3, o1, S, odd, z);
     L += 8u * kNormRow;
     kl += 4u * kNormRow;
@@ -170,32 +169,52 @@ __device__ __forceinline__ void norm_sweep_v(const uint32_t (&b)[7], const NormD
   if (rest & 1u) norm_group<FOLD, TOP, 1>(L, kl, e4, e2, e0, o3, o1, S, odd, z);
 }
 
-// Sum of two elements of F_q given as logs (M = zero), by the form A table of
-// level 1 (entries 2 Z, 6M where 1 + gamma^d = 0); no branches, so the reads
-// of one translate overlap.
-__device__ __forceinline__ uint32_t norm_add(uint32_t tab, uint32_t M, uint32_t a, uint32_t b) {
+// Sum of two elements of F_q given as logs (M = zero), by the Zech rows; no
+// branches, so the reads of one translate overlap.
+__device__ __forceinline__ uint32_t norm_add(uint32_t M, uint32_t S, uint32_t lane4, uint32_t a, uint32_t b) {
   const bool az = a == M, bz = b == M;
   uint32_t d = b >= a ? b - a : b + M - a;
   d = (az || bz) ? 0u : d;
-  const uint32_t v = lds_u16(tab + 2u * d);
-  uint32_t s = a + (v >> 1);
+  const uint32_t v = lds_u32(d * kNormRow + lane4);
+  uint32_t s = a + v / kNormRow;
   s = s >= M ? s - M : s;
-  s = v == 6u * M ? M : s;
+  s = v == S ? M : s;
   return az ? b : (bz ? a : s);
+}
+
+// The counts of level 1 over the nonzero x = gamma^L, L in share `part` of
+// 2^plog: f by one chain of the same steps as level 2's.
+template <bool FOLD>
+__device__ __forceinline__ uint32_t norm_level1(const NormDesc& D, const uint32_t (&w)[7], uint32_t lane4,
+                                                uint32_t part, uint32_t plog) {
+  const uint32_t M = D.M, S = D.srow * kNormRow, zrow = FOLD ? 2u * M : 3u * M;
+  uint32_t beta = w[6] == M ? 0u : w[6];
+  const uint32_t a0 = w[6] == M ? S : 0u;
+  NormStep st[6];
+#pragma unroll
+  for (int i = 5; i >= 0; --i) st[i] = norm_link(beta, w[i], M, zrow, lane4);
+  uint32_t odd = 0, z = 0;
+  const uint32_t l1 = (M * (part + 1u)) >> plog;
+  for (uint32_t l = (M * part) >> plog; l < l1; ++l) {
+    const uint32_t L = l * kNormRow;
+    uint32_t a = a0;
+#pragma unroll
+    for (int i = 5; i >= 0; --i) a = norm_step<FOLD>(a, st[i], L);
+    const bool root = a >= S;
+    z += root;
+    odd += root ? 0u : ((a / kNormRow + beta) & 1u);
+  }
+  return z | (odd << 8);
 }
 
 // The counts of level 2 over the orbits (t, v), t in part `part` of 2^plog
 // shares of F_q: roots | nonsquares << 8, as count_level returns them.
-template <bool FOLD, bool TOP>
-__device__ __forceinline__ uint32_t norm_level(const NormDesc& D, const uint32_t (&code)[7], uint32_t part,
-                                               uint32_t plog) {
+template <bool FOLD, bool TOP, int U>
+__device__ __forceinline__ uint32_t norm_level2(const NormDesc& D, const uint32_t (&code)[7], const uint32_t (&w)[7],
+                                                uint32_t lane4, uint32_t part, uint32_t plog) {
   const uint32_t M = D.M, q = M + 1u;
-  const uint32_t lane4 = (threadIdx.x & 31u) * 4u;
   const uint32_t t0 = (q * part) >> plog, t1 = (q * (part + 1u)) >> plog;
   uint32_t odd = 0, z = 0;
-  uint32_t w[7];
-#pragma unroll
-  for (int i = 0; i < 7; ++i) w[i] = lds_u32(D.emb_off + 4u * code[i]);
   uint32_t pk[4];   // coefficient pairs for the integer translates
 #pragma unroll
   for (int k = 0; k < 4; ++k) pk[k] = code[2 * k] | (k < 3 ? code[2 * k + 1 < 7 ? 2 * k + 1 : 6] << 16 : 0u);
@@ -205,19 +224,17 @@ __device__ __forceinline__ uint32_t norm_level(const NormDesc& D, const uint32_t
     b[6] = w[6];
     if (D.tmat) {
       // prime q: b_i = sum_j binom(j, i) t^(j-i) c_j mod q by 2 x 16-bit dot
-      // products with the uniform rows of t, whose entries come times 4, so
-      // the residue times 4 is a byte offset into the logs
+      // products with the uniform rows of t, whose entries come times the
+      // bytes of a log's slot, so the scaled residue is its offset
       uint32_t at = t * kNormTmatWords;
 #pragma unroll
       for (int i = 0; i < 6; ++i) {
         uint32_t acc = 0;
 #pragma unroll
-        for (int k = i / 2; k < 4; ++k) {
-          const uint32_t row = sload(D.tmat, at++);
-          acc = __builtin_amdgcn_udot2(__builtin_bit_cast(ushort2_t, row), __builtin_bit_cast(ushort2_t, pk[k]), acc,
-                                       false);
-        }
-        b[i] = lds_u32(D.emb_off + acc - __umul24(norm_mulhi24(acc, D.qm), 4u * q));
+        for (int k = i / 2; k < 4; ++k)
+          acc = __builtin_amdgcn_udot2(__builtin_bit_cast(ushort2_t, sload(D.tmat, at++)), __builtin_bit_cast(ushort2_t, pk[k]),
+                                       acc, false);
+        b[i] = lds_u32(D.emb_off + acc - __umul24(norm_mulhi24(acc, D.qm), q << D.esh));
       }
     } else {
       // prime powers: repeated synthetic division by X - t in logs; t runs
@@ -232,13 +249,53 @@ __device__ __forceinline__ uint32_t norm_level(const NormDesc& D, const uint32_t
           for (int i = 5; i >= k; --i) {
             uint32_t m = b[i + 1] + lt;
             m = m >= M ? m - M : m;
-            b[i] = norm_add(D.tab1_off, M, b[i], b[i + 1] == M ? M : m);
+            b[i] = norm_add(M, D.srow * kNormRow, lane4, b[i], b[i + 1] == M ? M : m);
           }
       }
     }
-    norm_sweep_v<FOLD, TOP>(b, D, lane4, odd, z);
+    norm_sweep_v<FOLD, TOP, U>(b, D, lane4, odd, z);
   }
   return z | (odd << 8);
+}
+
+// One tile, or part `part` of 2^plog of it, as process_tile for a plan with
+// norm tables.
+template <typename CT, int U>
+__device__ __forceinline__ void norm_tile(const PlanDesc& P, const CT* __restrict__ codes,
+                                          const uint32_t* __restrict__ perm, uint64_t w, int32_t* __restrict__ outN,
+                                          uint32_t* __restrict__ outLv, uint32_t tile, uint32_t part, uint32_t plog,
+                                          uint32_t* __restrict__ acc, uint32_t* __restrict__ done) {
+  const uint32_t lane = threadIdx.x & (kWave - 1);
+  const uint32_t cnt = uniform((uint32_t)((w >> 16) & 0xFFFFu) + 1u);
+  const uint32_t start = uniform((uint32_t)(w >> 32));
+  const bool live = lane < cnt;                     // lanes past the end shadow the last curve
+  const uint32_t curve = perm[start + (live ? lane : cnt - 1)];
+  const NormDesc D = load_norm(P);
+  uint32_t code[7], lg[7];
+#pragma unroll
+  for (int i = 0; i < 7; ++i) {
+    int v = (int)codes[(uint64_t)curve * 7 + i];
+    v = v < 0 ? 0 : (v > (int)D.M ? (int)D.M : v);  // keeps reads in bounds on bad input
+    code[i] = (uint32_t)v;
+  }
+#pragma unroll
+  for (int i = 0; i < 7; ++i) lg[i] = lds_u32(D.emb_off + (code[i] << D.esh));
+  const bool top = uniform((uint32_t)(w & 0xFFFFu)) >> 6;   // the pattern's bit of degree 6
+  const uint32_t lane4 = (lane & 31u) * 4u;
+  const bool fold = D.kind == kNormFold;
+  uint32_t lv[2] = {0, 0};
+  // level 1 is shared out over the last 2^slog parts (part 0 of a whole tile)
+  const uint32_t pts = D.M / kPartPoints, last = (1u << plog) - 1u;
+  const uint32_t slog = pts < 2u ? 0u : min(plog, 31u - (uint32_t)__builtin_clz(pts));
+  if (((last - part) >> slog) == 0)
+    lv[0] = fold ? norm_level1<true>(D, lg, lane4, last - part, slog) : norm_level1<false>(D, lg, lane4, last - part, slog);
+  if (fold)
+    lv[1] = top ? norm_level2<true, true, U>(D, code, lg, lane4, part, plog)
+                : norm_level2<true, false, U>(D, code, lg, lane4, part, plog);
+  else
+    lv[1] = top ? norm_level2<false, true, U>(D, code, lg, lane4, part, plog)
+                : norm_level2<false, false, U>(D, code, lg, lane4, part, plog);
+  finish_tile<2>(P, code[0], code[6], lg[0], lg[6], lv, live, curve, 0, 1, outN, outLv, tile, plog, acc, done);
 }
 
 }  // namespace hwc

@@ -75,8 +75,7 @@ struct LevelDesc {
 };
 
 // Genus 2 with the norm tables (norm_impl.h) in place of level 2's Zech table.
-// Image: the rows at offset 0, level 1's form A table and logs, the byte table
-// of the last step.
+// Image: the rows at offset 0, the codes' logs, the byte table of the last step.
 constexpr uint32_t kNormRow = 128;         // bytes of a row: one u32 per LDS bank
 constexpr uint32_t kNormTmatWords = 18;    // words per t of the translates of degree 6
 constexpr uint32_t kNormPlain = 1, kNormFold = 2;
@@ -84,10 +83,9 @@ struct NormDesc {
   uint32_t kind;          // 0: none, kNormPlain, kNormFold
   uint32_t M;             // q - 1
   uint32_t srow;          // row a vanished sum reads as: a power of two, at least 4M
-  uint32_t emb_off;       // logs of the codes in F_q (u32)
-  uint32_t tab1_off;      // F_q's form A table
+  uint32_t emb_off, esh;  // logs of the codes in F_q: u32 every 2^esh bytes
   uint32_t fin_off;       // byte table of the last step
-  uint32_t qm, pad;       // floor(v / 4q) = (v * qm) >> 32 for the integer translates
+  uint32_t qm;            // floor(v / (q << esh)) = (v * qm) >> 32 for the integer translates
   const uint32_t* tmat;   // prime q: [q][kNormTmatWords] translate rows; nullptr: log arithmetic
 };
 
@@ -249,6 +247,7 @@ struct JobDesc {
   // the parts add their level counts into acc and the last part of a tile
   // (counted in done) assembles N.  plog = 0: whole tiles.
   uint32_t plog;
+  uint32_t norm;          // the plan has norm tables
   float cost;             // relative work of one queue entry
   uint32_t* acc;          // [n][g] packed level counts (zero before the launch)
   uint32_t* done;         // [tiles] parts finished (zero before the launch)
