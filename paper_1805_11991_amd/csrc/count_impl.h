@@ -217,26 +217,6 @@ __device__ __forceinline__ uint32_t submod(uint32_t a, uint32_t b, uint32_t M) {
   return a >= b ? a - b : a + M - b;
 }
 
-// Zero-safe sum of two field elements given as absolute logs in byte units
-// (2 log, in [0, 2M)) or the zero marker S: one read of the table's first
-// 2M bytes (2 Z(k), or S where 1 + gamma^k = 0).
-__device__ __forceinline__ uint32_t zadd(uint32_t tab, uint32_t M2, uint32_t S, uint32_t u,
-                                         uint32_t v) {
-  const bool uz = u == S, vz = v == S;
-  uint32_t d = v - u;
-  d = min(d, d + M2);
-  const uint32_t r = lds_u16(tab + ((uz || vz) ? 0u : d));
-  uint32_t s = u + r;
-  s = min(s, s - M2);
-  return uz ? v : (vz ? u : (r == S ? S : s));
-}
-
-__device__ __forceinline__ uint32_t zmul(uint32_t v, uint32_t k, uint32_t M2, uint32_t S) {  // k < 2M bytes
-  uint32_t s = v + k;
-  s = min(s, s - M2);
-  return v == S ? S : s;
-}
-
 // Split evaluation over mu_MS cosets (form A).  With w = gamma^(M/MS) in F_q,
 // f(w^s x) = sum_r w^(s r) x^r f_r(x^MS): the MS points of a tuple share the
 // sub-polynomial values at y = x^MS.
@@ -249,8 +229,7 @@ __device__ __forceinline__ uint32_t zmul(uint32_t v, uint32_t k, uint32_t M2, ui
 //     E(v) = f_0(v^2) + v f_2(v^2), O(v) = f_1(v^2) + v f_3(v^2); the points
 //     x, -x share E(x^2), O(x^2), and ix, -ix share E(-x^2), O(-x^2): four
 //     additions for E and O, one per point.  Relative form as above; when a
-//     base vanishes (f_0(y), f_1(y) or E) the wave redoes the eight additions
-//     zero-safe on absolute logs.
+//     base vanishes (f_0(y), f_1(y) or E) the lanes concerned are patched.
 template <int NC, int MS, bool FULL, int D>
 __device__ __forceinline__ void sweep_split_a(const LevelDesc& L, const uint32_t (&sdel)[NC],
                                               const uint32_t (&del)[NC], uint32_t d, uint32_t mask,
@@ -292,8 +271,8 @@ __device__ __forceinline__ void sweep_split_a(const LevelDesc& L, const uint32_t
       const uint32_t uO = addmod(addmod(x2, p3, M), p1 ? M - p1 : 0u, M);
       const uint32_t vf = addmod(addmod(x, p1, M), p0 ? M - p0 : 0u, M);
       // clamped bases keep every index in the table while the wave decides
-      const bool base_zero = (a0 == S) || (a1 == S);
-      const uint32_t b0 = base_zero ? 0u : a0, b1 = base_zero ? 0u : a1;
+      const bool z0 = a0 == S, z1 = a1 == S, base_zero = z0 || z1;
+      const uint32_t b0 = z0 ? 0u : a0, b1 = z1 ? 0u : a1;
       uint32_t FE = K2 - b0;                          // (0, 4M)
       FE = min(FE, FE - M2);
       uint32_t FO = K3 - b1;
@@ -335,26 +314,39 @@ __device__ __forceinline__ void sweep_split_a(const LevelDesc& L, const uint32_t
         u >>= 1;
         odd = ((a0 >> 1) ^ fix) & 1u ? (4 - zs) - u : u;
       } else {
-        // absolute logs (byte units) of f_r(y) w^.. x^..: 2 (ll_r + p_r) + a_r
-        const uint32_t v0 = zmul(a0, 2 * addmod(K.ll[0], p0, M), M2, S);
-        const uint32_t v1 = zmul(a1, 2 * addmod(K.ll[1], p1, M), M2, S);
-        const uint32_t v2 = zmul(a2, 2 * addmod(K.ll[2], p2, M), M2, S);
-        const uint32_t v3 = zmul(a3, 2 * addmod(K.ll[3], p3, M), M2, S);
-        const uint32_t ep = zadd(tab, M2, S, v0, zmul(v2, 2 * x2, M2, S));
-        const uint32_t em = zadd(tab, M2, S, v0, zmul(v2, 2 * addmod(x2, h, M), M2, S));
-        const uint32_t op = zadd(tab, M2, S, v1, zmul(v3, 2 * x2, M2, S));
-        const uint32_t om = zadd(tab, M2, S, v1, zmul(v3, 2 * addmod(x2, h, M), M2, S));
-        odd = 0;
+        // A vanished f_0(y) (or f_1(y)) leaves E = +-x^2 f_2 (O = +-x^2 f_3): that
+        // term takes the base's place, E relative to it is 1 or -1.  Where E
+        // vanishes, f = x O and the last read's index is already its log.  No
+        // table reads: the lanes that met a zero are patched and the wave goes
+        // on (redoing the eight additions zero-safe for such waves, 12 % of
+        // them at M = 2196, cost twice the vector work of the common path).
+        const bool z2 = a2 == S, z3 = a3 == S;
+        uint32_t t0 = a2 + K2 - M2 + 2 * uE, t1 = a3 + K3 - M2 + 2 * uO;   // < 6M where a2, a3 are no markers
+        t0 = min(t0, t0 - M2); t0 = min(t0, t0 - M2);
+        t1 = min(t1, t1 - M2); t1 = min(t1, t1 - M2);
+        const uint32_t c0 = z0 ? (z2 ? 0u : t0) : a0, c1 = z1 ? (z3 ? 0u : t1) : a1;
+        const uint32_t ep = z0 ? (z2 ? S : 0u) : Ep, em = z0 ? (z2 ? S : M) : Em;   // log(-1) = M / 2
+        const uint32_t op = z1 ? (z3 ? S : 0u) : Op, om = z1 ? (z3 ? S : M) : Om;
+        uint32_t G = c1 + K1 - c0;                      // (0, 6M)
+        G = min(G, G - M2);
+        G = min(G, G - M2);
+        G += M2;
 #pragma unroll
         for (uint32_t s = 0; s < 4; ++s) {
-          const uint32_t E = (s & 1u) ? em : ep;
-          const uint32_t O = (s & 1u) ? om : op;
-          const uint32_t f = zadd(tab, M2, S, E, zmul(O, 2 * addmod(x, s * step, M), M2, S));
-          const bool z = f == S;
+          const uint32_t E = (s & 1u) ? em : ep, O = (s & 1u) ? om : op;
+          const bool ez = E == S;
+          const uint32_t e = ez ? 0u : E;
+          uint32_t F = G - e;                           // (0, 4M)
+          F = min(F, F - M2);
+          const uint32_t at = O + F + 2 * addmod(vf, s * step, M);
+          const uint32_t t = lds_u16(at + tab);
+          const uint32_t rr = ez ? (O == S ? S : at) : t;   // at < 6M = S; its bit 1 is that of at mod 2M
+          const bool z = rr == S;
           zs += z;
-          // A = log f - log c_low - t_0 Y
-          odd += z ? 0u : (((f >> 1) ^ K.blane ^ cls) & 1u);
+          u += z ? 0u : ((e ^ rr) & 2u);
         }
+        u >>= 1;
+        odd = ((c0 >> 1) ^ fix) & 1u ? (4 - zs) - u : u;
       }
       c.add_n(cls, 4, zs, odd);
       continue;
@@ -660,8 +652,8 @@ __device__ __forceinline__ void sweep_split_c(const LevelDesc& L, const uint32_t
     // Every index below stays under 2M, the table's two periods, whatever the
     // marker values (a_r <= M, folded bases and offsets < M), so no clamps are
     // needed.  Any vanishing
-    // sub-polynomial, E or O value sends the wave through the zero-safe
-    // recomputation, which keeps the common path free of selects.
+    // sub-polynomial, E or O value sends the wave through the patched form of
+    // the last step, which keeps the common path free of selects.
     const bool rare = (a0 == M) | (a1 == M) | (a2 == M) | (a3 == M);
     const uint32_t FE = fold(K2 - a0, M), FO = fold(K3 - a1, M);    // [0, M)
     // the bases a2 + FE, a3 + FO folded once each ([0, M)), so that the two
@@ -699,24 +691,30 @@ __device__ __forceinline__ void sweep_split_c(const LevelDesc& L, const uint32_t
       }
       odd = (((a0 >> 1) ^ fix) & 1u) ? (4 - zs) - u : u;
     } else {
-      const uint32_t v0 = zmul_c(a0, addmod(K.ll[0], p0, M), M);
-      const uint32_t v1 = zmul_c(a1, addmod(K.ll[1], p1, M), M);
-      const uint32_t v2 = zmul_c(a2, addmod(K.ll[2], p2, M), M);
-      const uint32_t v3 = zmul_c(a3, addmod(K.ll[3], p3, M), M);
-      const uint32_t ep = zadd_c<TM>(tab, gtab, M, v0, zmul_c(v2, x2, M));
-      const uint32_t em = zadd_c<TM>(tab, gtab, M, v0, zmul_c(v2, addmod(x2, h, M), M));
-      const uint32_t op = zadd_c<TM>(tab, gtab, M, v1, zmul_c(v3, x2, M));
-      const uint32_t om = zadd_c<TM>(tab, gtab, M, v1, zmul_c(v3, addmod(x2, h, M), M));
-      odd = 0;
+      // as in sweep_split_a: a vanished base is replaced by the term it leaves,
+      // 1 or -1 times x^2 f_2 (x^2 f_3); here a vanished second term (no zero
+      // region in the table) leaves the base itself, log 1; where E vanishes
+      // the last read's index is the log of x O
+      const bool z0 = a0 == M, z1 = a1 == M, z2 = a2 == M, z3 = a3 == M;
+      const uint32_t t0 = fold(fold(a2 + K2 - M + uE, M), M), t1 = fold(fold(a3 + K3 - M + uO, M), M);
+      const uint32_t c0 = z0 ? (z2 ? 0u : t0) : a0, c1 = z1 ? (z3 ? 0u : t1) : a1;
+      const uint32_t ep = z0 ? (z2 ? M : 0u) : (z2 ? 0u : Ep), em = z0 ? (z2 ? M : h) : (z2 ? 0u : Em);
+      const uint32_t op = z1 ? (z3 ? M : 0u) : (z3 ? 0u : Op), om = z1 ? (z3 ? M : h) : (z3 ? 0u : Om);
+      const uint32_t G = fold(fold(c1 + K1 - c0, M), M) + M;         // [M, 2M)
+      uint32_t u = 0;
 #pragma unroll
       for (uint32_t s = 0; s < 4; ++s) {
-        const uint32_t E = (s & 1u) ? em : ep;
-        const uint32_t O = (s & 1u) ? om : op;
-        const uint32_t f = zadd_c<TM>(tab, gtab, M, E, zmul_c(O, addmod(x, s * step, M), M));
-        const bool z = f == M;
+        const uint32_t E = (s & 1u) ? em : ep, O = (s & 1u) ? om : op;
+        const bool ez = E == M, oz = O == M;
+        const uint32_t e = ez ? 0u : E;
+        const uint32_t at = fold((oz ? 0u : O) + fold(G - e, M), M) + addmod(vf, s * step, M);   // < 2M
+        const uint32_t t = tab_c<TM>(tab, gtab, M, at);
+        const uint32_t rr = oz ? (ez ? M : 0u) : (ez ? fold(at, M) : t);
+        const bool z = rr == M;
         zs += z;
-        odd += z ? 0u : (((f >> 1) ^ K.blane ^ cls) & 1u);
+        u += z ? 0u : (((e ^ rr) >> 1) & 1u);
       }
+      odd = (((c0 >> 1) ^ fix) & 1u) ? (4 - zs) - u : u;
     }
     c.add_n(cls, 4, zs, odd);
   }
