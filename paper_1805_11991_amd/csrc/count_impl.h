@@ -26,6 +26,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "count_core.h"
 #include "norm_impl.h"
@@ -271,8 +272,7 @@ __device__ __forceinline__ void sweep_split_a(const LevelDesc& L, const uint32_t
       const uint32_t uO = addmod(addmod(x2, p3, M), p1 ? M - p1 : 0u, M);
       const uint32_t vf = addmod(addmod(x, p1, M), p0 ? M - p0 : 0u, M);
       // clamped bases keep every index in the table while the wave decides
-      const bool z0 = a0 == S, z1 = a1 == S, base_zero = z0 || z1;
-      const uint32_t b0 = z0 ? 0u : a0, b1 = z1 ? 0u : a1;
+      const uint32_t b0 = min(a0, M2), b1 = min(a1, M2);
       uint32_t FE = K2 - b0;                          // (0, 4M)
       FE = min(FE, FE - M2);
       uint32_t FO = K3 - b1;
@@ -282,15 +282,14 @@ __device__ __forceinline__ void sweep_split_a(const LevelDesc& L, const uint32_t
       const uint32_t Op = lds_u16(a3 + FO + 2 * uO + tab);
       const uint32_t Om = lds_u16(a3 + FO + 2 * addmod(uO, h, M) + tab);
       uint32_t u = 0, zs = 0, odd;
-      if (!__ballot(base_zero || Ep == S || Em == S)) {
+      if (!__ballot(max(max(a0, a1), max(Ep, Em)) == S)) {   // no value exceeds the marker
         uint32_t G = b1 + K1 - b0;                    // (0, 6M)
         G = min(G, G - M2);
         G = min(G, G - M2);
         G += M2;
         // bit 1 of E + r (both even) is bit 1 of E ^ r; a zero point (r = S)
         // must not count, which the rare branch below takes care of
-        uint32_t r[4];
-        bool anyz = false;
+        uint32_t r[4], mr = 0;
 #pragma unroll
         for (uint32_t s = 0; s < 4; ++s) {
           const uint32_t E = (s & 1u) ? Em : Ep;
@@ -299,9 +298,9 @@ __device__ __forceinline__ void sweep_split_a(const LevelDesc& L, const uint32_t
           F = min(F, F - M2);
           r[s] = lds_u16(O + F + 2 * addmod(vf, s * step, M) + tab);
           u += (E ^ r[s]) & 2u;
-          anyz |= r[s] == S;
+          mr = max(mr, r[s]);
         }
-        if (__ballot(anyz)) {
+        if (__ballot(mr == S)) {
           u = 0;
 #pragma unroll
           for (uint32_t s = 0; s < 4; ++s) {
@@ -320,7 +319,7 @@ __device__ __forceinline__ void sweep_split_a(const LevelDesc& L, const uint32_t
         // table reads: the lanes that met a zero are patched and the wave goes
         // on (redoing the eight additions zero-safe for such waves, 12 % of
         // them at M = 2196, cost twice the vector work of the common path).
-        const bool z2 = a2 == S, z3 = a3 == S;
+        const bool z0 = a0 == S, z1 = a1 == S, z2 = a2 == S, z3 = a3 == S;
         uint32_t t0 = a2 + K2 - M2 + 2 * uE, t1 = a3 + K3 - M2 + 2 * uO;   // < 6M where a2, a3 are no markers
         t0 = min(t0, t0 - M2); t0 = min(t0, t0 - M2);
         t1 = min(t1, t1 - M2); t1 = min(t1, t1 - M2);
@@ -449,13 +448,14 @@ __device__ __forceinline__ uint32_t tab_c(uint32_t tab, const uint32_t* __restri
 //
 // Form C/D relative Horner for two x at once (index folded into the table's
 // two periods; reads of both chains inside one uniform branch per position).
-// Not EXACT: a vanishing partial sum sets hit and the caller redoes the pair
-// with EXACT, which restarts from the coefficient.
+// Not EXACT: mx is the largest value read -- M, the marker, if a partial sum
+// vanished -- and the caller then redoes the pair with EXACT, which restarts
+// from the coefficient.
 template <int NC, bool EXACT, int TM>
 __device__ __forceinline__ void horner_c2(uint32_t tab, const uint32_t* __restrict__ gtab, uint32_t M,
                                           const uint32_t (&del)[NC], uint32_t d, uint32_t mask, uint32_t x0,
                                           uint32_t x1, uint32_t& a0, uint32_t& a1, uint32_t& pend0, uint32_t& pend1,
-                                          bool& hit) {
+                                          uint32_t& mx) {
   uint32_t p0 = 0, p1 = 0;
   a0 = a1 = 0;
 #pragma unroll
@@ -472,7 +472,7 @@ __device__ __forceinline__ void horner_c2(uint32_t tab, const uint32_t* __restri
           a0 = (a0 == M) ? 0u : v0;
           a1 = (a1 == M) ? 0u : v1;
         } else {
-          hit |= (v0 == M) | (v1 == M);
+          mx = max(mx, max(v0, v1));
           a0 = v0;
           a1 = v1;
         }
@@ -496,10 +496,9 @@ __device__ __forceinline__ void sweep_form_c(const LevelDesc& L, const uint32_t*
     const uint32_t x0 = 2 * (xs ? sload(xs, ix) : ix);
     const bool two = ix + 1 < nx;
     const uint32_t x1 = two ? 2 * (xs ? sload(xs, ix + 1) : ix + 1) : x0;
-    bool hit = false;
-    uint32_t p0, p1, a0, a1;
-    horner_c2<NC, false, TM>(tab, gtab, M, delb, d, mask, x0, x1, a0, a1, p0, p1, hit);
-    if (__ballot(hit)) horner_c2<NC, true, TM>(tab, gtab, M, delb, d, mask, x0, x1, a0, a1, p0, p1, hit);
+    uint32_t mx = 0, p0, p1, a0, a1;
+    horner_c2<NC, false, TM>(tab, gtab, M, delb, d, mask, x0, x1, a0, a1, p0, p1, mx);
+    if (__ballot(mx == M)) horner_c2<NC, true, TM>(tab, gtab, M, delb, d, mask, x0, x1, a0, a1, p0, p1, mx);
     c.add((p0 >> 1) & 1u, a0 == M, (a0 >> 1) & 1u);   // bit 1 of the marker 2M is 0
     if (two) c.add((p1 >> 1) & 1u, a1 == M, (a1 >> 1) & 1u);
   }
@@ -508,11 +507,11 @@ __device__ __forceinline__ void sweep_form_c(const LevelDesc& L, const uint32_t*
 
 // Sub-polynomial r of the split on a form C/D level (byte units): as
 // horner_class, with the index folded into the table's two periods.  Not
-// EXACT: a vanishing partial sum sets hit (the caller redoes the tuple).
+// EXACT: mx as in horner_c2 (the caller redoes the tuple).
 template <int NC, int MS, int R, bool FULL, int D, bool EXACT, int TM>
 __device__ __forceinline__ uint32_t horner_class_c(uint32_t tab, const uint32_t* __restrict__ gtab,
                                                    const uint32_t (&sdel)[NC], uint32_t M, uint32_t d, uint32_t sup,
-                                                   uint32_t Y, uint32_t& pend, bool& hit) {
+                                                   uint32_t Y, uint32_t& pend, uint32_t& mx) {
   uint32_t a = 0;
   if (FULL) {
     constexpr int TOP = D - ((D - R) % MS);
@@ -523,7 +522,7 @@ __device__ __forceinline__ uint32_t horner_class_c(uint32_t tab, const uint32_t*
       const uint32_t r = (i == TOP - MS) ? sdel[i] + Y : fold(a + sdel[i] + Y, M);
       const uint32_t v = tab_c<TM>(tab, gtab, M, r);
       if (EXACT) a = (a == M) ? 0u : v;
-      else { hit |= v == M; a = v; }
+      else { mx = max(mx, v); a = v; }
     }
     pend = 0;
     return a;
@@ -539,7 +538,7 @@ __device__ __forceinline__ uint32_t horner_class_c(uint32_t tab, const uint32_t*
       if (started) {
         const uint32_t v = tab_c<TM>(tab, gtab, M, fold(a + sdel[i] + p, M));
         if (EXACT) a = (a == M) ? 0u : v;
-        else { hit |= v == M; a = v; }
+        else { mx = max(mx, v); a = v; }
       }
       started = true;
       p = 0;
@@ -550,11 +549,11 @@ __device__ __forceinline__ uint32_t horner_class_c(uint32_t tab, const uint32_t*
 }
 
 // The MS sub-polynomials of a sparse row on a form C/D level in one pass
-// (as horner_classes_a); not EXACT: a vanishing partial sum sets hit.
+// (as horner_classes_a); not EXACT: mx as in horner_c2.
 template <int NC, int MS, bool EXACT, int TM>
 __device__ __forceinline__ void horner_classes_c(uint32_t tab, const uint32_t* __restrict__ gtab,
                                                  const uint32_t (&sdel)[NC], uint32_t M, uint32_t d, uint32_t sup,
-                                                 uint32_t Y, uint32_t (&a)[4], uint32_t (&pend)[4], bool& hit) {
+                                                 uint32_t Y, uint32_t (&a)[4], uint32_t (&pend)[4], uint32_t& mx) {
   uint32_t p[4] = {0, 0, 0, 0};
   bool st[4] = {false, false, false, false};
 #pragma unroll
@@ -570,7 +569,7 @@ __device__ __forceinline__ void horner_classes_c(uint32_t tab, const uint32_t* _
     const uint32_t v = tab_c<TM>(tab, gtab, M, go ? fold(a[r] + sdel[i] + p[r], M) : 0u);
     if (EXACT) a[r] = go ? ((a[r] == M) ? 0u : v) : a[r];
     else {
-      hit |= go && v == M;
+      mx = max(mx, v);                // entry 0 is no marker: 1 + gamma^0 = 2
       a[r] = go ? v : a[r];
     }
     if (present) {
@@ -626,71 +625,77 @@ __device__ __forceinline__ void sweep_split_c(const LevelDesc& L, const uint32_t
     const uint32_t Y = addmod(x2, x2, M);
     uint32_t p0, p1, p2, p3;
     uint32_t a0, a1, a2, a3;
-    bool hit = false;
-    if (FULL) {
-      a0 = horner_class_c<NC, 4, 0, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p0, hit);
-      a1 = horner_class_c<NC, 4, 1, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p1, hit);
-      a2 = horner_class_c<NC, 4, 2, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p2, hit);
-      a3 = horner_class_c<NC, 4, 3, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p3, hit);
-      if (__ballot(hit)) {
-        a0 = horner_class_c<NC, 4, 0, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p0, hit);
-        a1 = horner_class_c<NC, 4, 1, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p1, hit);
-        a2 = horner_class_c<NC, 4, 2, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p2, hit);
-        a3 = horner_class_c<NC, 4, 3, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p3, hit);
+    uint32_t mx = 0;
+    // the sub-polynomials, exact: restarting where a partial sum vanished
+    auto classes = [&](auto exact) {
+      constexpr bool EX = decltype(exact)::value;
+      if (FULL) {
+        a0 = horner_class_c<NC, 4, 0, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p0, mx);
+        a1 = horner_class_c<NC, 4, 1, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p1, mx);
+        a2 = horner_class_c<NC, 4, 2, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p2, mx);
+        a3 = horner_class_c<NC, 4, 3, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p3, mx);
+      } else {
+        uint32_t av[4], pv[4];
+        horner_classes_c<NC, 4, EX, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, mx);
+        a0 = av[0]; a1 = av[1]; a2 = av[2]; a3 = av[3];
+        p0 = pv[0]; p1 = pv[1]; p2 = pv[2]; p3 = pv[3];
       }
-    } else {
-      uint32_t av[4], pv[4];
-      horner_classes_c<NC, 4, false, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, hit);
-      if (__ballot(hit)) horner_classes_c<NC, 4, true, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, hit);
-      a0 = av[0]; a1 = av[1]; a2 = av[2]; a3 = av[3];
-      p0 = pv[0]; p1 = pv[1]; p2 = pv[2]; p3 = pv[3];
-    }
+    };
+    classes(std::false_type{});
     const uint32_t cls = FULL ? 0u : ((p0 >> 1) & 1u);
     const uint32_t uE = addmod(addmod(x2, p2, M), p0 ? M - p0 : 0u, M);
     const uint32_t uO = addmod(addmod(x2, p3, M), p1 ? M - p1 : 0u, M);
     const uint32_t vf = addmod(addmod(x, p1, M), p0 ? M - p0 : 0u, M);
     // Every index below stays under 2M, the table's two periods, whatever the
     // marker values (a_r <= M, folded bases and offsets < M), so no clamps are
-    // needed.  Any vanishing
-    // sub-polynomial, E or O value sends the wave through the patched form of
-    // the last step, which keeps the common path free of selects.
-    const bool rare = (a0 == M) | (a1 == M) | (a2 == M) | (a3 == M);
-    const uint32_t FE = fold(K2 - a0, M), FO = fold(K3 - a1, M);    // [0, M)
-    // the bases a2 + FE, a3 + FO folded once each ([0, M)), so that the two
-    // reads of each (offsets uE, uE + h below M) need no fold of their own
-    const uint32_t bE = fold(a2 + FE, M), bO = fold(a3 + FO, M);
-    const uint32_t Ep = tab_c<TM>(tab, gtab, M, bE + uE);
-    const uint32_t Em = tab_c<TM>(tab, gtab, M, bE + addmod(uE, h, M));
-    const uint32_t Op = tab_c<TM>(tab, gtab, M, bO + uO);
-    const uint32_t Om = tab_c<TM>(tab, gtab, M, bO + addmod(uO, h, M));
+    // needed.  Any vanishing partial sum, sub-polynomial, E or O value (mx, the
+    // largest value read, is then the marker) sends the wave through the exact
+    // classes and the patched form of the last step, which keeps the common
+    // path free of selects.
+    uint32_t Ep, Em, Op, Om;
+    auto halves = [&]() {
+      const uint32_t FE = fold(K2 - a0, M), FO = fold(K3 - a1, M);    // [0, M)
+      // the bases a2 + FE, a3 + FO folded once each ([0, M)), so that the two
+      // reads of each (offsets uE, uE + h below M) need no fold of their own
+      const uint32_t bE = fold(a2 + FE, M), bO = fold(a3 + FO, M);
+      Ep = tab_c<TM>(tab, gtab, M, bE + uE);
+      Em = tab_c<TM>(tab, gtab, M, bE + addmod(uE, h, M));
+      Op = tab_c<TM>(tab, gtab, M, bO + uO);
+      Om = tab_c<TM>(tab, gtab, M, bO + addmod(uO, h, M));
+    };
+    halves();
     uint32_t zs = 0, odd;
-    if (!__ballot(rare | (Ep == M) | (Em == M) | (Op == M) | (Om == M))) {
+    if (!__ballot(max(max(mx, max(Ep, Em)), max(Op, Om)) == M)) {
       const uint32_t G = fold(fold(a1 + K1 - a0, M), M) + M;       // [M, 2M)
       // O + F for the points x, -x (s even) and ix, -ix (s odd), folded once
       const uint32_t OFp = fold(Op + fold(G - Ep, M), M), OFm = fold(Om + fold(G - Em, M), M);
-      uint32_t u = 0;
+      uint32_t u = 0, mr = 0;
       uint32_t r[4];
-      bool anyz = false;
 #pragma unroll
       for (uint32_t s = 0; s < 4; ++s) {
         const uint32_t E = (s & 1u) ? Em : Ep;
         const uint32_t OF = (s & 1u) ? OFm : OFp;
         r[s] = tab_c<TM>(tab, gtab, M, OF + addmod(vf, s * step, M));
-        u += ((E ^ r[s]) >> 1) & 1u;
-        anyz |= r[s] == M;
+        u += (E ^ r[s]) & 2u;
+        mr = max(mr, r[s]);
       }
-      if (__ballot(anyz)) {
+      if (__ballot(mr == M)) {
         u = 0;
 #pragma unroll
         for (uint32_t s = 0; s < 4; ++s) {
           const uint32_t E = (s & 1u) ? Em : Ep;
           const bool z = r[s] == M;
           zs += z;
-          u += z ? 0u : (((E ^ r[s]) >> 1) & 1u);
+          u += z ? 0u : ((E ^ r[s]) & 2u);
         }
       }
+      u >>= 1;
       odd = (((a0 >> 1) ^ fix) & 1u) ? (4 - zs) - u : u;
     } else {
+      if (__ballot(mx == M)) {
+        classes(std::true_type{});
+        halves();
+      }
       // as in sweep_split_a: a vanished base is replaced by the term it leaves,
       // 1 or -1 times x^2 f_2 (x^2 f_3); here a vanished second term (no zero
       // region in the table) leaves the base itself, log 1; where E vanishes
@@ -748,18 +753,18 @@ __device__ __forceinline__ void sweep_split2_c(const LevelDesc& L, const uint32_
     if (it + 1 < nt) xnext = xt ? sload(xt, it + 1) : it + 1;
     const uint32_t Y = addmod(x, x, M);
     uint32_t p0, p1, a0, a1;
-    bool hit = false;
+    uint32_t mx = 0;
     if (FULL) {
-      a0 = horner_class_c<NC, 2, 0, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p0, hit);
-      a1 = horner_class_c<NC, 2, 1, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p1, hit);
-      if (__ballot(hit)) {
-        a0 = horner_class_c<NC, 2, 0, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p0, hit);
-        a1 = horner_class_c<NC, 2, 1, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p1, hit);
+      a0 = horner_class_c<NC, 2, 0, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p0, mx);
+      a1 = horner_class_c<NC, 2, 1, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p1, mx);
+      if (__ballot(mx == M)) {
+        a0 = horner_class_c<NC, 2, 0, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p0, mx);
+        a1 = horner_class_c<NC, 2, 1, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p1, mx);
       }
     } else {
       uint32_t av[4], pv[4];
-      horner_classes_c<NC, 2, false, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, hit);
-      if (__ballot(hit)) horner_classes_c<NC, 2, true, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, hit);
+      horner_classes_c<NC, 2, false, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, mx);
+      if (__ballot(mx == M)) horner_classes_c<NC, 2, true, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, mx);
       a0 = av[0]; a1 = av[1];
       p0 = pv[0]; p1 = pv[1];
     }
