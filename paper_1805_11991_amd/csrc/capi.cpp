@@ -33,7 +33,7 @@ hipError_t occupancy_count(uint32_t g, int coeff_bytes, uint32_t block, uint32_t
                            int* blocks_per_cu);
 hipError_t prepare_kernels();
 hipError_t prepare_vcount();
-hipError_t occupancy_vcount(uint32_t g, uint32_t block, uint32_t lds_bytes, int* blocks_per_cu);
+hipError_t occupancy_vcount(uint32_t g, bool frac, uint32_t block, uint32_t lds_bytes, int* blocks_per_cu);
 hipError_t launch_vcount(const VPlanDesc& V, const VPlanDesc* dV, int coeff_bytes, const void* codes, uint64_t n,
                          uint32_t lvl_lo, uint32_t lvl_hi, uint32_t tw, bool acc, int32_t* outN, uint32_t* outLv,
                          uint32_t* err, uint32_t grid, uint32_t block, hipStream_t s);
@@ -610,8 +610,7 @@ bool div_magic(uint64_t vmax, uint32_t div, uint32_t* m, uint32_t* s) {
 // which keeps large blocks of a split level reachable).  False when the image
 // would pass `limit` or the quotient constants do not exist.
 bool append_vlevel(std::vector<uint8_t>& img, const hwc::Field& F, uint32_t j, const std::vector<uint32_t>& xs,
-                   size_t i0, size_t i1, uint32_t p, uint32_t NC, uint32_t tw, bool bal, uint32_t sb, uint64_t limit,
-                   hwc::VLevel* out) {
+                   size_t i0, size_t i1, uint32_t p, uint32_t NC, uint32_t tw, uint64_t limit, hwc::VLevel* out) {
   const uint32_t KC = j + 1, M = (uint32_t)F.M;
   hwc::VLevel L{};
   L.pts = (uint32_t)(i1 - i0);
@@ -633,37 +632,21 @@ bool append_vlevel(std::vector<uint8_t>& img, const hwc::Field& F, uint32_t j, c
   }
   const uint64_t vend = vo + (uint64_t)L.nblk * KC * 512;
   const uint64_t cap = (uint64_t)(16 - NC) * 127;   // what the spare slots can add, in units of 127
-  // balanced form: coordinate 0 offset by 127 tw p, the others by 127 sb p^2
-  const uint64_t h = (p - 1) / 2, off0 = bal ? 127ull * tw * p : 0, offd = 127ull * sb * p * p;
-  if (std::max(vend, to + tw * Q) > limit || (off0 + to) / hwc::kVSlotUnit > cap) return false;
+  if (std::max(vend, to + tw * Q) > limit || to / hwc::kVSlotUnit > cap) return false;
   L.vo = (uint32_t)vo;
   L.to = (uint32_t)to;
-  if (bal) {
-    const uint64_t span0 = (uint64_t)tw * NC * h * h, spand = (uint64_t)sb * p * NC * h * h;
-    if (tw % sb || off0 < span0 || offd < spand || sb * p * p > cap || sb * p * p < 256) return false;
-    if (!div_magic(off0 + span0, tw * p, &L.m0, &L.s0)) return false;
-    if (off0 + span0 + L.to >= (1u << 24) || offd + spand >= (1u << 24)) return false;
-    const uint64_t div = (uint64_t)sb * p * p, m = ((1ull << 32) + div - 1) / div;
-    if (m >= (1u << 24) || (offd + spand) * (m * div - (1ull << 32)) >= (1ull << 32)) return false;
-    L.m1 = (uint32_t)m;
-    L.s1 = 32;
-  } else {
-    const uint64_t vmax1 = (uint64_t)NC * (p - 1) * (p - 1);
-    if (!div_magic(tw * vmax1, tw * p, &L.m0, &L.s0) || !div_magic(vmax1, p, &L.m1, &L.s1)) return false;
-    if (tw * vmax1 + L.to >= (1u << 24)) return false;   // coordinate 0 with the offset stays a 24-bit operand
-  }
+  const uint64_t vmax1 = (uint64_t)NC * (p - 1) * (p - 1);
+  if (!div_magic(tw * vmax1, tw * p, &L.m0, &L.s0) || !div_magic(vmax1, p, &L.m1, &L.s1)) return false;
+  if (tw * vmax1 + L.to >= (1u << 24)) return false;   // coordinate 0 with the offset stays a 24-bit operand
   L.nbm0 = (uint32_t)(0u - (uint32_t)((uint64_t)L.to * L.m0));
   if (img.size() < vend) img.resize(vend, 0);
-  // spare slots: coordinate 0 rows sum to (off0 + to) / 127, the others
-  // (balanced form) to sb p^2; the curve side holds 127 there
+  // spare slots: coordinate 0 rows sum to to / 127; the curve side holds 127 there
   for (uint32_t pi = 0; pi < L.nblk * 32; ++pi) {
-    for (uint32_t d = 0; d < (bal ? KC : 1u); ++d) {
-      uint32_t rest = (uint32_t)(d == 0 ? (off0 + L.to) / hwc::kVSlotUnit : offd / hwc::kVSlotUnit);
-      for (uint32_t k = NC; k < 16; ++k) {
-        const uint32_t a = rest < 127 ? rest : 127;
-        img[L.vo + ((size_t)((pi / 32) * KC + d) * 32 + pi % 32) * 16 + k] = (uint8_t)a;
-        rest -= a;
-      }
+    uint32_t rest = L.to / hwc::kVSlotUnit;
+    for (uint32_t k = NC; k < 16; ++k) {
+      const uint32_t a = rest < 127 ? rest : 127;
+      img[L.vo + ((size_t)(pi / 32) * KC * 32 + pi % 32) * 16 + k] = (uint8_t)a;
+      rest -= a;
     }
   }
   for (uint32_t pi = 0; pi < L.pts; ++pi) {
@@ -672,14 +655,7 @@ bool append_vlevel(std::vector<uint8_t>& img, const hwc::Field& F, uint32_t j, c
       uint32_t el = F.exp[(uint64_t)i * xs[i0 + pi] % M];   // x^i, packed coordinates
       for (uint32_t d = 0; d < KC; ++d, el /= p) {
         const uint32_t digit = el % p;
-        int32_t a;
-        if (bal) {
-          const int32_t db = 2 * digit > p ? (int32_t)digit - (int32_t)p : (int32_t)digit;
-          a = d == 0 ? (int32_t)(tw / sb) * db : (int32_t)p * db;
-        } else {
-          a = (int32_t)(d == 0 ? tw * digit : digit);
-        }
-        img[L.vo + ((size_t)(bb * KC + d) * 32 + row) * 16 + i] = (uint8_t)(int8_t)a;
+        img[L.vo + ((size_t)(bb * KC + d) * 32 + row) * 16 + i] = (uint8_t)(d == 0 ? tw * digit : digit);
       }
     }
   }
@@ -689,6 +665,106 @@ bool append_vlevel(std::vector<uint8_t>& img, const hwc::Field& F, uint32_t j, c
     for (uint32_t b = 0; b < tw; ++b) img[L.to + el * tw + b] = (uint8_t)(v >> (8 * b));
   }
   while (img.size() % 16) img.push_back(0);
+  *out = L;
+  return true;
+}
+
+// Appends the points xs[i0, i1) of level j to an image of the fractional form:
+// the word table at the first multiple of its size, the blocks where they fit.
+// False when the image would pass `limit` or two residues could share a cell.
+bool append_flevel(std::vector<uint8_t>& img, const hwc::Field& F, uint32_t j, const std::vector<uint32_t>& xs,
+                   size_t i0, size_t i1, uint32_t p, uint32_t NC, uint32_t wt, uint64_t limit, hwc::VLevel* out) {
+  const uint32_t KC = j + 1, M = (uint32_t)F.M, h = (p - 1) / 2, one = 1u << hwc::kFracBits;
+  hwc::VLevel L{};
+  L.pts = (uint32_t)(i1 - i0);
+  L.nblk = (L.pts + 31) / 32;
+  L.pad = L.nblk * 32 - L.pts;
+  const uint64_t tbytes = KC == 1 ? 256 : KC == 2 ? 4096 : 65536;
+  const uint64_t to = (img.size() + tbytes - 1) / tbytes * tbytes;
+  // the blocks in the gap before the table if it holds them, else behind it
+  const uint64_t gap = (img.size() + 15) / 16 * 16, blk = (uint64_t)L.nblk * KC * 1024;
+  const uint64_t vo = gap + blk <= to ? gap : to + tbytes;
+  const uint64_t end = std::max(to + tbytes, vo + blk);
+  if (end > limit) return false;
+  img.resize(end, 0);
+  L.vo = (uint32_t)vo;
+  L.to = (uint32_t)to;
+  // fractions of the residues: a 2^12 / p rounded, for balanced a
+  auto frac = [&](int32_t a) { return (int32_t)std::lround((double)a * one / p); };
+  std::vector<double> err(KC, 0.0);   // most the coordinate's sum can be off
+  for (uint32_t pi = 0; pi < L.pts; ++pi) {
+    std::vector<double> e(KC, 0.0);
+    for (uint32_t i = 0; i < NC; ++i) {
+      uint32_t el = F.exp[(uint64_t)i * xs[i0 + pi] % M];   // x^i, packed coordinates
+      for (uint32_t d = 0; d < KC; ++d, el /= p) {
+        const uint32_t digit = el % p;
+        const int32_t a = 2 * digit > p ? (int32_t)digit - (int32_t)p : (int32_t)digit, f = frac(a);
+        e[d] += std::fabs(f - (double)a * one / p) * h;
+        const int32_t hi = (int32_t)std::lround((double)f / wt), lo = f - (int32_t)wt * hi;
+        if (hi < -128 || hi > 127 || lo < -128 || lo > 127) return false;
+        const uint32_t slot = 2 * i;   // [slots 0 .. 15, 16 .. 31][row][16]
+        const size_t at = vo + ((size_t)((pi / 32) * KC + d) * 64 + slot / 16 * 32 + pi % 32) * 16 + slot % 16;
+        img[at] = (uint8_t)(int8_t)hi;
+        img[at + 1] = (uint8_t)(int8_t)lo;
+      }
+    }
+    for (uint32_t d = 0; d < KC; ++d) err[d] = std::max(err[d], e[d]);
+  }
+  // cells (unit 2^-bits of a turn) that the sums of residue r reach
+  auto reach = [&](uint32_t r, uint32_t bits, double er) {
+    const double unit = (double)one / (1u << bits), c = (double)r * one / p;
+    std::vector<uint32_t> v;
+    for (int64_t k = (int64_t)std::floor((c - er) / unit); k <= (int64_t)std::floor((c + er) / unit); ++k)
+      v.push_back((uint32_t)(k & ((1 << bits) - 1)));
+    return v;
+  };
+  // the residue of each 4-bit cell of the word index's coordinates
+  std::vector<std::vector<int32_t>> res(KC, std::vector<int32_t>(16, -1));
+  for (uint32_t d = 1; d < KC; ++d)
+    for (uint32_t r = 0; r < p; ++r)
+      for (uint32_t k : reach(r, 4, err[d] + 1e-6)) {
+        if (res[d][k] >= 0) return false;
+        res[d][k] = (int32_t)r;
+      }
+  // windows of coordinate 0: the rotations a residue can ask for; the bits of
+  // two residues' windows must not meet
+  std::vector<std::vector<uint32_t>> win(p);
+  uint32_t used = 0;
+  for (uint32_t r = 0; r < p; ++r) {
+    win[r] = reach(r, 5, err[0] + 1e-6);
+    uint32_t bits = 0;
+    for (uint32_t k : win[r]) bits |= (1u << k) | (1u << ((k + 1) & 31u));
+    if (used & bits) return false;
+    used |= bits;
+  }
+  const uint32_t words = KC == 1 ? 1u : KC == 2 ? 16u : KC == 3 ? 256u : 4096u;
+  for (uint32_t wi = 0; wi < words; ++wi) {
+    const uint32_t cell[4] = {0, wi & 15u, (wi >> 4) & 15u, (wi >> 8) & 15u};
+    bool any = true;
+    uint64_t base = 0, pw = p;
+    for (uint32_t d = 1; d < KC; ++d, pw *= p) {
+      if (res[d][cell[d]] < 0) any = false;
+      else base += (uint64_t)res[d][cell[d]] * pw;
+    }
+    uint32_t w = 0;
+    if (any)
+      for (uint32_t r = 0; r < p; ++r) {
+        const uint64_t el = base + r;
+        if (el == 0) {   // zero: exactly one bit of every window it can be seen through
+          for (size_t k = 0; k < win[r].size(); ++k)
+            if (k % 2 == 0) w |= 1u << ((win[r][k] + 1) & 31u);
+          if (win[r].size() > 2) return false;
+        } else if (F.log[el] & 1u) {
+          for (uint32_t k : win[r]) w |= (1u << k) | (1u << ((k + 1) & 31u));
+        }
+      }
+    if (KC <= 3) {
+      for (uint32_t l = 0; l < 64; ++l) std::memcpy(img.data() + to + (size_t)wi * 256 + 4 * l, &w, 4);
+    } else {   // address cell_1 << 8 | cell_2 << 12 | cell_3 << 4
+      for (uint32_t l = 0; l < 4; ++l)
+        std::memcpy(img.data() + to + (cell[1] << 8 | cell[2] << 12 | cell[3] << 4) + 4 * l, &w, 4);
+    }
+  }
   *out = L;
   return true;
 }
@@ -708,23 +784,63 @@ int build_vplan(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, uint32_t g, uint
   }
   struct Built { std::vector<uint8_t> img; hwc::VPlanDesc d{}; uint32_t lo, hi, tw; };
   std::vector<Built> passes;
-  // the balanced form where its constants exist (p = 11, 13; plan.h)
-  const uint32_t sb = p == 13 ? 2u : 4u;
-  auto use_bal = [&](uint32_t tw) { return (p == 13 || p == 11) && tw % sb == 0; };
+  const uint64_t limit = hwc::kLdsImageLimit;
+  // The fractional form: p <= kFracMaxP (from 17 on two residues share a cell),
+  // from genus 2 on, as genus 1's handful of points leaves reading the rows the
+  // bound (2^20 curves, p = 5: 16.9 us by residues, 18.0 by fractions), and in
+  // genus 4 from p = 7 on, as the few points of p = 3 and 5 do not repay the
+  // conflicts of four copies (2^19 curves: 39 and 77 us by residues, 55 and 83 by
+  // fractions; p = 7: 199 and 153).  Elsewhere it is faster at 500 rows and at
+  // 2^20: fcount_kernel.
+  if (p <= hwc::kFracMaxP && g >= 2 && (g < 4 || p >= 7)) {
+    // every level in one image (the largest table first, at offset 0), else the
+    // lower levels in one and the top level's points over several
+    const hwc::Field& F1 = P->fields[0]->F;
+    auto start = [&](uint32_t lo, uint32_t hi) {
+      Built b;
+      b.d.p = p; b.d.g = g; b.d.ncoef = NC; b.d.orbit = orbit;
+      b.d.frac = 127 / ((p - 1) / 2);
+      for (uint32_t cd = 1; cd < p; ++cd) b.d.nsmask |= (F1.log[cd] & 1u) << cd;
+      b.lo = lo; b.hi = hi; b.tw = 4;
+      return b;
+    };
+    auto levels = [&](Built& b) {
+      for (uint32_t j = b.hi + 1; j-- > b.lo;)
+        if (!append_flevel(b.img, P->fields[j]->F, j, xs[j], 0, xs[j].size(), p, NC, b.d.frac, limit, &b.d.lv[j]))
+          return false;
+      return true;
+    };
+    bool ok_all = true;
+    Built all = start(0, g - 1);
+    if (levels(all)) {
+      passes.push_back(std::move(all));
+    } else {
+      const uint32_t top = g - 1;
+      Built low = start(0, top - 1);
+      ok_all = levels(low);
+      if (ok_all) passes.push_back(std::move(low));
+      const uint64_t tb = top == 1 ? 4096 : 65536;
+      const size_t per = (size_t)((limit - tb) / ((uint64_t)(top + 1) * 1024)) * 32;
+      for (size_t i0 = 0; ok_all && i0 < xs[top].size(); i0 += per) {
+        Built b = start(top, top);
+        ok_all = append_flevel(b.img, P->fields[top]->F, top, xs[top], i0, std::min(xs[top].size(), i0 + per), p, NC,
+                               b.d.frac, limit, &b.d.lv[top]);
+        if (ok_all) passes.push_back(std::move(b));
+      }
+    }
+    if (!ok_all) passes.clear();
+  }
   auto start_pass = [&](uint32_t lo, uint32_t hi, uint32_t tw) {
     Built b;
     b.d.p = p; b.d.g = g; b.d.ncoef = NC; b.d.orbit = orbit;
-    b.d.bal = use_bal(tw) ? 1u : 0u;
-    b.d.sb = sb;
     b.lo = lo; b.hi = hi; b.tw = tw;
     return b;
   };
-  const uint64_t limit = hwc::kLdsImageLimit;
-  {   // every level in one image
+  if (passes.empty()) {   // every level in one image
     Built b = start_pass(0, g - 1, 4);
     bool fits = true;
     for (uint32_t j = 0; j < g && fits; ++j)
-      fits = append_vlevel(b.img, P->fields[j]->F, j, xs[j], 0, xs[j].size(), p, NC, 4, b.d.bal, sb, limit,
+      fits = append_vlevel(b.img, P->fields[j]->F, j, xs[j], 0, xs[j].size(), p, NC, 4, limit,
                            &b.d.lv[j]);
     if (fits) passes.push_back(std::move(b));
   }
@@ -734,7 +850,7 @@ int build_vplan(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, uint32_t g, uint
     if (g > 1) {
       Built b = start_pass(0, top - 1, 4);
       for (uint32_t j = 0; j < top; ++j)
-        if (!append_vlevel(b.img, P->fields[j]->F, j, xs[j], 0, xs[j].size(), p, NC, 4, b.d.bal, sb, limit,
+        if (!append_vlevel(b.img, P->fields[j]->F, j, xs[j], 0, xs[j].size(), p, NC, 4, limit,
                            &b.d.lv[j]))
           return HWC_OK;
       passes.push_back(std::move(b));
@@ -742,20 +858,21 @@ int build_vplan(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, uint32_t g, uint
     uint64_t Q = 1;
     for (uint32_t d = 0; d <= top; ++d) Q *= p;
     const uint32_t tw = 4 * Q <= 48 * 1024 ? 4 : 2;
-    if (tw == 2 && 2 * (p - 1) > 127) return HWC_OK;
+    if (tw == 2 && (2 * (p - 1) > 127 || g != 3)) return HWC_OK;
     const uint64_t blk_bytes = (uint64_t)(top + 1) * 512, room = limit - 1024 - tw * Q;
     if (tw * Q + 1024 >= limit || room < blk_bytes) return HWC_OK;
     const size_t per = (size_t)(room / blk_bytes) * 32;
     for (size_t i0 = 0; i0 < xs[top].size(); i0 += per) {
       Built b = start_pass(top, top, tw);
       const size_t i1 = std::min(xs[top].size(), i0 + per);
-      if (!append_vlevel(b.img, P->fields[top]->F, top, xs[top], i0, i1, p, NC, tw, b.d.bal, sb, limit,
+      if (!append_vlevel(b.img, P->fields[top]->F, top, xs[top], i0, i1, p, NC, tw, limit,
                          &b.d.lv[top]))
         return HWC_OK;
       passes.push_back(std::move(b));
     }
   }
   for (auto& b : passes) {
+    while (b.img.size() % 16) b.img.push_back(0);
     DevPlan::VPass v;
     v.lo = b.lo; v.hi = b.hi; v.tw = b.tw;
     v.desc = b.d;
@@ -768,12 +885,13 @@ int build_vplan(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, uint32_t g, uint
     P->dev_bytes += b.img.size() + sizeof(v.desc);
     c->table_bytes += b.img.size() + sizeof(v.desc);
     // the block size that keeps the most waves per CU resident (LDS holds one
-    // image per workgroup), unless a block size is set
+    // image per workgroup), unless a block size is set; the fractional form's
+    // images are too large for a small block to fill a CU, so it takes its own
     int best_waves = 0;
     for (uint32_t blk : {256u, 512u, 1024u}) {
-      if (block_opt && blk != block_opt) continue;
+      if (block_opt && blk != block_opt && !v.desc.frac) continue;
       int bpc = 0;
-      HIPX(c, hwc::occupancy_vcount(g, blk, v.desc.image_bytes, &bpc));
+      HIPX(c, hwc::occupancy_vcount(g, v.desc.frac != 0, blk, v.desc.image_bytes, &bpc));
       if (bpc * (int)blk > best_waves * 64) {
         best_waves = bpc * (int)blk / 64;
         v.block = blk;
@@ -2887,7 +3005,7 @@ int hwc_plan_info(hwc_ctx* c, uint32_t q, uint32_t g, uint32_t flags, hwc_level_
     levels[j].lds_bytes = P->vpath ? vmax : P->desc.image_bytes;
     levels[j].mfma = 0;
     for (const auto& v : P->vpasses)
-      if (P->vpath && v.lo <= j && j <= v.hi) levels[j].mfma = v.desc.bal ? 2u : 1u;
+      if (P->vpath && v.lo <= j && j <= v.hi) levels[j].mfma = q == 11 || q == 13 ? 2u : 1u;
   }
   return HWC_OK;
 }

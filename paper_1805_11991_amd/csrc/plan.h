@@ -213,15 +213,21 @@ struct VLevel {
   uint32_t nbm0;          // -to * m0 mod 2^32: coordinate 0 arrives with the table offset added
   uint32_t m1, s1;        // floor(v / p) = (v * m1) >> s1 for the other coordinates
 };
-// Balanced form (p = 11, 13): digits and coefficients in -(p-1)/2 .. (p-1)/2,
-// coefficients times sb, coordinates d >= 1 times p, coordinate 0 times tw/sb,
-// and constants in the spare K slots that make every value nonnegative and
-// a multiple of the divisor where it must vanish; then coordinate d >= 1 is
-// sb p D_d + 127 sb p^2 and its quotient by sb p^2 (>= 256) is one 24-bit
-// multiply-high by m1.
+// Fractional form (p <= 13): the points' coordinates come as fractions of
+// 2^kFracBits, a -> a 2^12 / p rounded (two int8 parts, matched by the codes
+// times `frac` and the codes on the curve side, 22 of 32 slots), so the
+// product is D_d 2^12 / p up to a small error and, modulo 2^12, the fraction of
+// D_d / p: no division by p.  Its top four bits are one of 16 cells, and no two
+// residues share a cell (16 / p - 2 err 2^-8 >= 1, checked for the points of
+// every level); coordinates 1 .. k - 1 give a word's index, coordinate 0's top
+// five bits rotate the word, whose two low bits then say square (00),
+// nonsquare (11) or zero (01 or 10).  Words: [cell_1 | cell_2 << 4][64 lanes],
+// or for four coordinates [cell_1 << 8 | cell_2 << 12 | cell_3 << 4][4 copies].
+constexpr uint32_t kFracBits = 12, kFracMaxP = 13;
 struct VPlanDesc {
   uint32_t p, g, ncoef, orbit;
-  uint32_t bal, sb;       // balanced form and the coefficient scale
+  uint32_t frac;          // fractional form: the curve side's weight floor(127 / ((p - 1) / 2)), else 0
+  uint32_t nsmask;        // fractional form: bit c set where the code c is a nonsquare of F_p
   uint32_t image_bytes;
   const uint32_t* image;
   VLevel lv[kMaxG];
