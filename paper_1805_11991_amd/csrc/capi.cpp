@@ -526,7 +526,7 @@ uint32_t lds_table_bytes(uint32_t form, uint64_t M) {
   if (form == hwc::kFormE) return align16((uint32_t)(2 * M));
   if (form == hwc::kFormF) {
     const uint64_t h1 = M / 2 + 1;   // entries of the half table
-    return align16((uint32_t)(2 * h1)) + align16((uint32_t)(4 * ((h1 + 31) / 32)));
+    return hwc::kFormFPlane + align16((uint32_t)(2 * h1));
   }
   if (form == hwc::kFormG) return align16((uint32_t)(4 * (M / 2 + 1)));
   return 0;
@@ -1087,19 +1087,14 @@ int get_plan(hwc_ctx* c, uint32_t q, uint32_t g, uint32_t orbit, DevPlan** out) 
       tab.resize(M);
       for (uint32_t i = 0; i < M; ++i) tab[i] = (uint16_t)F.zech[i];   // Z(i) < M, or the marker M
     } else if (form[j] == hwc::kFormF) {
-      // low halves of Z(0..M/2) (17-bit values, the marker M at M/2), padded
-      // to 16 bytes, then the 17th bits as u32 words (little-endian halves)
-      const uint32_t h1 = M / 2 + 1;
-      tab.assign(((size_t)h1 + 7) / 8 * 8, 0);
-      std::vector<uint32_t> bits(((size_t)h1 + 31) / 32, 0);
-      for (uint32_t i = 0; i < h1; ++i) {
-        const uint32_t z = F.zech[i];
-        tab[i] = (uint16_t)(z & 0xFFFFu);
-        bits[i >> 5] |= ((z >> 16) & 1u) << (i & 31);
-      }
-      for (uint32_t w : bits) {
-        tab.push_back((uint16_t)(w & 0xFFFFu));
-        tab.push_back((uint16_t)(w >> 16));
+      // Z(k), k = M/2 - i, for i = 0..M/2 (17-bit values, the marker M at i = 0):
+      // the plane of the 17th bits, then the low halves (plan.h)
+      const uint32_t h = M / 2, plane = hwc::kFormFPlane / 2;
+      tab.assign(plane + (size_t)h + 1, 0);
+      for (uint32_t i = 0; i <= h; ++i) {
+        const uint32_t z = F.zech[h - i];
+        tab[plane + i] = (uint16_t)(z & 0xFFFFu);
+        tab[i % plane] |= (uint16_t)(((z >> 16) & 1u) << (i / plane));
       }
     } else {
       // u32 halves of 2 Z(0..M/2) (byte units; little-endian pairs of u16),

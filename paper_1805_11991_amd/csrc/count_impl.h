@@ -407,6 +407,24 @@ __device__ __forceinline__ uint32_t fold(uint32_t v, uint32_t M) { return min(v,
 // as u32 entries in byte units, where it fits).
 constexpr int kTabC = 0, kTabD = 1, kTabE = 2, kTabF = 3, kTabG = 4;
 
+// |a - b|, one instruction
+__device__ __forceinline__ uint32_t absdiff(uint32_t a, uint32_t b) {
+  uint32_t r;
+  asm("v_sad_u32 %0, %1, %2, 0" : "=v"(r) : "v"(a), "s"(b));
+  return r;
+}
+
+// Form F: 2 Z((r/2) mod M) (plus M2 at most), not reduced; i2 is twice the entry
+// read, 0 at the zero marker.  k2 = 2k in one period; entries count from k = M/2
+// outwards, so that entry |k - M/2| serves both halves.
+__device__ __forceinline__ uint32_t half_f(uint32_t tab, uint32_t M2, uint32_t r, uint32_t& i2) {
+  const uint32_t h2 = M2 >> 1, k2 = fold(r, M2);
+  i2 = absdiff(k2, h2);
+  const uint32_t hi = ((uint32_t)lds_u16(tab + (i2 & (kFormFPlane - 2u))) >> (i2 >> 13)) & 1u;
+  const uint32_t z = lds_u16(tab + kFormFPlane + i2) | hi << 16;
+  return 2u * z + (k2 > h2 ? k2 : 0u);                  // < 2 M2
+}
+
 // Table entry at byte offset r in [0, 2 M2) (M2 = 2 M, the byte period):
 // 2 Z((r/2) mod M), or the marker M2 where 1 + gamma^(r/2) = 0.  Form E folds
 // the offset into its one period and doubles the entry it reads (its marker M
@@ -416,17 +434,9 @@ __device__ __forceinline__ uint32_t tab_c(uint32_t tab, const uint32_t* __restri
   if (TM == kTabD) return gtab[r >> 1];
   if (TM == kTabE) return 2u * lds_u16(tab + fold(r, M2));
   if (TM == kTabF) {
-    // k2 = 2k in one period; past the half, Z(k) = Z(M - k) + k mod M, so the
-    // entry is at j = min(k, M - k)
-    const uint32_t k2 = fold(r, M2), j2 = min(k2, M2 - k2);
-    const uint32_t bits = tab + ((2u * ((M2 >> 2) + 1u) + 15u) & ~15u);   // the 17th bits after the low halves
-    const uint32_t hi = (lds_u32(bits + 4u * (j2 >> 6)) >> ((j2 >> 1) & 31u)) & 1u;
-    const uint32_t z = lds_u16(tab + j2) | hi << 16;
-    // Z(k) is never 0 (1 + gamma^k = 1 has no solution), so the sum is reduced
-    // into [2, M2] instead of [0, M2): the same value for every entry, and the
-    // marker M (at j = M/2, not mirrored) becomes M2
-    const uint32_t y = 2u * z + (k2 > j2 ? k2 : 0u) - 2u;                 // < 2 M2 - 2
-    return fold(y, M2) + 2u;
+    uint32_t i2;
+    const uint32_t y = half_f(tab, M2, r, i2);
+    return i2 == 0 ? M2 : fold(y, M2);
   }
   if (TM == kTabG) {
     // entries 2 Z(j), j <= M/2, and 2 M2 at j = M/2 (the marker, which the
@@ -439,21 +449,50 @@ __device__ __forceinline__ uint32_t tab_c(uint32_t tab, const uint32_t* __restri
   return lds_u16(tab + r);
 }
 
+// As tab_c on the common path, where a marker read sends the wave to the exact
+// one and need not be told from an entry: met gathers what mark() recognises,
+// the largest entry, or in form F the lowest index read (entry 0 is the marker),
+// which spares the two additions that keep the marker apart in the reduced value.
+// Form F, bound by vector issue: 12 vector instructions and two reads where bits
+// in words behind entries counted from k = 0 took 17 (100 003 curves at g = 3, q =
+// 49: 7.98 -> 6.71 ms; 50 000 at g = 4, q = 17: 2.14 -> 1.82).
+template <int TM>
+__device__ __forceinline__ uint32_t tab_fast(uint32_t tab, const uint32_t* __restrict__ gtab, uint32_t M2, uint32_t r,
+                                             uint32_t& met) {
+  if (TM == kTabF) {
+    uint32_t i2;
+    const uint32_t y = half_f(tab, M2, r, i2);
+    met = min(met, i2);
+    return fold(y, M2);
+  }
+  const uint32_t v = tab_c<TM>(tab, gtab, M2, r);
+  met = max(met, v);
+  return v;
+}
+template <int TM>
+constexpr uint32_t kUnmet = TM == kTabF ? ~0u : 0u;     // met before the first read
+template <int TM>
+__device__ __forceinline__ bool mark(uint32_t met, uint32_t M2) {
+  return met == (TM == kTabF ? 0u : M2);
+}
+
 // As tab_c where only the parity of the log (bit 1 of the result) and the
 // marker (zero) are wanted, the last step of a point.  The half tables need no
 // second half of the entry and no reduction for it: with j = min(k, M - k),
-// Z(k) = Z(j) + (k > M / 2 ? k : 0) mod M, and M is even.  11 vector
-// instructions and one read instead of about 17 and two (form F; 100 003 curves
-// at g = 3, q = 49: 8.74 -> 8.19 ms).
+// Z(k) = Z(j) + (k > M / 2 ? k : 0) mod M, and M is even.  7 vector
+// instructions and one read in form F instead of 13 and two.
 template <int TM>
 __device__ __forceinline__ uint32_t tab_parity(uint32_t tab, const uint32_t* __restrict__ gtab, uint32_t M2, uint32_t r,
                                                bool& zero) {
-  if (TM == kTabF || TM == kTabG) {
+  if (TM == kTabF) {
+    const uint32_t h2 = M2 >> 1, k2 = fold(r, M2), i2 = absdiff(k2, h2);
+    zero = i2 == 0;                                     // k = M / 2
+    return (lds_u16(tab + kFormFPlane + i2) << 1) + (k2 > h2 ? k2 : 0u);   // bit 1: no carry reaches it
+  }
+  if (TM == kTabG) {
     const uint32_t k2 = fold(r, M2), j2 = min(k2, M2 - k2);
-    zero = 2u * j2 == M2;                             // k = M / 2
-    const uint32_t t = k2 > j2 ? k2 : 0u;
-    if (TM == kTabF) return (lds_u16(tab + j2) << 1) + t;      // bit 1: no carry reaches it
-    return lds_u32(tab + 2u * j2) + t;
+    zero = 2u * j2 == M2;                               // k = M / 2
+    return lds_u32(tab + 2u * j2) + (k2 > j2 ? k2 : 0u);
   }
   const uint32_t v = tab_c<TM>(tab, gtab, M2, r);
   zero = v == M2;
@@ -468,14 +507,14 @@ __device__ __forceinline__ uint32_t tab_parity(uint32_t tab, const uint32_t* __r
 //
 // Form C/D relative Horner for two x at once (index folded into the table's
 // two periods; reads of both chains inside one uniform branch per position).
-// Not EXACT: mx is the largest value read -- M, the marker, if a partial sum
-// vanished -- and the caller then redoes the pair with EXACT, which restarts
-// from the coefficient.
+// Not EXACT: met is as in tab_fast -- a partial sum vanished where mark() says so
+// -- and the caller then redoes the pair with EXACT, which restarts from the
+// coefficient.
 template <int NC, bool EXACT, int TM>
 __device__ __forceinline__ void horner_c2(uint32_t tab, const uint32_t* __restrict__ gtab, uint32_t M,
                                           const uint32_t (&del)[NC], uint32_t d, uint32_t mask, uint32_t x0,
                                           uint32_t x1, uint32_t& a0, uint32_t& a1, uint32_t& pend0, uint32_t& pend1,
-                                          uint32_t& mx) {
+                                          uint32_t& met) {
   uint32_t p0 = 0, p1 = 0;
   a0 = a1 = 0;
 #pragma unroll
@@ -486,15 +525,13 @@ __device__ __forceinline__ void horner_c2(uint32_t tab, const uint32_t* __restri
       if ((mask >> i) & 1u) {
         const uint32_t r0 = min(a0 + del[i] + p0, a0 + del[i] + p0 - M);   // < 2M
         const uint32_t r1 = min(a1 + del[i] + p1, a1 + del[i] + p1 - M);
-        const uint32_t v0 = tab_c<TM>(tab, gtab, M, r0);
-        const uint32_t v1 = tab_c<TM>(tab, gtab, M, r1);
         if (EXACT) {
+          const uint32_t v0 = tab_c<TM>(tab, gtab, M, r0), v1 = tab_c<TM>(tab, gtab, M, r1);
           a0 = (a0 == M) ? 0u : v0;
           a1 = (a1 == M) ? 0u : v1;
         } else {
-          mx = max(mx, max(v0, v1));
-          a0 = v0;
-          a1 = v1;
+          a0 = tab_fast<TM>(tab, gtab, M, r0, met);
+          a1 = tab_fast<TM>(tab, gtab, M, r1, met);
         }
         p0 = p1 = 0;
       }
@@ -516,9 +553,9 @@ __device__ __forceinline__ void sweep_form_c(const LevelDesc& L, const uint32_t*
     const uint32_t x0 = 2 * (xs ? sload(xs, ix) : ix);
     const bool two = ix + 1 < nx;
     const uint32_t x1 = two ? 2 * (xs ? sload(xs, ix + 1) : ix + 1) : x0;
-    uint32_t mx = 0, p0, p1, a0, a1;
-    horner_c2<NC, false, TM>(tab, gtab, M, delb, d, mask, x0, x1, a0, a1, p0, p1, mx);
-    if (__ballot(mx == M)) horner_c2<NC, true, TM>(tab, gtab, M, delb, d, mask, x0, x1, a0, a1, p0, p1, mx);
+    uint32_t met = kUnmet<TM>, p0, p1, a0, a1;
+    horner_c2<NC, false, TM>(tab, gtab, M, delb, d, mask, x0, x1, a0, a1, p0, p1, met);
+    if (__ballot(mark<TM>(met, M))) horner_c2<NC, true, TM>(tab, gtab, M, delb, d, mask, x0, x1, a0, a1, p0, p1, met);
     c.add((p0 >> 1) & 1u, a0 == M, (a0 >> 1) & 1u);   // bit 1 of the marker 2M is 0
     if (two) c.add((p1 >> 1) & 1u, a1 == M, (a1 >> 1) & 1u);
   }
@@ -527,11 +564,11 @@ __device__ __forceinline__ void sweep_form_c(const LevelDesc& L, const uint32_t*
 
 // Sub-polynomial r of the split on a form C/D level (byte units): as
 // horner_class, with the index folded into the table's two periods.  Not
-// EXACT: mx as in horner_c2 (the caller redoes the tuple).
+// EXACT: met as in horner_c2 (the caller redoes the tuple).
 template <int NC, int MS, int R, bool FULL, int D, bool EXACT, int TM>
 __device__ __forceinline__ uint32_t horner_class_c(uint32_t tab, const uint32_t* __restrict__ gtab,
                                                    const uint32_t (&sdel)[NC], uint32_t M, uint32_t d, uint32_t sup,
-                                                   uint32_t Y, uint32_t& pend, uint32_t& mx) {
+                                                   uint32_t Y, uint32_t& pend, uint32_t& met) {
   uint32_t a = 0;
   if (FULL) {
     constexpr int TOP = D - ((D - R) % MS);
@@ -540,9 +577,12 @@ __device__ __forceinline__ uint32_t horner_class_c(uint32_t tab, const uint32_t*
       // index < 3M, folded below 2M, which every form reads; the first step
       // (a = 0) is below 2M already
       const uint32_t r = (i == TOP - MS) ? sdel[i] + Y : fold(a + sdel[i] + Y, M);
-      const uint32_t v = tab_c<TM>(tab, gtab, M, r);
-      if (EXACT) a = (a == M) ? 0u : v;
-      else { mx = max(mx, v); a = v; }
+      if (EXACT) {
+        const uint32_t v = tab_c<TM>(tab, gtab, M, r);
+        a = (a == M) ? 0u : v;
+      } else {
+        a = tab_fast<TM>(tab, gtab, M, r, met);
+      }
     }
     pend = 0;
     return a;
@@ -556,9 +596,13 @@ __device__ __forceinline__ uint32_t horner_class_c(uint32_t tab, const uint32_t*
     if (started) p = addmod(p, Y, M);
     if ((sup >> i) & 1u) {
       if (started) {
-        const uint32_t v = tab_c<TM>(tab, gtab, M, fold(a + sdel[i] + p, M));
-        if (EXACT) a = (a == M) ? 0u : v;
-        else { mx = max(mx, v); a = v; }
+        const uint32_t r = fold(a + sdel[i] + p, M);
+        if (EXACT) {
+          const uint32_t v = tab_c<TM>(tab, gtab, M, r);
+          a = (a == M) ? 0u : v;
+        } else {
+          a = tab_fast<TM>(tab, gtab, M, r, met);
+        }
       }
       started = true;
       p = 0;
@@ -569,11 +613,11 @@ __device__ __forceinline__ uint32_t horner_class_c(uint32_t tab, const uint32_t*
 }
 
 // The MS sub-polynomials of a sparse row on a form C/D level in one pass
-// (as horner_classes_a); not EXACT: mx as in horner_c2.
+// (as horner_classes_a); not EXACT: met as in horner_c2.
 template <int NC, int MS, bool EXACT, int TM>
 __device__ __forceinline__ void horner_classes_c(uint32_t tab, const uint32_t* __restrict__ gtab,
                                                  const uint32_t (&sdel)[NC], uint32_t M, uint32_t d, uint32_t sup,
-                                                 uint32_t Y, uint32_t (&a)[4], uint32_t (&pend)[4], uint32_t& mx) {
+                                                 uint32_t Y, uint32_t (&a)[4], uint32_t (&pend)[4], uint32_t& met) {
   uint32_t p[4] = {0, 0, 0, 0};
   bool st[4] = {false, false, false, false};
 #pragma unroll
@@ -586,10 +630,12 @@ __device__ __forceinline__ void horner_classes_c(uint32_t tab, const uint32_t* _
     if (st[r]) p[r] = addmod(p[r], Y, M);
     const bool go = present && st[r];
     // a position that does not step reads entry 0 on every lane (a broadcast)
-    const uint32_t v = tab_c<TM>(tab, gtab, M, go ? fold(a[r] + sdel[i] + p[r], M) : 0u);
-    if (EXACT) a[r] = go ? ((a[r] == M) ? 0u : v) : a[r];
-    else {
-      mx = max(mx, v);                // entry 0 is no marker: 1 + gamma^0 = 2
+    const uint32_t at = go ? fold(a[r] + sdel[i] + p[r], M) : 0u;   // 0 is no marker: 1 + gamma^0 = 2
+    if (EXACT) {
+      const uint32_t v = tab_c<TM>(tab, gtab, M, at);
+      a[r] = go ? ((a[r] == M) ? 0u : v) : a[r];
+    } else {
+      const uint32_t v = tab_fast<TM>(tab, gtab, M, at, met);
       a[r] = go ? v : a[r];
     }
     if (present) {
@@ -645,18 +691,18 @@ __device__ __forceinline__ void sweep_split_c(const LevelDesc& L, const uint32_t
     const uint32_t Y = addmod(x2, x2, M);
     uint32_t p0, p1, p2, p3;
     uint32_t a0, a1, a2, a3;
-    uint32_t mx = 0;
+    uint32_t met = kUnmet<TM>;
     // the sub-polynomials, exact: restarting where a partial sum vanished
     auto classes = [&](auto exact) {
       constexpr bool EX = decltype(exact)::value;
       if (FULL) {
-        a0 = horner_class_c<NC, 4, 0, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p0, mx);
-        a1 = horner_class_c<NC, 4, 1, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p1, mx);
-        a2 = horner_class_c<NC, 4, 2, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p2, mx);
-        a3 = horner_class_c<NC, 4, 3, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p3, mx);
+        a0 = horner_class_c<NC, 4, 0, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p0, met);
+        a1 = horner_class_c<NC, 4, 1, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p1, met);
+        a2 = horner_class_c<NC, 4, 2, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p2, met);
+        a3 = horner_class_c<NC, 4, 3, FULL, D, EX, TM>(tab, gtab, sdel, M, d, sup, Y, p3, met);
       } else {
         uint32_t av[4], pv[4];
-        horner_classes_c<NC, 4, EX, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, mx);
+        horner_classes_c<NC, 4, EX, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, met);
         a0 = av[0]; a1 = av[1]; a2 = av[2]; a3 = av[3];
         p0 = pv[0]; p1 = pv[1]; p2 = pv[2]; p3 = pv[3];
       }
@@ -668,24 +714,25 @@ __device__ __forceinline__ void sweep_split_c(const LevelDesc& L, const uint32_t
     const uint32_t vf = addmod(addmod(x, p1, M), p0 ? M - p0 : 0u, M);
     // Every index below stays under 2M, the table's two periods, whatever the
     // marker values (a_r <= M, folded bases and offsets < M), so no clamps are
-    // needed.  Any vanishing partial sum, sub-polynomial, E or O value (mx, the
-    // largest value read, is then the marker) sends the wave through the exact
+    // needed.  Any vanishing partial sum, sub-polynomial, E or O value (met) sends the wave through the exact
     // classes and the patched form of the last step, which keeps the common
     // path free of selects.
     uint32_t Ep, Em, Op, Om;
-    auto halves = [&]() {
+    auto halves = [&](auto exact) {
+      constexpr bool EX = decltype(exact)::value;
       const uint32_t FE = fold(K2 - a0, M), FO = fold(K3 - a1, M);    // [0, M)
       // the bases a2 + FE, a3 + FO folded once each ([0, M)), so that the two
       // reads of each (offsets uE, uE + h below M) need no fold of their own
       const uint32_t bE = fold(a2 + FE, M), bO = fold(a3 + FO, M);
-      Ep = tab_c<TM>(tab, gtab, M, bE + uE);
-      Em = tab_c<TM>(tab, gtab, M, bE + addmod(uE, h, M));
-      Op = tab_c<TM>(tab, gtab, M, bO + uO);
-      Om = tab_c<TM>(tab, gtab, M, bO + addmod(uO, h, M));
+      const auto get = [&](uint32_t r) { return EX ? tab_c<TM>(tab, gtab, M, r) : tab_fast<TM>(tab, gtab, M, r, met); };
+      Ep = get(bE + uE);
+      Em = get(bE + addmod(uE, h, M));
+      Op = get(bO + uO);
+      Om = get(bO + addmod(uO, h, M));
     };
-    halves();
+    halves(std::false_type{});
     uint32_t zs = 0, odd;
-    if (!__ballot(max(max(mx, max(Ep, Em)), max(Op, Om)) == M)) {
+    if (!__ballot(mark<TM>(met, M))) {
       const uint32_t G = fold(fold(a1 + K1 - a0, M), M) + M;       // [M, 2M)
       // O + F for the points x, -x (s even) and ix, -ix (s odd), folded once
       const uint32_t OFp = fold(Op + fold(G - Ep, M), M), OFm = fold(Om + fold(G - Em, M), M);
@@ -718,9 +765,9 @@ __device__ __forceinline__ void sweep_split_c(const LevelDesc& L, const uint32_t
       u >>= 1;
       odd = (((a0 >> 1) ^ fix) & 1u) ? (4 - zs) - u : u;
     } else {
-      if (__ballot(mx == M)) {
+      if (__ballot(mark<TM>(met, M))) {
         classes(std::true_type{});
-        halves();
+        halves(std::true_type{});
       }
       // as in sweep_split_a: a vanished base is replaced by the term it leaves,
       // 1 or -1 times x^2 f_2 (x^2 f_3); here a vanished second term (no zero
@@ -779,18 +826,18 @@ __device__ __forceinline__ void sweep_split2_c(const LevelDesc& L, const uint32_
     if (it + 1 < nt) xnext = xt ? sload(xt, it + 1) : it + 1;
     const uint32_t Y = addmod(x, x, M);
     uint32_t p0, p1, a0, a1;
-    uint32_t mx = 0;
+    uint32_t met = kUnmet<TM>;
     if (FULL) {
-      a0 = horner_class_c<NC, 2, 0, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p0, mx);
-      a1 = horner_class_c<NC, 2, 1, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p1, mx);
-      if (__ballot(mx == M)) {
-        a0 = horner_class_c<NC, 2, 0, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p0, mx);
-        a1 = horner_class_c<NC, 2, 1, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p1, mx);
+      a0 = horner_class_c<NC, 2, 0, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p0, met);
+      a1 = horner_class_c<NC, 2, 1, FULL, D, false, TM>(tab, gtab, sdel, M, d, sup, Y, p1, met);
+      if (__ballot(mark<TM>(met, M))) {
+        a0 = horner_class_c<NC, 2, 0, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p0, met);
+        a1 = horner_class_c<NC, 2, 1, FULL, D, true, TM>(tab, gtab, sdel, M, d, sup, Y, p1, met);
       }
     } else {
       uint32_t av[4], pv[4];
-      horner_classes_c<NC, 2, false, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, mx);
-      if (__ballot(mx == M)) horner_classes_c<NC, 2, true, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, mx);
+      horner_classes_c<NC, 2, false, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, met);
+      if (__ballot(mark<TM>(met, M))) horner_classes_c<NC, 2, true, TM>(tab, gtab, sdel, M, d, sup, Y, av, pv, met);
       a0 = av[0]; a1 = av[1];
       p0 = pv[0]; p1 = pv[1];
     }

@@ -16,10 +16,12 @@
 //           into the period once more than form C and doubles the entry it
 //           reads, so it shares form C's code; twice the field size of form C
 //           fits in LDS.
-//   form F  (M <= 131070)  "half table": Z(k) for k = 0..M/2 only, as u16
-//           low halves followed by a bitmap of the 17th bits; the other half
-//           follows from Z(-k) = Z(k) - k (1 + g^-k = g^-k (1 + g^k)), so
-//           Z(k) = Z(M - k) + k mod M for k > M/2.  Two reads per lookup.
+//   form F  (M <= 131070)  "half table": Z(k) for k = 0..M/2 only, entry
+//           i = M/2 - k, as u16 low halves; the 17th bit of entry i is bit
+//           i >> 12 of word i mod 4096 of a plane of kFormFPlane bytes before
+//           them.  The other half follows from Z(-k) = Z(k) - k
+//           (1 + g^-k = g^-k (1 + g^k)), so Z(k) = Z(M - k) + k mod M for
+//           k > M/2: both halves read entry |k - M/2|.  Two reads per lookup.
 //   form D  (any M)  the form C layout with u32 entries, kept in device
 //           memory (L2/MALL-resident) when the level does not fit in LDS.
 //   emb     q u32 entries: log of the F_q code c in F_{q^j}, or M for c = 0.
@@ -40,6 +42,7 @@ constexpr uint32_t kFormAMaxM = 10922;   // 6M must fit in u16
 constexpr uint32_t kFormCMaxM = 32767;   // M must fit in 15 bits
 constexpr uint32_t kFormEMaxM = 65534;   // M (the zero marker) must fit in u16
 constexpr uint32_t kFormFMaxM = 131070;  // M must fit in 17 bits, M/2 + 1 entries in the half table
+constexpr uint32_t kFormFPlane = 8192;   // 4096 u16 words: 16 bits each reach the largest M / 2
 // Form G: the half table of form F as u32 entries in byte units (one read, no
 // bit plane), used where its 4 (M/2 + 1) bytes fit the LDS image
 constexpr int kWave = 64;
