@@ -59,7 +59,7 @@ hipError_t prepare_hist_small();
 hipError_t launch_norm(const PlanDesc& P, const PlanDesc* dP, int coeff_bytes, const void* codes, const uint32_t* perm,
                        const uint64_t* tiles, const uint32_t* ntiles, uint32_t* queue, int32_t* outN, uint32_t* outLv,
                        uint32_t plog, uint32_t* acc, uint32_t* done, uint32_t grid, uint32_t block, hipStream_t s);
-hipError_t occupancy_norm(uint32_t block, uint32_t lds_bytes, int* blocks_per_cu);
+hipError_t occupancy_norm(bool pair, uint32_t block, uint32_t lds_bytes, int* blocks_per_cu);
 hipError_t prepare_norm();
 hipError_t launch_bucket_small(const BucketJob& J, uint32_t* err, hipStream_t s);
 hipError_t launch_bucket_small_batch(const BucketJob* hjobs, const BucketJob* jobs, uint32_t njobs, uint32_t* err,
@@ -915,7 +915,7 @@ constexpr uint32_t kNormMinPrime = 37, kNormMinPower = 81;
 
 // The image of norm_impl.h for (q, 2), or an empty one when it does not fit.
 // Fills the offsets of D.
-std::vector<uint8_t> norm_image(const hwc::Field& F1, uint32_t q, bool fold, hwc::NormDesc* D) {
+std::vector<uint8_t> norm_image(const hwc::Field& F1, uint32_t q, bool fold, bool pair, hwc::NormDesc* D) {
   const uint32_t M = q - 1, H = M / 2, zrow = fold ? 2 * M : 3 * M, rows = zrow + 2 * M + 1;
   // slots of 16 bytes below q = 65, where the quotient's constant, 2^32 / (q <<
   // esh), would not fit 24 bits with 4
@@ -923,7 +923,7 @@ std::vector<uint8_t> norm_image(const hwc::Field& F1, uint32_t q, bool fold, hwc
   uint32_t srow = 1;
   while (srow < 4 * M) srow *= 2;
   const uint32_t S = srow * hwc::kNormRow, nfin = 2 * srow + 2 * M;
-  const uint64_t need = (uint64_t)rows * hwc::kNormRow + align16(q << esh) + align16(nfin);
+  const uint64_t need = (uint64_t)rows * hwc::kNormRow + align16(q << esh) + align16(nfin * (pair ? 2 : 1));
   if (need > kLdsLimit) return {};
   std::vector<uint8_t> img((size_t)need, 0);
   auto put32 = [&](size_t off, uint32_t v) { std::memcpy(img.data() + off, &v, 4); };
@@ -948,8 +948,26 @@ std::vector<uint8_t> norm_image(const hwc::Field& F1, uint32_t q, bool fold, hwc
   D->esh = esh;
   D->fin_off = (uint32_t)off;
   const uint32_t par = H % 2 ? 0u : 1u;    // parity of log(-v), v a nonsquare
+  D->pair = pair ? 1u : 0u;
   for (uint32_t i = 0; i < nfin; ++i) {
     const int64_t d = (int64_t)i - (int64_t)srow;
+    if (pair) {
+      // d = log(v B) - log A: the odd logs among A + vB, A - vB where log A has
+      // parity pa, plus 254 where one is zero
+      for (uint32_t pa = 0; pa < 2; ++pa) {
+        uint32_t v = 0;
+        if (d < -(int64_t)M) {
+          v = 2 * (uint32_t)(d & 1);                                // A = 0: +-v B
+        } else if (d >= (int64_t)(5 * M) / 2) {
+          v = 2 * pa;                                               // B = 0: A twice
+        } else {
+          const uint32_t dm = (uint32_t)((d + 2 * M) % M);
+          for (uint32_t z : {F1.zech[dm], F1.zech[(dm + H) % M]}) v += z == M ? 254u : ((z + pa) & 1u);
+        }
+        img[off + 2 * i + pa] = (uint8_t)v;
+      }
+      continue;
+    }
     uint32_t v;
     if (d < -(int64_t)M) v = par;                               // E = 0: -v O^2
     else if (d >= (int64_t)(5 * M) / 2) v = 0;                  // O = 0: E^2
@@ -967,13 +985,14 @@ int build_norm(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, const Tuning& T, 
   if (q < (e == 1 ? kNormMinPrime : kNormMinPower) || !T.split || top.M < T.split_min_m || (T.device_tables & 3u)) return HWC_OK;
   const hwc::Field& F1 = P->fields[0]->F;
   hwc::NormDesc D{};
-  std::vector<uint8_t> img = norm_image(F1, q, false, &D);
-  if (img.empty()) img = norm_image(F1, q, true, &D);
+  const bool pair = e == 1 && q % 4 == 1;
+  std::vector<uint8_t> img = norm_image(F1, q, false, pair, &D);
+  if (img.empty()) img = norm_image(F1, q, true, pair, &D);
   if (img.empty()) return HWC_OK;
   std::vector<uint32_t> tm;
   if (e == 1) {
     // rows i < 6 of t: binom(j, i) t^(j-i) mod q, times 2^esh, pairs j = 2k, 2k + 1
-    const uint64_t qs = (uint64_t)q << D.esh, m = ((1ull << 32) + qs - 1) / qs, vmax = (7ull * M * M) << D.esh;
+    const uint64_t qs = (uint64_t)q << D.esh, m = ((1ull << 32) + qs - 1) / qs, vmax = (7ull * q * M) << D.esh;
     if (m >= (1u << 24) || vmax >= (1u << 24) || vmax * (m * qs - (1ull << 32)) >= (1ull << 32)) return HWC_OK;
     D.qm = (uint32_t)m;
     uint32_t binom[7][7] = {};
@@ -995,7 +1014,7 @@ int build_norm(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, const Tuning& T, 
   for (uint32_t b : {256u, 512u, 1024u}) {
     if (T.block && b != T.block) continue;
     int n = 0;
-    HIPX(c, hwc::occupancy_norm(b, (uint32_t)img.size(), &n));
+    HIPX(c, hwc::occupancy_norm(pair, b, (uint32_t)img.size(), &n));
     if (n * (int)(b / hwc::kWave) > best) {
       best = n * (int)(b / hwc::kWave);
       block = b;

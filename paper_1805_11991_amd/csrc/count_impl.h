@@ -1169,10 +1169,10 @@ __device__ __forceinline__ void process_job_tile(const JobDesc& J, uint32_t lb, 
   if constexpr (GMAX >= 2) {
     if (J.norm) {   // genus 2, level 2 by norms
       if (J.cb == 1)
-        norm_tile<int8_t, 8>(P, static_cast<const int8_t*>(J.codes), J.perm, w, J.outN, nullptr, tile, part, plog, J.acc,
+        norm_tile<int8_t, 8, 2>(P, static_cast<const int8_t*>(J.codes), J.perm, w, J.outN, nullptr, tile, part, plog, J.acc,
                           J.done);
       else
-        norm_tile<int16_t, 8>(P, static_cast<const int16_t*>(J.codes), J.perm, w, J.outN, nullptr, tile, part, plog, J.acc,
+        norm_tile<int16_t, 8, 2>(P, static_cast<const int16_t*>(J.codes), J.perm, w, J.outN, nullptr, tile, part, plog, J.acc,
                            J.done);
       return;
     }

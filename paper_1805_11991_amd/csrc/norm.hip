@@ -11,7 +11,7 @@
 namespace hwc {
 namespace {
 
-template <typename CT, int WPE>
+template <typename CT, int WPE, int PAIR>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))) void norm_kernel(const PlanDesc* __restrict__ Pd, const CT* __restrict__ codes,
                                                     const uint32_t* __restrict__ perm,
                                                     const uint64_t* __restrict__ tiles,
@@ -30,7 +30,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))) voi
     if (lane == 0) v = atomicAdd(queue, 1u);
     const uint32_t t = uniform(v);
     if (t >= entries) break;
-    norm_tile<CT, WPE == 8 ? 4 : 8>(P, codes, perm, sload64(tiles, t >> plog), outN, outLv, t >> plog, t & ((1u << plog) - 1u), plog, acc,
+    norm_tile<CT, WPE == 8 ? 4 : 8, PAIR>(P, codes, perm, sload64(tiles, t >> plog), outN, outLv, t >> plog, t & ((1u << plog) - 1u), plog, acc,
                   done);
   }
 }
@@ -45,33 +45,45 @@ hipError_t launch_norm(const PlanDesc& P, const PlanDesc* dP, int coeff_bytes, c
                        const uint64_t* tiles, const uint32_t* ntiles, uint32_t* queue, int32_t* outN, uint32_t* outLv,
                        uint32_t plog, uint32_t* acc, uint32_t* done, uint32_t grid, uint32_t block, hipStream_t s) {
   if (P.g != 2 || !P.norm.kind || P.image_bytes > kLdsImageLimit) return hipErrorInvalidValue;
-#define HWC_NORM(CT, W)                                                                                      \
-  hipLaunchKernelGGL((norm_kernel<CT, W>), dim3(grid), dim3(block), P.image_bytes, s, dP,                     \
+#define HWC_NORM(CT, W, PR)                                                                                  \
+  hipLaunchKernelGGL((norm_kernel<CT, W, PR>), dim3(grid), dim3(block), P.image_bytes, s, dP,                 \
                      static_cast<const CT*>(codes), perm, tiles, ntiles, queue, outN, outLv, plog, acc, done)
+#define HWC_NORM_W(CT, W)               \
+  do {                                  \
+    if (P.norm.pair) HWC_NORM(CT, W, 1); \
+    else HWC_NORM(CT, W, 0);             \
+  } while (0)
   if (two_blocks(P.image_bytes)) {
-    if (coeff_bytes == 1) HWC_NORM(int8_t, 8);
-    else HWC_NORM(int16_t, 8);
+    if (coeff_bytes == 1) HWC_NORM_W(int8_t, 8);
+    else HWC_NORM_W(int16_t, 8);
   } else {
-    if (coeff_bytes == 1) HWC_NORM(int8_t, 4);
-    else HWC_NORM(int16_t, 4);
+    if (coeff_bytes == 1) HWC_NORM_W(int8_t, 4);
+    else HWC_NORM_W(int16_t, 4);
   }
+#undef HWC_NORM_W
 #undef HWC_NORM
   return hipGetLastError();
 }
 
-hipError_t occupancy_norm(uint32_t block, uint32_t lds_bytes, int* blocks_per_cu) {
-  if (two_blocks(lds_bytes))
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, norm_kernel<int16_t, 8>, block, lds_bytes);
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, norm_kernel<int16_t, 4>, block, lds_bytes);
+hipError_t occupancy_norm(bool pair, uint32_t block, uint32_t lds_bytes, int* blocks_per_cu) {
+  const void* f = two_blocks(lds_bytes) ? (pair ? reinterpret_cast<const void*>(&norm_kernel<int16_t, 8, 1>)
+                                                : reinterpret_cast<const void*>(&norm_kernel<int16_t, 8, 0>))
+                                        : (pair ? reinterpret_cast<const void*>(&norm_kernel<int16_t, 4, 1>)
+                                                : reinterpret_cast<const void*>(&norm_kernel<int16_t, 4, 0>));
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, block, lds_bytes);
 }
 
 // The whole image budget, and no static LDS (the rows start at LDS address 0).
 hipError_t prepare_norm() {
   hipError_t e = hipSuccess;
-  for (const void* f : {reinterpret_cast<const void*>(&norm_kernel<int8_t, 4>),
-                        reinterpret_cast<const void*>(&norm_kernel<int16_t, 4>),
-                        reinterpret_cast<const void*>(&norm_kernel<int8_t, 8>),
-                        reinterpret_cast<const void*>(&norm_kernel<int16_t, 8>)}) {
+  for (const void* f : {reinterpret_cast<const void*>(&norm_kernel<int8_t, 4, 0>),
+                        reinterpret_cast<const void*>(&norm_kernel<int16_t, 4, 0>),
+                        reinterpret_cast<const void*>(&norm_kernel<int8_t, 8, 0>),
+                        reinterpret_cast<const void*>(&norm_kernel<int16_t, 8, 0>),
+                        reinterpret_cast<const void*>(&norm_kernel<int8_t, 4, 1>),
+                        reinterpret_cast<const void*>(&norm_kernel<int16_t, 4, 1>),
+                        reinterpret_cast<const void*>(&norm_kernel<int8_t, 8, 1>),
+                        reinterpret_cast<const void*>(&norm_kernel<int16_t, 8, 1>)}) {
     if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsImageLimit);
     hipFuncAttributes a{};
     if (e == hipSuccess) e = hipFuncGetAttributes(&a, f);

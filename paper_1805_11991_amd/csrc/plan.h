@@ -88,6 +88,7 @@ struct NormDesc {
   uint32_t srow;          // row a vanished sum reads as: a power of two, at least 4M
   uint32_t emb_off, esh;  // logs of the codes in F_q: u32 every 2^esh bytes
   uint32_t fin_off;       // byte table of the last step
+  uint32_t pair;          // prime q = 1 mod 4: v and -v together (its byte table has two entries an index)
   uint32_t qm;            // floor(v / (q << esh)) = (v * qm) >> 32 for the integer translates
   const uint32_t* tmat;   // prime q: [q][kNormTmatWords] translate rows; nullptr: log arithmetic
 };
