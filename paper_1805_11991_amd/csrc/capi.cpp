@@ -1469,7 +1469,14 @@ uint32_t part_log(const DevPlan* P, uint32_t flags, double cost, double target) 
 uint32_t part_log_single(const DevPlan* P, uint32_t flags, uint64_t n) {
   const double tiles = (double)((n + hwc::kWave - 1) / hwc::kWave);
   const double waves = P->npath ? (double)P->ngrid * P->nblock / hwc::kWave : (double)P->grid * P->block / hwc::kWave;
-  return part_log(P, flags, 1.0, tiles / (P->desc.lv[P->g - 1].nx >= 6000 ? 2.0 * waves : waves));
+  const uint32_t nx = P->desc.lv[P->g - 1].nx;
+  uint32_t pl = part_log(P, flags, 1.0, tiles / (nx >= 6000 ? 2.0 * waves : waves));
+  // below eight rounds of the resident waves the last one is a large part of the
+  // time: finer while a part keeps 512 points (count kernel: g = 4, q = 13, 2^19
+  // curves 3.67 -> 2.72 ms; g = 3, q = 25, 2^17 1.01 -> 0.54)
+  if (!P->npath && nx >= kPartMinPoints / 2 && part_log(P, flags, 1.0, 0.5) > 0)
+    while (tiles * (double)(1u << pl) < 8.0 * waves && (nx >> pl) >= 1024) ++pl;
+  return pl;
 }
 
 // Rows up to which one workgroup buckets a request alone (bucket_small.hip: 9 us

@@ -54,6 +54,46 @@ __device__ __forceinline__ void stage_image(uint32_t* lds, const uint32_t* __res
   for (uint32_t i = threadIdx.x; i < bytes / 16; i += blockDim.x) dst[i] = src[i];
 }
 
+// How the waves of a persistent launch take its n entries.  With one queue in
+// device memory for all of them every wave pops it once more than it has entries,
+// 13 to 20 ns a pop: 8192 waves, 164 us, whatever the entries' work.  So the first
+// round, or all of a request of at most two rounds, is each workgroup's own, every
+// gridDim-th entry, taken through a word in LDS; the rest is common, and the first
+// wave that finds it empty tells its workgroup.  Beyond twelve rounds everything
+// is common: the pops of one round matter little, and waves that start apart
+// overlap LDS and vector work better (g = 4, q = 13, 2^22 curves 20.39 -> 20.25
+// ms).  Three quarters of the rounds as own entries would leave those of the
+// workgroups that do not become resident at once for the end (2^24 curves at g =
+// 3, q = 13: 7.77 -> 8.31 ms).  Count alone, one queue -> this: 20 000 curves at g =
+// 2, q = 101 223 -> 75 us, 80 000 at g = 3, q = 13 209 -> 107.
+struct EntryShare {
+  uint32_t* taken;        // LDS: own entries taken; the common queue found empty
+  uint32_t* queue;        // common entries taken (nullptr: every entry is some workgroup's own)
+  uint32_t n, own;        // entries; a workgroup's own share
+};
+
+__device__ __forceinline__ EntryShare entry_share(uint32_t* lds, uint32_t* queue, uint32_t n) {
+  EntryShare s{lds, queue, n, ~0u};
+  const uint32_t wpb = blockDim.x / kWave;
+  if (queue && n > 2u * gridDim.x * wpb) s.own = n > 12u * gridDim.x * wpb ? 0u : wpb;
+  return s;
+}
+
+// The calling wave's next entry, or one past the last.
+__device__ __forceinline__ uint32_t next_entry(const EntryShare& s) {
+  const bool lead = (threadIdx.x & (kWave - 1)) == 0;
+  uint32_t v = 0;
+  if (lead) v = atomicAdd(s.taken, 1u);
+  v = uniform(v);
+  if (v < s.own) return v * gridDim.x + blockIdx.x;
+  if (lead) {
+    volatile uint32_t* empty = s.taken + 1;
+    v = *empty ? s.n : s.own * gridDim.x + atomicAdd(s.queue, 1u);
+    if (v >= s.n) *empty = 1u;
+  }
+  return uniform(v);
+}
+
 // N_k from the per-level counts (Sec. 1.1 decomposition; x = 0 and the
 // points at infinity of the model in P(1, g+1, 1) added here).
 template <int G>

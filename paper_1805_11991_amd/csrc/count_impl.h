@@ -1112,32 +1112,20 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))) voi
   const PlanDesc& P = *Pd;
   extern __shared__ uint32_t lds32[];
   constexpr uint32_t lb = kImageBase;
+  uint32_t* taken = lds32 + P.image_bytes / 4;
   stage_image(lds32, P.image, P.image_bytes);
+  if (threadIdx.x < 2) taken[threadIdx.x] = 0;
   __syncthreads();
-  const uint32_t lane = threadIdx.x & (kWave - 1);
-  // queue entries: tiles, or (plog > 0, levels 0..G-1 through the queue) the
-  // 2^plog parts of every tile, as in the batch kernel
+  // entries: tiles, or (plog > 0, levels 0..G-1 together) the 2^plog parts of
+  // every tile, as in the batch kernel
   const uint32_t ntiles = *ntiles_p << plog;
   const uint32_t pmask = (1u << plog) - 1u;
-  const uint32_t nwaves = (gridDim.x * blockDim.x) / kWave;
-  uint32_t t;
-  if (queue) {
-    uint32_t v = 0;
-    if (lane == 0) v = atomicAdd(queue, 1u);
-    t = uniform(v);
-  } else {
-    t = uniform((blockIdx.x * blockDim.x + threadIdx.x) / kWave);
-  }
-  while (t < ntiles) {
+  const EntryShare share = entry_share(taken, queue, ntiles);
+  for (;;) {
+    const uint32_t t = next_entry(share);
+    if (t >= ntiles) break;
     process_tile<G, CT>(P, lb, codes, perm, sload64(tiles, t >> plog), lvl_lo, lvl_hi, outN, outLv, t >> plog,
                         t & pmask, plog, acc, done);
-    if (queue) {
-      uint32_t v = 0;
-      if (lane == 0) v = atomicAdd(queue, 1u);
-      t = uniform(v);
-    } else {
-      t = uniform(t + nwaves);
-    }
   }
 }
 

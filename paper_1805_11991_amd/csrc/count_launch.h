@@ -13,7 +13,7 @@ hipError_t CountEntry<G>::launch(const PlanDesc& P, const PlanDesc* dP, int coef
                                  uint32_t* acc, uint32_t* done, uint32_t grid, uint32_t block, uint32_t wpe,
                                  hipStream_t s) {
 #define HWC_LAUNCH(CT, W)                                                                                   \
-  hipLaunchKernelGGL((count_kernel<G, CT, W>), dim3(grid), dim3(block), P.image_bytes, s, dP,                \
+  hipLaunchKernelGGL((count_kernel<G, CT, W>), dim3(grid), dim3(block), P.image_bytes + 16, s, dP,                \
                      static_cast<const CT*>(codes), perm, tiles, ntiles, queue, lo, hi, outN, outLv, plog, acc, done)
   if (coeff_bytes == 1) {
     if (wpe >= 8) HWC_LAUNCH(int8_t, 8);
@@ -39,7 +39,7 @@ template <int G>
 hipError_t CountEntry<G>::occupancy(int coeff_bytes, uint32_t block, uint32_t lds_bytes, uint32_t wpe,
                                     int* blocks_per_cu) {
 #define HWC_OCC(CT, W) \
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, count_kernel<G, CT, W>, block, lds_bytes)
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, count_kernel<G, CT, W>, block, lds_bytes + 16)
   if (coeff_bytes == 1) {
     if (wpe >= 8) HWC_OCC(int8_t, 8);
     if (wpe >= 6) HWC_OCC(int8_t, 6);
@@ -67,7 +67,7 @@ hipError_t CountEntry<G>::prepare() {
   const void* batch = reinterpret_cast<const void*>(&batch_kernel<G>);
   hipError_t e = hipSuccess;
   for (const void* f : counts)
-    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsImageLimit);
+    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsImageLimit + 16);
   if (e == hipSuccess)
     e = hipFuncSetAttribute(batch, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsImageLimit + 16);
   auto no_static = [&](const void* f) {

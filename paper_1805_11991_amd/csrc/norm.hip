@@ -21,14 +21,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))) voi
                                                     uint32_t* __restrict__ done) {
   const PlanDesc& P = *Pd;
   extern __shared__ uint32_t lds32[];
+  uint32_t* taken = lds32 + P.image_bytes / 4;
   stage_image(lds32, P.image, P.image_bytes);
+  if (threadIdx.x < 2) taken[threadIdx.x] = 0;
   __syncthreads();
-  const uint32_t lane = threadIdx.x & (kWave - 1);
   const uint32_t entries = *ntiles_p << plog;     // tiles, or the 2^plog parts of every tile
+  const EntryShare share = entry_share(taken, queue, entries);
   for (;;) {
-    uint32_t v = 0;
-    if (lane == 0) v = atomicAdd(queue, 1u);
-    const uint32_t t = uniform(v);
+    const uint32_t t = next_entry(share);
     if (t >= entries) break;
     norm_tile<CT, WPE == 8 ? 4 : 8, PAIR>(P, codes, perm, sload64(tiles, t >> plog), outN, outLv, t >> plog, t & ((1u << plog) - 1u), plog, acc,
                   done);
@@ -37,7 +37,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))) voi
 
 // Images that leave room for a second workgroup on the CU: worth the build of
 // 8 waves a SIMD.
-bool two_blocks(uint32_t image_bytes) { return image_bytes <= 80 * 1024; }
+bool two_blocks(uint32_t image_bytes) { return image_bytes + 16 <= 80 * 1024; }
 
 }  // namespace
 
@@ -46,7 +46,7 @@ hipError_t launch_norm(const PlanDesc& P, const PlanDesc* dP, int coeff_bytes, c
                        uint32_t plog, uint32_t* acc, uint32_t* done, uint32_t grid, uint32_t block, hipStream_t s) {
   if (P.g != 2 || !P.norm.kind || P.image_bytes > kLdsImageLimit) return hipErrorInvalidValue;
 #define HWC_NORM(CT, W, PR)                                                                                  \
-  hipLaunchKernelGGL((norm_kernel<CT, W, PR>), dim3(grid), dim3(block), P.image_bytes, s, dP,                 \
+  hipLaunchKernelGGL((norm_kernel<CT, W, PR>), dim3(grid), dim3(block), P.image_bytes + 16, s, dP,                 \
                      static_cast<const CT*>(codes), perm, tiles, ntiles, queue, outN, outLv, plog, acc, done)
 #define HWC_NORM_W(CT, W)               \
   do {                                  \
@@ -70,7 +70,7 @@ hipError_t occupancy_norm(bool pair, uint32_t block, uint32_t lds_bytes, int* bl
                                                 : reinterpret_cast<const void*>(&norm_kernel<int16_t, 8, 0>))
                                         : (pair ? reinterpret_cast<const void*>(&norm_kernel<int16_t, 4, 1>)
                                                 : reinterpret_cast<const void*>(&norm_kernel<int16_t, 4, 0>));
-  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, block, lds_bytes);
+  return hipOccupancyMaxActiveBlocksPerMultiprocessor(blocks_per_cu, f, block, lds_bytes + 16);
 }
 
 // The whole image budget, and no static LDS (the rows start at LDS address 0).
@@ -84,7 +84,7 @@ hipError_t prepare_norm() {
                         reinterpret_cast<const void*>(&norm_kernel<int16_t, 4, 1>),
                         reinterpret_cast<const void*>(&norm_kernel<int8_t, 8, 1>),
                         reinterpret_cast<const void*>(&norm_kernel<int16_t, 8, 1>)}) {
-    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsImageLimit);
+    if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsImageLimit + 16);
     hipFuncAttributes a{};
     if (e == hipSuccess) e = hipFuncGetAttributes(&a, f);
     if (e == hipSuccess && a.sharedSizeBytes != 0) e = hipErrorInvalidKernelFile;
