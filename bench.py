@@ -12,8 +12,9 @@ Also measured in the same run, each as its own object of the JSON line:
   zech_path        the Zech path at g=3 and g=4 over F_13: batched and plain
                    (one launch per level, no graph) with per-step spread,
                    lookups/s against the LDS peak and the measured gather ceiling
-  largest_field_g2 g = 2 over F_293: the top level's Zech table as a half
-                   table in LDS (the default), and placed in device memory
+  largest_field_g2 g = 2 over F_293: level 2 by norms in F_293 (the default; its
+                   plain form reads a half table in LDS), and by its own Zech
+                   table in device memory
                    (lookups/s against the measured ceiling of random gathers
                    from such a table, L2/MALL-served)
   matrix_core_path the opt-in int8 matrix-product formulation on the same sets
@@ -109,20 +110,35 @@ def lookups_per_batch(curves, levels: list[dict]) -> tuple[int, int]:
 def mfma_work(n: int, levels: list[dict]) -> dict:
     """Work of the matrix-product count kernel for n curves.  Every level j
     (j coordinates) evaluates each curve at its swept points: per (curve,
-    point) pair 3j + 1 vector ALU operations in the balanced form (mfma = 2:
-    a multiply-high and two multiply-adds per coordinate but the first, which
-    arrives with the table offset added; one add of the character read), 4j
-    otherwise, and one random 32-bit read of the character table from LDS.
+    point) pair, in the fractional form (p <= 13; genus 4 from p = 7),
+    the table address (a selection for each coordinate but the first, a shift
+    for each but the first two), a shift and a rotation by coordinate 0, the
+    collection of two bits and 7 / 16 operation for counting them; 4j by
+    residues, for larger p; and one read of the character table from LDS.
     Work is counted on the real points only; the kernel also sweeps the
     padding of each level's last 32-point block (reported beside)."""
+    p, g = levels[0]["M"] + 1, len(levels)
+    frac = g >= 2 and p <= 13 and (g < 4 or p >= 7)
     pairs = padded = valu = mfma = 0
     for j, L in enumerate(levels, start=1):
         pr = n * L["nx"]
         pairs += pr
         padded += n * ((L["nx"] + 31) // 32 * 32)
-        valu += pr * ((3 * j + 1) if L["mfma"] == 2 else 4 * j)
-        mfma += ((n + 31) // 32 * 32) * ((L["nx"] + 31) // 32 * 32) * j * 16 * 2
-    return {"pairs": pairs, "pairs_padded": padded, "valu_ops": valu, "mfma_ops": mfma}
+        valu += pr * (((j - 1) + max(j - 2, 0) + 3 + 7 / 16) if frac else 4 * j)
+        mfma += ((n + 31) // 32 * 32) * ((L["nx"] + 31) // 32 * 32) * j * (32 if frac else 16) * 2
+    return {"pairs": pairs, "pairs_padded": padded, "valu_ops": int(valu), "mfma_ops": mfma, "fractional": frac}
+
+
+def norm_lookups(q: int, curves) -> int:
+    """LDS reads of genus 2 counted by norms at a prime q = 1 mod 4: per
+    translate of F_q and pair of nonsquares v, -v, three steps for A, two for B
+    and one for the answer (one less in degree 5), six logs a translate, and
+    Horner's six steps at every nonzero x of level 1."""
+    import numpy as np
+    deg6 = int(np.count_nonzero(curves[:, 6]))
+    n = len(curves)
+    pairs = q * ((q - 1) // 4)
+    return pairs * (6 * deg6 + 5 * (n - deg6)) + 6 * n * (q + q - 1)
 
 
 def evaluated_rows(ctx, q: int, g: int, d_rows):
@@ -370,7 +386,7 @@ def main():
             # the same curves priced in the Zech path's algorithmic gathers
             "zech_equivalent_lookups_per_s": round(alg / s, 1),
             "zech_equivalent_frac_of_lds_peak": round(alg / s / LDS_PEAK_LOOKUPS, 4),
-            "levels": [{"M": L["M"], "nx": L["nx"], "balanced": L["mfma"] == 2} for L in levels],
+            "levels": [{"M": L["M"], "nx": L["nx"], "fractional": w["fractional"]} for L in levels],
         }
 
     if args.profile_case:
@@ -540,7 +556,7 @@ def main():
         del bufs4, N4
         torch.cuda.empty_cache()
 
-        # ---------------- the largest field of the g=2 range: half table in LDS, and in device memory ----------------
+        # ---------------- the largest field of the g=2 range: by norms, and with its table in device memory ----------------
         qd, gd, nd = 293, 2, 1 << 20
         bufsd = setup(qd, gd, nd, curvegen.BASE_SEED + 2 + qd)
         lv_d = ctx.plan_info(qd, gd)
@@ -551,7 +567,11 @@ def main():
         Nd = bufsd[2].cpu().numpy()
         kd = kernel_ms(ctx, runner(ctx, qd, gd, bufsd, 0), 3)
         rd = zech_roofline(ctx, qd, gd, bufsd, kd["count_ms"])
-        rd["kernel"] = "count_kernel<2,int16> (top level as a half table in LDS, form F)"
+        # counted by norms in F_q: lane-private rows, conflict-free reads
+        pn = norm_lookups(qd, bufsd[0])
+        rd.update(performed_lookups_per_launch=pn, performed_lookups_per_s=round(pn / (kd["count_ms"] * 1e-3), 1),
+                  performed_frac=round(pn / (kd["count_ms"] * 1e-3) / LDS_PEAK_LOOKUPS, 4),
+                  performed_frac_of_gather_ceiling=None, kernel="norm_kernel<int16,4,1> (level 2 by norms in F_q)")
         big = {"q": qd, "g": gd, "curves": nd, "top_level_form": lv_d[-1]["form"], "batched": td, "plain": tdp,
                "batched_vs_plain": ratio(tdp, td), "curves_per_s": round(nd / (td["ms_per_step"] * 1e-3), 1),
                "roofline": rd}
@@ -560,7 +580,7 @@ def main():
         dctx.set_option(hwcount.HWC_OPT_DEVICE_TABLES, 1 << (gd - 1))
         tdd = timed_steps(torch, stream, runner(dctx, qd, gd, bufsd, 0), 3, 1)
         dctx.status()
-        assert np.array_equal(bufsd[2].cpu().numpy(), Nd), "device-memory tables differ from the LDS half table"
+        assert np.array_equal(bufsd[2].cpu().numpy(), Nd), "device-memory tables differ from the norms"
         kdd = kernel_ms(dctx, runner(dctx, qd, gd, bufsd, 0), 2)
         dev_ceiling = dctx.device_gather_rate(2 * Md, chains=4)
         rdd = zech_roofline(dctx, qd, gd, bufsd, kdd["count_ms"], ceiling=dev_ceiling)
@@ -570,10 +590,10 @@ def main():
                                       f"table (hwc_device_gather_rate)")
         big["device_memory_tables"] = {"batched": tdd, "curves_per_s": round(nd / (tdd["ms_per_step"] * 1e-3), 1),
                                        "roofline": rdd,
-                                       "lds_half_table_speedup": round(tdd["ms_per_step"] / td["ms_per_step"], 3)}
+                                       "norms_speedup": round(tdd["ms_per_step"] / td["ms_per_step"], 3)}
         dctx.close()
         extra["largest_field_g2"] = big
-        log(f"q={qd} g={gd}: half table in LDS {td['ms_per_step']} ms (plain {tdp['ms_per_step']} ms), "
+        log(f"q={qd} g={gd}: by norms {td['ms_per_step']} ms (plain {tdp['ms_per_step']} ms), "
             f"tables in device memory {tdd['ms_per_step']} ms, {rdd['performed_lookups_per_s'] / 1e9:.1f} G performed "
             f"lookups/s there = {rdd['performed_frac_of_gather_ceiling']} of the measured device gather ceiling")
         del bufsd
