@@ -443,7 +443,7 @@ def main():
         roofline["kernel"] = "count_kernel<3,int8>"
     else:
         roofline = mfma_roofline(mctx, q, g, curves, km["count_ms"], ceiling3)
-        roofline["kernel"] = "vcount_kernel<3,int8>"
+        roofline["kernel"] = "fcount_kernel<3,int8>"
     traffic = measured_traffic(args.path)
     roofline["traffic"] = None if traffic is None else traffic["fetch"] + traffic["write"]
     roofline["traffic_unit"] = "HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated)"
@@ -492,7 +492,7 @@ def main():
         mroof["traffic_detail"] = mtraffic
         mroof["counters"] = measured_counters("mfma")
         mroof["valu_issue_ceiling_per_cu_clock"] = roofline["valu_issue_ceiling_per_cu_clock"]
-        mroof["kernel"] = "vcount_kernel<3,int8>"
+        mroof["kernel"] = "fcount_kernel<3,int8>"
         mp["g3_q13"] = {"curves": n, "batched": mb, "plain": mpl, "batched_vs_plain": ratio(mpl, mb),
                         "curves_per_s": round(n / (mb["ms_per_step"] * 1e-3), 1), "roofline": mroof,
                         "vs_zech_path": round(head["ms_per_step"] / mb["ms_per_step"], 3)}
@@ -546,7 +546,7 @@ def main():
         assert np.array_equal(bufs4[2].cpu().numpy(), N4), "g=4: matrix-product path differs from the Zech path"
         mk4 = kernel_ms(mctx, runner(mctx, 13, 4, bufs4, 0), 2)
         mr4 = mfma_roofline(mctx, 13, 4, bufs4[0], mk4["count_ms"], ceiling4)
-        mr4["kernel"] = "vcount_kernel<4,int8> (level 4 over several passes)"
+        mr4["kernel"] = "fcount_kernel<4,int8> (level 4 over several passes)"
         mp["g4_q13"] = {"curves": n4, "batched": mb4, "plain": mpl4, "batched_vs_plain": ratio(mpl4, mb4),
                         "curves_per_s": round(n4 / (mb4["ms_per_step"] * 1e-3), 1), "roofline": mr4,
                         "vs_zech_path": round(zb["ms_per_step"] / mb4["ms_per_step"], 3)}
