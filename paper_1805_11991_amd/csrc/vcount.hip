@@ -216,14 +216,14 @@ __global__ __launch_bounds__(1024) void vcount_kernel(const VPlanDesc* __restric
 // A pair costs k - 1 bit selections and k - 2 shifts for the word's address, one
 // LDS read, the shift that brings coordinate 0's cell to the low bits, the
 // rotation, the collection of its two bits and 7 / 16 for counting them: 6.4
-// vector operations with three coordinates, against 9.75 by
-// residues.  Vector issue is the bound of both; 764 M wave instructions are 1.25 ms of the
-// 1.61 that 2^23 curves of genus 3 over F_13 take (residues: 2.61 ms), the rest
-// is waits that one workgroup of 16 waves per CU does not hide.  Each lane reads
-// a copy in its own bank (four copies with four coordinates, where 64 KB hold no
-// more): no conflicts, LDS 0.2 of the time; the matrix products 0.16.  2^17
-// curves of genus 4 over F_13: 464 -> 357 us, though its larger images take more
-// passes.
+// vector operations with three coordinates, against 11.6 by residues (9.75 with
+// the quotients by a multiply-high).  Vector issue is the bound: 0.89
+// instructions per CU and clock at genus 3 over F_13, the rest waits that one
+// workgroup of 16 waves per CU does not hide.  Each lane reads a copy in its own
+// bank (four copies with four coordinates, where 64 KB hold no more): no
+// conflicts, LDS active 35 % of the clocks, matrix cores 18 %.  Count of 2^23
+// curves 2.61 (multiply-high) -> 1.61 ms; 2^17 curves of genus 4 over F_13 464 ->
+// 357 us, though its larger images take more passes.
 
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(3))) v4i* vlds128_ptr;
