@@ -910,7 +910,8 @@ int build_vplan(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, uint32_t g, uint
 // from 81 on, whose translates cost more.  Count kernel on 2^18 curves, level
 // table -> norms: 29 0.149 -> 0.195 ms, 37 0.238 -> 0.209, 61 0.540 -> 0.380,
 // 101 1.31 -> 0.80, 293 19.2 -> 5.7; 49 0.381 -> 0.399, 81 0.81 -> 0.72, 169
-// 3.15 -> 1.96.
+// 3.15 -> 1.96.  (Points singly; primes q = 1 mod 4 take v and -v together since:
+// norm_impl.h.)
 constexpr uint32_t kNormMinPrime = 37, kNormMinPower = 81;
 
 // The image of norm_impl.h for (q, 2), or an empty one when it does not fit.
@@ -1440,8 +1441,7 @@ int get_scratch(hwc_ctx* c, int set, uint64_t n, uint32_t g, int cb, bool plain,
 // Workgroups of a persistent launch over about `tiles` tiles: at most the
 // resident grid, and no more than the tiles need, so that a small request's
 // tiles land one workgroup per CU (the dispatcher spreads workgroups over
-// the CUs) instead of on whichever waves win the queue first, which can put
-// several of them on one CU while others idle.
+// the CUs) and the launch has no workgroups without work.
 uint32_t persistent_grid(uint32_t resident, uint32_t block, uint64_t tiles) {
   const uint64_t per = std::max<uint32_t>(block / hwc::kWave, 1);
   const uint64_t need = (tiles + per - 1) / per;
