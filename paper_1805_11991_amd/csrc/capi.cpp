@@ -210,16 +210,6 @@ struct JobSlot {          // job descriptors of a direct multi-plan launch
 };
 
 constexpr uint32_t kSmallStride = 4 * 2048 + 16;   // per-job bucketing words (u32)
-// Tile parts.  A request whose top level sweeps at least kPartMinPoints points
-// by orbits has every tile cut into 2^kPartLog parts, so that the last tiles of
-// a launch do not hold a few waves long after the rest of the GPU has run dry
-// (one 2^20-curve request at q = 293, g = 2: 80 -> 72 ms).  A request (or batch)
-// of fewer entries than the waves in flight want is cut further, down to
-// kPartPoints top-level points a part: there a wave's serial sweep is the time
-// (500 curves at g = 3, q = 13: 8 tiles of 112 us, now 128 parts in 37 us).
-constexpr uint32_t kPartMinPoints = 8192;
-constexpr uint32_t kPartLog = 3;
-constexpr uint32_t kPartMaxLog = 8;
 constexpr int kJobSlots = 4;
 
 // Scratch of the work enqueued on one stream.  Calls on different streams
@@ -1448,35 +1438,24 @@ uint32_t persistent_grid(uint32_t resident, uint32_t block, uint64_t tiles) {
   return (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(resident, need));
 }
 
-// log2 of the parts each tile of a request is cut into (kPartMinPoints), when
-// an entry costing `cost` should cost at most `target`: orbit sweeps of the
-// Zech path only (the point lists are explicit), not the plain form (one launch
-// per level, whole tiles)
-uint32_t part_log(const DevPlan* P, uint32_t flags, double cost, double target) {
-  if (P->vpath || !P->orbit || (flags & HWC_PLAIN)) return 0;
-  const hwc::LevelDesc& top = P->desc.lv[P->g - 1];
-  if (!top.xs) return 0;
-  uint32_t pl = top.nx >= kPartMinPoints ? kPartLog : 0;
-  while (pl < kPartMaxLog && (top.nx >> pl) >= 2 * hwc::kPartPoints && cost > target * (double)(1u << pl)) ++pl;
-  return pl;
+// Whether the tiles of a request can be cut into parts (parts.h): orbit sweeps
+// of the Zech path only (the point lists are explicit), not the plain form (one
+// launch per level, whole tiles)
+bool takes_parts(const DevPlan* P, uint32_t flags) {
+  return !P->vpath && P->orbit && !(flags & HWC_PLAIN) && P->desc.lv[P->g - 1].xs;
 }
 
-// ... of a single request of n rows: one entry for each resident wave, two
-// where the top level sweeps thousands of points and a part's setup is small
-// beside its share (count kernel, one against two entries a wave: g = 4, q = 13,
-// 7098 points, 2^16 curves 1015 / 627 us; g = 3, q = 13, 728 points, 2^17 curves
-// 164 / 186 us).
+// log2 of the parts of a job's tiles in a batch
+uint32_t part_log(const DevPlan* P, uint32_t flags, double cost, double target) {
+  return takes_parts(P, flags) ? hwc::part_log(P->desc.lv[P->g - 1].nx, cost, target) : 0u;
+}
+
+// ... and of a single request of n rows
 uint32_t part_log_single(const DevPlan* P, uint32_t flags, uint64_t n) {
+  if (!takes_parts(P, flags)) return 0;
   const double tiles = (double)((n + hwc::kWave - 1) / hwc::kWave);
   const double waves = P->npath ? (double)P->ngrid * P->nblock / hwc::kWave : (double)P->grid * P->block / hwc::kWave;
-  const uint32_t nx = P->desc.lv[P->g - 1].nx;
-  uint32_t pl = part_log(P, flags, 1.0, tiles / (nx >= 6000 ? 2.0 * waves : waves));
-  // below eight rounds of the resident waves the last one is a large part of the
-  // time: finer while a part keeps 512 points (count kernel: g = 4, q = 13, 2^19
-  // curves 3.67 -> 2.72 ms; g = 3, q = 25, 2^17 1.01 -> 0.54)
-  if (!P->npath && nx >= kPartMinPoints / 2 && part_log(P, flags, 1.0, 0.5) > 0)
-    while (tiles * (double)(1u << pl) < 8.0 * waves && (nx >> pl) >= 1024) ++pl;
-  return pl;
+  return hwc::part_log_single(P->desc.lv[P->g - 1].nx, tiles, waves, P->npath);
 }
 
 // Rows up to which one workgroup buckets a request alone (bucket_small.hip: 9 us

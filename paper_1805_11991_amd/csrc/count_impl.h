@@ -927,15 +927,15 @@ __device__ __forceinline__ uint32_t count_level(const LevelDesc& Lp, uint32_t lb
   if (plog) {
     if (ms ? (L.xs_t != nullptr && L.xs_s != nullptr) : (L.xs != nullptr)) {
       if (ms) {
-        const uint32_t t0 = (L.nt * part) >> plog, t1 = (L.nt * (part + 1)) >> plog;
-        const uint32_t s0 = (L.ns * part) >> plog, s1 = (L.ns * (part + 1)) >> plog;
+        const uint32_t t0 = part_begin(L.nt, part, plog), t1 = part_begin(L.nt, part + 1, plog);
+        const uint32_t s0 = part_begin(L.ns, part, plog), s1 = part_begin(L.ns, part + 1, plog);
         L.xs_t += t0;
         L.nt = t1 - t0;
         L.xs_s += s0;
         L.ns = s1 - s0;
         L.nx = L.nt * ms + L.ns;
       } else {
-        const uint32_t x0 = (L.nx * part) >> plog, x1 = (L.nx * (part + 1)) >> plog;
+        const uint32_t x0 = part_begin(L.nx, part, plog), x1 = part_begin(L.nx, part + 1, plog);
         L.xs += x0;
         L.nx = x1 - x0;
       }

@@ -298,8 +298,8 @@ __device__ __forceinline__ uint32_t norm_level1(const NormDesc& D, const uint32_
 #pragma unroll
   for (int i = 5; i >= 0; --i) st[i] = norm_link(beta, w[i], M, zrow, lane4);
   uint32_t odd = 0, z = 0;
-  const uint32_t l1 = (M * (part + 1u)) >> plog;
-  for (uint32_t l = (M * part) >> plog; l < l1; ++l) {
+  const uint32_t l1 = part_begin(M, part + 1u, plog);
+  for (uint32_t l = part_begin(M, part, plog); l < l1; ++l) {
     const uint32_t L = l * kNormRow;
     uint32_t a = a0;
 #pragma unroll
@@ -317,7 +317,7 @@ template <bool FOLD, bool TOP, bool PAIR, int U>
 __device__ __forceinline__ uint32_t norm_level2(const NormDesc& D, const uint32_t (&code)[7], const uint32_t (&w)[7],
                                                 uint32_t lane4, uint32_t part, uint32_t plog) {
   const uint32_t M = D.M, q = M + 1u;
-  const uint32_t t0 = (q * part) >> plog, t1 = (q * (part + 1u)) >> plog;
+  const uint32_t t0 = part_begin(q, part, plog), t1 = part_begin(q, part + 1u, plog);
   uint32_t odd = 0, z = 0;
   uint32_t pk[4];   // coefficient pairs for the integer translates
 #pragma unroll

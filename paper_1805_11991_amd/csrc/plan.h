@@ -33,6 +33,8 @@
 
 #include <cstdint>
 
+#include "parts.h"
+
 namespace hwc {
 
 constexpr int kMaxG = 4;                 // genus handled by the kernels
@@ -236,11 +238,6 @@ struct VPlanDesc {
   const uint32_t* image;
   VLevel lv[kMaxG];
 };
-
-// Tile parts: least points of a part's share of a level, and the distance
-// between the first parts of neighbouring levels (odd: no two start alike).
-constexpr uint32_t kPartPoints = 48;
-constexpr uint32_t kPartStep = 5;
 
 // One request of a multi-plan launch (device memory).
 struct JobDesc {
