@@ -10,6 +10,7 @@
 #include <chrono>
 #include <cstdio>
 #include <cstring>
+#include <functional>
 #include <list>
 #include <map>
 #include <memory>
@@ -659,24 +660,37 @@ bool append_vlevel(std::vector<uint8_t>& img, const hwc::Field& F, uint32_t j, c
   return true;
 }
 
-// Appends the points xs[i0, i1) of level j to an image of the fractional form:
-// the word table at the first multiple of its size, the blocks where they fit.
+// Where level j's blocks (32 points each) and word table go in an image of the
+// fractional form that is `size` bytes so far: the table at the first multiple of
+// its size, the blocks in the gap before it if they fit there, else behind it.
+struct FPlace {
+  uint64_t vo, to, end;
+};
+FPlace place_flevel(uint64_t size, uint32_t j, uint64_t nblk) {
+  const uint32_t KC = j + 1;
+  const uint64_t tbytes = KC == 1 ? 256 : KC == 2 ? 4096 : 65536;
+  FPlace f;
+  f.to = (size + tbytes - 1) / tbytes * tbytes;
+  const uint64_t gap = (size + 15) / 16 * 16, blk = nblk * KC * 1024;
+  f.vo = gap + blk <= f.to ? gap : f.to + tbytes;
+  f.end = std::max(f.to + tbytes, f.vo + blk);
+  return f;
+}
+
+// Appends the points xs[i0, i1) of level j to an image of the fractional form.
 // False when the image would pass `limit` or two residues could share a cell.
 bool append_flevel(std::vector<uint8_t>& img, const hwc::Field& F, uint32_t j, const std::vector<uint32_t>& xs,
                    size_t i0, size_t i1, uint32_t p, uint32_t NC, uint32_t wt, uint64_t limit, hwc::VLevel* out) {
-  const uint32_t KC = j + 1, M = (uint32_t)F.M, h = (p - 1) / 2, one = 1u << hwc::kFracBits;
+  const uint32_t KC = j + 1, h = (p - 1) / 2, one = 1u << hwc::kFracBits;
+  const uint64_t M = F.M;
   hwc::VLevel L{};
   L.pts = (uint32_t)(i1 - i0);
   L.nblk = (L.pts + 31) / 32;
   L.pad = L.nblk * 32 - L.pts;
-  const uint64_t tbytes = KC == 1 ? 256 : KC == 2 ? 4096 : 65536;
-  const uint64_t to = (img.size() + tbytes - 1) / tbytes * tbytes;
-  // the blocks in the gap before the table if it holds them, else behind it
-  const uint64_t gap = (img.size() + 15) / 16 * 16, blk = (uint64_t)L.nblk * KC * 1024;
-  const uint64_t vo = gap + blk <= to ? gap : to + tbytes;
-  const uint64_t end = std::max(to + tbytes, vo + blk);
-  if (end > limit) return false;
-  img.resize(end, 0);
+  const FPlace at = place_flevel(img.size(), j, L.nblk);
+  if (at.end > limit) return false;
+  img.resize(at.end, 0);
+  const uint64_t vo = at.vo, to = at.to;
   L.vo = (uint32_t)vo;
   L.to = (uint32_t)to;
   // fractions of the residues: a 2^12 / p rounded, for balanced a
@@ -783,42 +797,42 @@ int build_vplan(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, uint32_t g, uint
   // fractions; p = 7: 199 and 153).  Elsewhere it is faster at 500 rows and at
   // 2^20: fcount_kernel.
   if (p <= hwc::kFracMaxP && g >= 2 && (g < 4 || p >= 7)) {
-    // every level in one image (the largest table first, at offset 0), else the
-    // lower levels in one and the top level's points over several
     const hwc::Field& F1 = P->fields[0]->F;
-    auto start = [&](uint32_t lo, uint32_t hi) {
+    // points [i0, i1) of level hi and, when with_low, all of the levels below it in
+    // one image (the largest table first, at offset 0)
+    auto add = [&](uint32_t hi, size_t i0, size_t i1, bool with_low) {
       Built b;
       b.d.p = p; b.d.g = g; b.d.ncoef = NC; b.d.orbit = orbit;
       b.d.frac = 127 / ((p - 1) / 2);
       for (uint32_t cd = 1; cd < p; ++cd) b.d.nsmask |= (F1.log[cd] & 1u) << cd;
-      b.lo = lo; b.hi = hi; b.tw = 4;
-      return b;
-    };
-    auto levels = [&](Built& b) {
-      for (uint32_t j = b.hi + 1; j-- > b.lo;)
-        if (!append_flevel(b.img, P->fields[j]->F, j, xs[j], 0, xs[j].size(), p, NC, b.d.frac, limit, &b.d.lv[j]))
-          return false;
+      b.lo = with_low ? 0 : hi; b.hi = hi; b.tw = 4;
+      for (uint32_t j = b.hi + 1; j-- > b.lo;) {
+        const size_t j0 = j == hi ? i0 : 0, j1 = j == hi ? i1 : xs[j].size();
+        if (!append_flevel(b.img, P->fields[j]->F, j, xs[j], j0, j1, p, NC, b.d.frac, limit, &b.d.lv[j])) return false;
+      }
+      passes.push_back(std::move(b));
       return true;
     };
-    bool ok_all = true;
-    Built all = start(0, g - 1);
-    if (levels(all)) {
-      passes.push_back(std::move(all));
-    } else {
-      const uint32_t top = g - 1;
-      Built low = start(0, top - 1);
-      ok_all = levels(low);
-      if (ok_all) passes.push_back(std::move(low));
-      const uint64_t tb = top == 1 ? 4096 : 65536;
-      const size_t per = (size_t)((limit - tb) / ((uint64_t)(top + 1) * 1024)) * 32;
-      for (size_t i0 = 0; ok_all && i0 < xs[top].size(); i0 += per) {
-        Built b = start(top, top);
-        ok_all = append_flevel(b.img, P->fields[top]->F, top, xs[top], i0, std::min(xs[top].size(), i0 + per), p, NC,
-                               b.d.frac, limit, &b.d.lv[top]);
-        if (ok_all) passes.push_back(std::move(b));
-      }
-    }
-    if (!ok_all) passes.clear();
+    auto blocks = [&](uint32_t j) { return (xs[j].size() + 31) / 32; };
+    auto low_fits = [&](uint32_t hi, size_t nblk) {   // nblk blocks of level hi with all levels below it
+      uint64_t size = nblk ? place_flevel(0, hi, nblk).end : 0;
+      for (uint32_t j = hi; j-- > 0 && size <= limit;) size = place_flevel(size, j, blocks(j)).end;
+      return size <= limit;
+    };
+    // levels 0 .. hi: as many of level hi's points as fit beside all below it, the
+    // rest in images of their own; without room for one block the levels below are
+    // packed by themselves
+    std::function<bool(uint32_t)> pack = [&](uint32_t hi) {
+      size_t nb = blocks(hi);
+      while (nb && !low_fits(hi, nb)) --nb;
+      size_t i0 = std::min(nb * 32, xs[hi].size());
+      if (nb ? !add(hi, 0, i0, true) : (hi == 0 || !pack(hi - 1))) return false;
+      const size_t per = (size_t)((limit - place_flevel(0, hi, 0).end) / ((uint64_t)(hi + 1) * 1024)) * 32;
+      for (; i0 < xs[hi].size(); i0 += per)
+        if (!add(hi, i0, std::min(xs[hi].size(), i0 + per), false)) return false;
+      return true;
+    };
+    if (!pack(g - 1)) passes.clear();
   }
   auto start_pass = [&](uint32_t lo, uint32_t hi, uint32_t tw) {
     Built b;

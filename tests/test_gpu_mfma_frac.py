@@ -58,3 +58,10 @@ def test_fractional_form(ctx, oracle_mod, q, g):
         assert np.array_equal(_run(ctx, q, g, rows[:m]), want[:m]), (q, g, m)
     assert np.array_equal(_run(ctx, q, g, rows.astype(np.int16), hw.HWC_NO_GRAPH), want)
     assert np.array_equal(_run(ctx, q, g, rows, hw.HWC_FULL_SWEEP), want)
+
+
+@pytest.mark.parametrize("q,g", [(11, 4), (7, 4), (11, 3), (13, 3)])
+def test_full_sweep_keeps_the_matrix_path(ctx, q, g):
+    """Levels whose points do not fit one image are spread over several."""
+    from paper_1805_11991_amd import hwcount as hw
+    assert all(level["mfma"] for level in ctx.plan_info(q, g, hw.HWC_FULL_SWEEP)), (q, g)
