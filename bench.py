@@ -111,15 +111,14 @@ def lookups_per_batch(curves, levels: list[dict]) -> tuple[int, int]:
 def mfma_work(n: int, levels: list[dict]) -> dict:
     """Work of the matrix-product count kernel for n curves.  Every level j
     (j coordinates) evaluates each curve at its swept points: per (curve,
-    point) pair, in the fractional form (p <= 13; genus 4 from p = 7),
+    point) pair, in the fractional form (plan_info's mfma = 2),
     the table address (a selection for each coordinate but the first, a shift
     for each but the first two), a shift and a rotation by coordinate 0, the
     collection of two bits and 7 / 16 operation for counting them; 4j by
-    residues, for larger p; and one read of the character table from LDS.
+    residues; and one read of the character table from LDS.
     Work is counted on the real points only; the kernel also sweeps the
     padding of each level's last 32-point block (reported beside)."""
-    p, g = levels[0]["M"] + 1, len(levels)
-    frac = g >= 2 and p <= 13 and (g < 4 or p >= 7)
+    frac = levels[0]["mfma"] == 2
     pairs = padded = valu = mfma = 0
     for j, L in enumerate(levels, start=1):
         pr = n * L["nx"]

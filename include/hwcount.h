@@ -341,7 +341,8 @@ int hwc_ctx_set_plan_option(hwc_ctx* ctx, uint32_t q, uint32_t g, uint32_t flags
  * tuples of m points x w^s, w^m = 1, sharing the sub-polynomial values at
  * x^m, plus ns single points), the LDS bytes of the plan, and mfma = 1 when
  * the plan counts by int8 matrix products (HWC_OPT_MFMA) instead of Zech
- * logarithms (2 at p = 11 and 13).  At g = 2 (primes
+ * logarithms, 2 when those are of fractions of the residues (p <= 13) rather than
+ * of the residues.  At g = 2 (primes
  * q >= 37, prime powers q >= 81) the orbit sweep's persistent forms count by
  * norms instead (f(x) in F_{q^2} as a pair over F_q, the character of its norm
  * read in F_q's Zech table) where that image fits LDS and no option moves a

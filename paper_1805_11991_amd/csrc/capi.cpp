@@ -3019,7 +3019,7 @@ int hwc_plan_info(hwc_ctx* c, uint32_t q, uint32_t g, uint32_t flags, hwc_level_
     levels[j].lds_bytes = P->vpath ? vmax : P->desc.image_bytes;
     levels[j].mfma = 0;
     for (const auto& v : P->vpasses)
-      if (P->vpath && v.lo <= j && j <= v.hi) levels[j].mfma = q == 11 || q == 13 ? 2u : 1u;
+      if (P->vpath && v.lo <= j && j <= v.hi) levels[j].mfma = v.desc.frac ? 2u : 1u;
   }
   return HWC_OK;
 }

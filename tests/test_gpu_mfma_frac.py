@@ -39,7 +39,9 @@ def _run(ctx, q, g, rows, flags=0):
 def test_fractional_form(ctx, oracle_mod, q, g):
     from paper_1805_11991_amd import hwcount as hw
     print(q, g, flush=True)
-    assert ctx.plan_info(q, g)[0]["mfma"] == (2 if q in (11, 13) else 1)
+    frac = g >= 2 and (g < 4 or q >= 7)          # the rule: below, residues are faster
+    for flags in (0, hw.HWC_FULL_SWEEP):
+        assert [level["mfma"] for level in ctx.plan_info(q, g, flags)] == [2 if frac else 1] * g
     n = 97 if g < 4 or q < 7 else 33
     rng = np.random.default_rng(100 * q + g)
     rows = rng.integers(0, q, (n, 2 * g + 3)).astype(np.int8)
