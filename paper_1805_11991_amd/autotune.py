@@ -48,6 +48,9 @@ SMALL_SPACE = {
 }
 
 
+FRACTIONAL_PRIMES = (3, 5, 7, 11, 13)     # fields of the matrix path's fractional form
+
+
 def _device_mask(choice, g: int) -> int:
     return {"none": 0, "top": 1 << (g - 1), "all": (1 << g) - 1}[choice] if isinstance(choice, str) else int(choice)
 
@@ -76,15 +79,23 @@ def load_db(path: str | None = None) -> dict:
         return json.load(fh).get("entries", {})
 
 
-def apply_db(ctx, db: dict) -> int:
-    """Set every entry of db as per-plan options on ctx; returns the count."""
+def apply_db(ctx, db: dict, mfma: bool = False) -> int:
+    """Set every entry of db as per-plan options on ctx; returns the count.
+
+    mfma: the context opted in to the matrix-product path.  An entry that was
+    tuned without it says nothing about the workgroup size of the fractional form,
+    whose images are far larger (a block that suits the Zech kernel leaves most of
+    a CU idle), so for that form's fields the size stays automatic."""
     from . import hwcount as hw
     ids = _opt_ids()
     n = 0
     for key, ent in db.items():
         q, g, sweep = key.split(",")
         flags = hw.HWC_FULL_SWEEP if sweep == "full" else 0
+        zech_only = "mfma" not in ent["options"]
         for name, val in ent["options"].items():
+            if name == "block" and mfma and zech_only and int(q) in FRACTIONAL_PRIMES:
+                continue
             if name == "device_tables":
                 val = _device_mask(val, int(g))
             ctx.set_plan_option(int(q), int(g), ids[name], int(val), flags)

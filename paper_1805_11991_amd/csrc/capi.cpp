@@ -889,11 +889,10 @@ int build_vplan(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, uint32_t g, uint
     P->dev_bytes += b.img.size() + sizeof(v.desc);
     c->table_bytes += b.img.size() + sizeof(v.desc);
     // the block size that keeps the most waves per CU resident (LDS holds one
-    // image per workgroup), unless a block size is set; the fractional form's
-    // images are too large for a small block to fill a CU, so it takes its own
+    // image per workgroup), unless a block size is set
     int best_waves = 0;
     for (uint32_t blk : {256u, 512u, 1024u}) {
-      if (block_opt && blk != block_opt && !v.desc.frac) continue;
+      if (block_opt && blk != block_opt) continue;
       int bpc = 0;
       HIPX(c, hwc::occupancy_vcount(g, v.desc.frac != 0, blk, v.desc.image_bytes, &bpc));
       if (bpc * (int)blk > best_waves * 64) {

@@ -204,7 +204,7 @@ class Context:
         if device >= 0 and autotune_db is not None:
             from . import autotune
             db = autotune.load_db(None if autotune_db == "default" else autotune_db)
-            self.tuned_entries = autotune.apply_db(self, db)
+            self.tuned_entries = autotune.apply_db(self, db, mfma=mfma)
 
     def _check(self, rc: int):
         if rc != HWC_OK:

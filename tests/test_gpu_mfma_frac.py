@@ -67,3 +67,28 @@ def test_full_sweep_keeps_the_matrix_path(ctx, q, g):
     """Levels whose points do not fit one image are spread over several."""
     from paper_1805_11991_amd import hwcount as hw
     assert all(level["mfma"] for level in ctx.plan_info(q, g, hw.HWC_FULL_SWEEP)), (q, g)
+
+
+def test_block_option_reaches_the_fractional_form(curvegen_mod):
+    """The images of genus 3 over F_13 leave one workgroup to a CU, so four waves of
+    256 threads take several times as long as sixteen."""
+    import torch
+    from paper_1805_11991_amd import hwcount as hw
+    rows = torch.from_numpy(curvegen_mod.sample(13, 3, 1 << 19, seed=5)).cuda()
+    out, ms = [], {}
+    with hw.Context(device=0, mfma=True) as c:
+        for block in (256, 1024):
+            c.set_plan_option(13, 3, hw.HWC_OPT_BLOCK, block)
+            assert c.plan_info(13, 3)[0]["mfma"] == 2
+            N = torch.empty((len(rows), 3), dtype=torch.int32, device="cuda")
+            c.count_curves_dev(13, 3, rows, N, flags=hw.HWC_NO_GRAPH)
+            c.status()
+            c.profile(True)
+            for _ in range(3):
+                c.count_curves_dev(13, 3, rows, N)
+            ms[block] = c.profile_read()["count_ms"]
+            c.profile(False)
+            c.status()
+            out.append(N)
+    assert torch.equal(out[0], out[1])
+    assert ms[256] > 1.5 * ms[1024], ms

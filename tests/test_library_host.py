@@ -142,3 +142,31 @@ def test_single_hip_runtime_in_process():
     out = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=300)
     assert out.returncode == 0, out.stderr
     assert out.stdout.strip().splitlines()[-1] == "1"
+
+
+@pytest.mark.parametrize("mfma", [False, True])
+def test_tuned_block_of_the_zech_path_stays_there(mfma):
+    """On a context of the matrix-product path, entries tuned without it set no
+    block size for the fields of its fractional form; every other option is set."""
+    from paper_1805_11991_amd import autotune
+
+    class Recorder:
+        def __init__(self):
+            self.set = {}
+
+        def set_plan_option(self, q, g, opt, value, flags=0):
+            self.set.setdefault((q, g), {})[opt] = value
+
+    db = {"13,3,orbit": {"options": {"split": 1, "block": 256}},
+          "9,3,orbit": {"options": {"split": 1, "block": 256}},
+          "11,3,orbit": {"options": {"mfma": 1, "block": 1024}},
+          "17,3,orbit": {"options": {"block": 512}}}
+    ctx = Recorder()
+    assert autotune.apply_db(ctx, db, mfma=mfma) == 4
+    want = {(13, 3): {hwcount.HWC_OPT_SPLIT: 1, hwcount.HWC_OPT_BLOCK: 256},
+            (9, 3): {hwcount.HWC_OPT_SPLIT: 1, hwcount.HWC_OPT_BLOCK: 256},
+            (11, 3): {hwcount.HWC_OPT_MFMA: 1, hwcount.HWC_OPT_BLOCK: 1024},
+            (17, 3): {hwcount.HWC_OPT_BLOCK: 512}}
+    if mfma:
+        del want[(13, 3)][hwcount.HWC_OPT_BLOCK]
+    assert ctx.set == want
