@@ -217,17 +217,21 @@ __global__ __launch_bounds__(kThreads) void hist_small_batch_kernel(const HistJo
 }  // namespace
 
 // Whether a request's histogram is taken by one workgroup: at most
-// kHistSmallMax rows and a key of bit fields within 64 bits.
+// kHistSmallMax rows and a key of bit fields within 64 bits, for a key space that
+// hist_run accepts (2^63 keys: at q = 61, g = 4 the fields fit, the space does not).
 bool hist_is_small(uint64_t n, uint32_t g, uint32_t q, bool lam) {
   if (n == 0 || n > kHistSmallMax) return false;
-  uint32_t bits = lam ? 32u - (uint32_t)__builtin_clz(lam_code_list(g, nullptr)) : 0u;
+  const uint32_t codes = lam ? lam_code_list(g, nullptr) : 0u;
+  uint32_t bits = lam ? 32u - (uint32_t)__builtin_clz(codes) : 0u;
+  double space = lam ? __builtin_log2((double)codes) : 0.0;
   uint64_t qk = 1;
   for (uint32_t k = 0; k < g; ++k) {
     qk *= q;
     if (qk > (1u << 24)) return false;
     bits += 32u - (uint32_t)__builtin_clz((uint32_t)(2 * qk + 2));
+    space += __builtin_log2((double)(2 * qk + 3));
   }
-  return bits <= 64;
+  return bits <= 64 && space <= 63.0;
 }
 
 hipError_t launch_hist_small(const HistJob& J, const LamCodes* lc, uint32_t* err, hipStream_t s) {

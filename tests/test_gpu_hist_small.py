@@ -106,3 +106,32 @@ def test_batch_of_small_and_large(ctx, curvegen_mod, flags):
         ctx.status()
     for j in jobs:
         _check(j, j["d_out_N"].cpu().numpy())
+
+
+@pytest.mark.parametrize("q", [59, 61])
+def test_key_space_limit(ctx, curvegen_mod, q):
+    """Genus 4: the tuples number less than 2^63 at q = 59 and more at q = 61, whose
+    histogram is refused in every form."""
+    import torch
+    from paper_1805_11991_amd import hwcount as hw
+    rng = np.random.default_rng(q)
+    rows = rng.integers(1, q, (5, 11)).astype(np.int8)
+    j = {"q": q, "g": 4, "d_coeffs": torch.from_numpy(rows).cuda(),
+         "d_out_N": torch.zeros((5, 4), dtype=torch.int32, device="cuda"),
+         "d_hist_keys": torch.full((5, 4), -7, dtype=torch.int32, device="cuda"),
+         "d_hist_counts": torch.full((5,), -7, dtype=torch.int64, device="cuda"),
+         "d_hist_len": torch.zeros(1, dtype=torch.int64, device="cuda")}
+    calls = [lambda: ctx.count_curves_dev(q, 4, j["d_coeffs"], j["d_out_N"], j["d_hist_keys"], j["d_hist_counts"],
+                                          j["d_hist_len"], flags=hw.HWC_NO_GRAPH),
+             lambda: ctx.count_batch([j], flags=hw.HWC_NO_GRAPH)]
+    for call in calls:
+        print(q, flush=True)
+        if q == 61:
+            with pytest.raises(hw.HwcError):
+                call()
+            ctx.status()
+            continue
+        call()
+        ctx.status()
+        _check(j, j["d_out_N"].cpu().numpy())
+    assert (j["d_hist_keys"].cpu().numpy() == -7).all() == (q == 61)
