@@ -1358,6 +1358,7 @@ struct Scratch {
   void* tcodes;   // dense translates of the rows (plans with a step table)
   uint32_t* acc;  // tile parts: [n][g] summed level counts, then [max_tiles] finished parts
   uint64_t max_tiles;
+  uint64_t lv_rows = 0;   // rows that lv holds, 0: all of them
 };
 
 // Byte sizes of the scratch parts of one request of n rows (plain: per-level
@@ -1531,16 +1532,22 @@ int enqueue(hwc_ctx* c, DevPlan* P, const Scratch& S, const void* codes, int cb,
         HIPX(c, hwc::launch_vcount(V[0].desc, V[0].d_desc, cb, codes, n, 0, g - 1, 4, false, N, lam ? S.lv : nullptr,
                                    c->d_err, V[0].grid, V[0].block, s));
       } else {
-        // one launch per level (plain form) or per pass, counts added up per curve
-        HIPX(c, hwc::launch_fill(S.lv, 0, n * g, s));
-        for (const auto& v : V)
-          for (uint32_t j = v.lo; j <= v.hi; ++j) {
-            if (!(flags & HWC_PLAIN) && j != v.lo) break;
-            const uint32_t hi = (flags & HWC_PLAIN) ? j : v.hi;
-            HIPX(c, hwc::launch_vcount(v.desc, v.d_desc, cb, codes, n, j, hi, v.tw, true, nullptr, S.lv, c->d_err,
-                                       v.grid, v.block, s));
-          }
-        HIPX(c, hwc::launch_assemble(P->desc, cb, codes, n, S.lv, N, s));
+        // one launch per level (plain form) or per pass, counts added up per curve,
+        // over all rows or as many at a time as S.lv holds
+        const uint64_t step = S.lv_rows ? S.lv_rows : n;
+        for (uint64_t r = 0; r < n; r += step) {
+          const uint64_t m = std::min(step, n - r);
+          const void* rows = static_cast<const uint8_t*>(codes) + r * (2 * g + 3) * (uint64_t)cb;
+          HIPX(c, hwc::launch_fill(S.lv, 0, m * g, s));
+          for (const auto& v : V)
+            for (uint32_t j = v.lo; j <= v.hi; ++j) {
+              if (!(flags & HWC_PLAIN) && j != v.lo) break;
+              const uint32_t hi = (flags & HWC_PLAIN) ? j : v.hi;
+              HIPX(c, hwc::launch_vcount(v.desc, v.d_desc, cb, rows, m, j, hi, v.tw, true, nullptr, S.lv, c->d_err,
+                                         v.grid, v.block, s));
+            }
+          HIPX(c, hwc::launch_assemble(P->desc, cb, rows, m, S.lv, N + r * g, s));
+        }
       }
       if (lam)
         HIPX(c, hwc::launch_lambda(P->desc, P->d_desc, cb, codes, n, S.lv, lam, (flags & kFlagSqf) ? 1u : 0u, s));
@@ -1721,13 +1728,25 @@ int run_dev_noalloc(hwc_ctx* c, uint32_t q, uint32_t g, const void* codes, int c
   if (rc) return rc;
   void* base = static_scratch(c->device);
   if (!base) return fail(c, HWC_ERR_DEVICE, "the static scratch of this device was not set up");
-  const ScratchSizes z = scratch_sizes(n, g, cb, needs_lv(P, flags, nullptr), hk != nullptr, needs_tcodes(P));
+  ScratchSizes z = scratch_sizes(n, g, cb, needs_lv(P, flags, nullptr), hk != nullptr, needs_tcodes(P));
   Scratch S;
-  const uint64_t need = carve_scratch(z, g, nullptr, &S);
+  uint64_t need = carve_scratch(z, g, nullptr, &S);
+  // the matrix path sorts no rows: where its passes' level counts do not fit
+  // beside the other parts, they go where the row order would, for n / g rows at
+  // a time
+  const bool in_perm = need > kStaticScratchBytes && P->vpath && !(flags & HWC_PLAIN) && z.lv;
+  if (in_perm) {
+    z.lv = 0;
+    need = carve_scratch(z, g, nullptr, &S);
+  }
   if (need > kStaticScratchBytes)
     return fail(c, HWC_ERR_ARG, "request needs " + std::to_string(need) + " bytes of scratch; the static scratch holds " +
                                     std::to_string(kStaticScratchBytes));
   carve_scratch(z, g, static_cast<uint8_t*>(base), &S);
+  if (in_perm) {
+    S.lv = S.perm;
+    S.lv_rows = n / g;
+  }
   if ((rc = enqueue(c, P, S, codes, cb, n, N, nullptr, hk, hc, hcap, hlen, flags, s, false))) return rc;
   HIPX(c, hipEventRecord(c->static_ev, s));
   c->static_ev_valid = true;

@@ -112,3 +112,23 @@ def test_noalloc_refuses_what_it_cannot_do(ctxs, curvegen_mod):
         with pytest.raises(hwcount.HwcError) as ei:
             fresh.count_curves_dev_noalloc(13, 3, big[:10], Nbig[:10], flags=hwcount.HWC_VALIDATE)
         assert ei.value.code == hwcount.HWC_ERR_ARG
+
+
+@pytest.mark.parametrize("q,g,n,flags", [(7, 4, 4_000_001, 0), (11, 3, 5_000_000, 1)])
+def test_noalloc_of_several_passes_needs_no_more_scratch(ctxs, q, g, n, flags):
+    """Matrix-path plans whose points take several images: the requests fit the
+    static scratch as those of one image do (about 6 bytes a row)."""
+    import torch
+    ctx = ctxs["mfma"]
+    ctx.plan_info(q, g, flags)
+    gen = torch.Generator(device="cuda").manual_seed(q)
+    d = torch.randint(0, q, (n, 2 * g + 3), dtype=torch.int8, device="cuda", generator=gen)
+    d[:, -2:] = torch.clamp(d[:, -2:], min=1)
+    N = [torch.full((n, g), -1, dtype=torch.int32, device="cuda") for _ in range(2)]
+    torch.cuda.synchronize()
+    print(q, g, n, flush=True)
+    ctx.count_curves_dev(q, g, d, N[0], flags=flags)
+    ctx.status()
+    ctx.count_curves_dev_noalloc(q, g, d, N[1], flags=flags)
+    ctx.status()
+    assert torch.equal(N[0], N[1])
