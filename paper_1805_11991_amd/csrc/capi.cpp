@@ -173,6 +173,7 @@ struct DevPlan {
   void* d_nimage = nullptr;
   uint32_t* d_tmat = nullptr;
   uint32_t nblock = 1024, ngrid = 0;
+  uint64_t norm_bytes = 0;           // of dev_bytes
   uint64_t dev_bytes = 0;
   uint64_t last_use = 0;
   uint32_t block = 256, grid = 0, wpe = 1;
@@ -475,6 +476,56 @@ std::shared_ptr<FieldEntry> get_field(hwc_ctx* c, uint32_t p, uint32_t e, uint32
   return fe;
 }
 
+// Relative cost of one tile, for ordering and cutting mixed batches.
+void set_tile_cost(DevPlan* P) {
+  P->tile_cost = 0;
+  for (uint32_t j = 0; j < P->g; ++j) {
+    const uint32_t form = P->desc.lv[j].form;
+    P->tile_cost += (double)P->desc.lv[j].nx * (2 * P->g + 2) *
+                    (P->npath              ? 0.9
+                     : form == hwc::kFormA ? 1.0
+                     : form == hwc::kFormC ? 1.3
+                     : form == hwc::kFormE ? 2.5
+                     : form == hwc::kFormG ? 4.0
+                     : form == hwc::kFormF ? 6.0
+                                           : 12.0);
+  }
+}
+
+// Releases a plan's norm tables (deferred, as free_plan), leaving it to count by
+// the level tables.
+void release_norm(hwc_ctx* c, DevPlan* P) {
+  defer_free(c, P->d_nimage, P->norm_bytes);
+  defer_free(c, P->d_ndesc, 0);
+  defer_free(c, P->d_tmat, 0);
+  P->d_nimage = nullptr;
+  P->d_ndesc = nullptr;
+  P->d_tmat = nullptr;
+  P->dev_bytes -= P->norm_bytes;
+  P->norm_bytes = 0;
+  P->npath = false;
+}
+
+// Norm tables are an extra: where the plans fit the table budget without them,
+// those of the least recently used plans are given back (P, not resident yet,
+// comes last), and no plan is evicted or refused for their sake.
+void fit_norms(hwc_ctx* c, DevPlan* P) {
+  uint64_t norms = P->norm_bytes;
+  for (const auto& kv : c->plans) norms += kv.second->norm_bytes;
+  if (c->table_bytes <= c->budget || c->table_bytes - norms > c->budget) return;
+  while (c->table_bytes > c->budget) {
+    DevPlan* lru = nullptr;
+    for (const auto& kv : c->plans)
+      if (kv.second->norm_bytes && (!lru || kv.second->last_use < lru->last_use)) lru = kv.second.get();
+    if (!lru) lru = P;
+    drop_graphs_of_plan(c, lru);
+    c->table_bytes -= lru->norm_bytes;
+    release_norm(c, lru);
+    set_tile_cost(lru);
+  }
+  (void)reap(c, true);
+}
+
 // Releases the plan's device memory (deferred: queued work may still read it).
 void free_plan(hwc_ctx* c, DevPlan* P) {
   drop_graphs_of_plan(c, P);
@@ -489,13 +540,7 @@ void free_plan(hwc_ctx* c, DevPlan* P) {
     defer_free(c, v.d_image, 0);
     defer_free(c, v.d_desc, 0);
   }
-  defer_free(c, P->d_nimage, 0);
-  defer_free(c, P->d_ndesc, 0);
-  defer_free(c, P->d_tmat, 0);
-  P->d_nimage = nullptr;
-  P->d_ndesc = nullptr;
-  P->d_tmat = nullptr;
-  P->npath = false;
+  release_norm(c, P);
   c->grave_bytes += P->dev_bytes;
   P->d_shift = nullptr;
   P->vpasses.clear();
@@ -1042,6 +1087,7 @@ int build_norm(hwc_ctx* c, DevPlan* P, uint32_t p, uint32_t e, const Tuning& T, 
   HIPX(c, hipMalloc(&P->d_ndesc, sizeof(N)));
   HIPX(c, hipMemcpy(P->d_ndesc, &N, sizeof(N), hipMemcpyHostToDevice));
   P->dev_bytes += bytes;
+  P->norm_bytes = bytes;
   c->table_bytes += bytes;
   P->npath = true;
   return HWC_OK;
@@ -1311,7 +1357,9 @@ int get_plan(hwc_ctx* c, uint32_t q, uint32_t g, uint32_t orbit, DevPlan** out) 
     // memory counts against the budget until it is actually freed (once the
     // work reading it is done)
     (void)reap(c, false);
-    while (c->table_bytes + c->grave_bytes > c->budget) {
+    for (;;) {
+      fit_norms(c, P.get());
+      if (c->table_bytes + c->grave_bytes <= c->budget) break;
       auto victim = c->plans.end();
       for (auto i2 = c->plans.begin(); i2 != c->plans.end(); ++i2)
         if (i2->second->pins == 0 && (victim == c->plans.end() || i2->second->last_use < victim->second->last_use))
@@ -1331,17 +1379,7 @@ int get_plan(hwc_ctx* c, uint32_t q, uint32_t g, uint32_t orbit, DevPlan** out) 
       return fail(c, HWC_ERR_OOM_BUDGET, "tables exceed the context's HBM budget");
     }
   }
-  // relative cost of one tile, for ordering mixed batches (longest first)
-  P->tile_cost = 0;
-  for (uint32_t j = 0; j < g; ++j)
-    P->tile_cost += (double)D.lv[j].nx * (2 * g + 2) *
-                    (P->npath                 ? 0.9
-                     : form[j] == hwc::kFormA ? 1.0
-                     : form[j] == hwc::kFormC ? 1.3
-                     : form[j] == hwc::kFormE ? 2.5
-                     : form[j] == hwc::kFormG ? 4.0
-                     : form[j] == hwc::kFormF ? 6.0
-                                              : 12.0);
+  set_tile_cost(P.get());
   P->last_use = ++c->tick;
   *out = P.get();
   c->plans[key] = std::move(P);

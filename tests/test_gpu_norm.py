@@ -115,3 +115,35 @@ def test_small_budget_keeps_the_level_tables(curvegen_mod):
         got, _ = c.count_curves(101, 2, rows)
         assert c.stats()["table_bytes"] < full - 1
     assert np.array_equal(got, want)
+
+
+def test_budget_of_several_plans(ctx, curvegen_mod):
+    """A budget that holds the level tables of several plans, and not all of their
+    norm tables: a batch over them runs (its plans cannot be evicted), and calls in
+    turn evict none of them."""
+    import torch
+    from paper_1805_11991_amd import hwcount as hw
+    fields = (101, 121, 199)
+    rows = {q: _rows(curvegen_mod, q, 200) for q in fields}
+    want = {q: _run(ctx, q, rows[q], hw.HWC_PLAIN) for q in fields}
+    with hw.Context(device=0, autotune_db=None) as c:
+        for q in fields:
+            c.plan_info(q, 2)
+        full = c.stats()["table_bytes"]
+    with hw.Context(device=0, autotune_db=None, hbm_budget_bytes=full - 1) as c:
+        for rep in range(2):
+            for q in fields:
+                assert np.array_equal(_run(c, q, rows[q], 0), want[q]), q
+        st = c.stats()
+        assert st["evictions"] == 0 and st["table_bytes"] + st["pending_free_bytes"] < full
+    with hw.Context(device=0, autotune_db=None, hbm_budget_bytes=full - 1) as c:
+        jobs = [{"q": q, "g": 2, "d_coeffs": torch.from_numpy(rows[q]).cuda(),
+                 "d_out_N": torch.zeros((len(rows[q]), 2), dtype=torch.int32, device="cuda")} for q in fields]
+        torch.cuda.synchronize()
+        for flags in (hw.HWC_NO_GRAPH, 0, 0):
+            c.count_batch(jobs, flags=flags)
+            c.status()
+            for j in jobs:
+                assert np.array_equal(j["d_out_N"].cpu().numpy(), want[j["q"]]), (j["q"], flags)
+                j["d_out_N"].zero_()
+            torch.cuda.synchronize()
