@@ -1200,25 +1200,68 @@ __device__ __forceinline__ uint32_t next_job(const JobDesc* __restrict__ jobs, u
   return (uint32_t)best - 1u;
 }
 
+// How a workgroup's waves take a job's entries: a chunk at a time from the job's
+// queue in device memory (one atomic, 13 to 20 ns on the one address for all
+// workgroups), entry by entry from the chunk through a word in LDS.  The word
+// holds the chunk's end in its high half and the next entry in its low one; every
+// wave adds one and reads what was there.  Below the end it has an entry; exactly
+// one wave meets the end itself, fetches the next chunk and writes the word anew
+// (kJobDone once the queue is empty); those past the end wait for that.  A chunk is
+// an entry for every wave, or a quarter of a workgroup's share of what is left,
+// so late workgroups find work and the queue is popped a few hundred times.
+constexpr uint64_t kJobDone = 0xFFFFFFFFull << 32;
+
+__device__ __forceinline__ uint32_t next_job_entry(uint64_t* range, uint32_t* queue, uint32_t n) {
+  uint32_t e = n;
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    for (;;) {
+      uint64_t v = __hip_atomic_fetch_add(range, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      const uint32_t end = (uint32_t)(v >> 32), at = (uint32_t)v;
+      if (end == 0xFFFFFFFFu) break;
+      if (at < end) {
+        e = at;
+        break;
+      }
+      if (at == end) {
+        const uint32_t waves = blockDim.x / kWave, share = (n - end) / (4u * gridDim.x);
+        const uint32_t chunk = share > waves ? share : waves;
+        const uint32_t got = end < n ? atomicAdd(queue, chunk) : n;
+        const uint32_t stop = got < n ? (n - got < chunk ? n : got + chunk) : 0u;
+        __hip_atomic_store(range, got < n ? (uint64_t)stop << 32 | (got + 1u) : kJobDone, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (got < n) e = got;
+        break;
+      }
+      do {   // the wave that met the end writes the word: it waits for nothing but its own atomic
+        __builtin_amdgcn_s_sleep(1);
+        v = __hip_atomic_load(range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+      } while ((uint32_t)v > (uint32_t)(v >> 32));
+    }
+  }
+  return uniform(e);
+}
+
 // One persistent launch over the jobs of a batch.  Each workgroup starts at the
 // job that the host gave it (workgroups in proportion to the jobs' work, so
-// that most stage one image only), its waves pop the job's tiles until its
+// that most stage one image only), its waves take the job's entries until its
 // queue is empty, and it goes on to the open job with the most work left,
 // restaging its LDS image where that one has another plan.  (Taking the jobs
 // one after another with every workgroup, each image was staged 256 times and
 // every wave popped every queue: 71 jobs of 8192 curves took 5.6 ms, now 4.3;
 // 32 mixed jobs of up to 8192 curves, their tiles in more parts, 4.0 and 0.6.)  slot: byte
-// offset, past every image, of the word that broadcasts the next job (inside
-// the dynamic block, so the kernel has no static LDS).
+// offset, past every image, of the word that broadcasts the next job and of the
+// chunk word (inside the dynamic block, so the kernel has no static LDS).
 template <int GMAX>
 __global__ __launch_bounds__(1024) void batch_kernel(const JobDesc* __restrict__ jobs, uint32_t njobs,
                                                      const uint32_t* __restrict__ first, uint32_t slot) {
   extern __shared__ uint32_t lds32[];
   uint32_t& sh_next = *reinterpret_cast<uint32_t*>(reinterpret_cast<uint8_t*>(lds32) + slot);
+  uint64_t* range = reinterpret_cast<uint64_t*>(reinterpret_cast<uint8_t*>(lds32) + slot + 8);
   constexpr uint32_t lb = kImageBase;
-  const uint32_t lane = threadIdx.x & (kWave - 1);
   const PlanDesc* staged = nullptr;
   uint32_t k = uniform(first[blockIdx.x]);
+  if (threadIdx.x == 0) *range = 0;
+  __syncthreads();
   while (k < njobs) {
     const JobDesc& J = jobs[k];
     const uint32_t nt = *J.ntiles << J.plog;   // queue entries: tiles, or parts of tiles
@@ -1229,16 +1272,17 @@ __global__ __launch_bounds__(1024) void batch_kernel(const JobDesc* __restrict__
       staged = P;
     }
     for (;;) {
-      uint32_t v = 0;
-      if (lane == 0) v = atomicAdd(J.queue, 1u);
-      const uint32_t t = uniform(v);
+      const uint32_t t = next_job_entry(range, J.queue, nt);
       if (t >= nt) break;
       process_job_tile<GMAX>(J, lb, t);
     }
     __syncthreads();
     if (threadIdx.x < kWave) {
       const uint32_t nx = next_job(jobs, njobs);
-      if (threadIdx.x == 0) sh_next = nx;
+      if (threadIdx.x == 0) {
+        sh_next = nx;
+        *range = 0;
+      }
     }
     __syncthreads();
     k = uniform(sh_next);
