@@ -177,7 +177,7 @@ struct DevPlan {
   uint64_t dev_bytes = 0;
   uint64_t last_use = 0;
   uint32_t block = 256, grid = 0, wpe = 1;
-  double tile_cost = 0;
+  double tile_cost = 0;              // set_tile_cost
   uint32_t pins = 0;                 // > 0 while a batch being assembled uses the plan
 };
 
@@ -476,20 +476,32 @@ std::shared_ptr<FieldEntry> get_field(hwc_ctx* c, uint32_t p, uint32_t e, uint32
   return fe;
 }
 
-// Relative cost of one tile, for ordering and cutting mixed batches.
+// Cost of one tile of 64 curves, for ordering and cutting mixed batches: the
+// nanoseconds that the whole chip takes per tile of a large request.  Measured
+// (count kernel, 2^16 to 2^20 curves, every field with g = 3, q < 54 and g = 4,
+// q < 20, some 50 with g = 2, q < 402): about 10 ns a tile whatever its points, and
+// per point and Horner step (2g + 2 a point), in picoseconds, by table form and
+// split factor
+//   A  mu_4 3.3-4.1, mu_3 5.3-6.2, else 5.7      C  mu_4 4.1-4.4, mu_2 6.9-7.8
+//   E  mu_4 6.1                                  G  mu_4 9.4, mu_2 14.1
+//   F  mu_4 9.0-11.6, mu_2 15.2                  D  76-105
+// and for genus 2 by norms 3.0-3.5 where v and -v go together, 4.7-5.9 at other
+// primes, 5.5-6.3 at prime powers.
 void set_tile_cost(DevPlan* P) {
-  P->tile_cost = 0;
+  double ps = 0;
   for (uint32_t j = 0; j < P->g; ++j) {
-    const uint32_t form = P->desc.lv[j].form;
-    P->tile_cost += (double)P->desc.lv[j].nx * (2 * P->g + 2) *
-                    (P->npath              ? 0.9
-                     : form == hwc::kFormA ? 1.0
-                     : form == hwc::kFormC ? 1.3
-                     : form == hwc::kFormE ? 2.5
-                     : form == hwc::kFormG ? 4.0
-                     : form == hwc::kFormF ? 6.0
-                                           : 12.0);
+    const hwc::LevelDesc& L = P->desc.lv[j];
+    const bool four = L.msplit == 4;
+    const double step = P->npath              ? (P->ndesc.norm.pair ? 3.2 : P->desc.p == P->q ? 5.3 : 6.0)
+                        : L.form == hwc::kFormA ? (four ? 3.9 : 5.7)
+                        : L.form == hwc::kFormC ? (four ? 4.3 : 7.2)
+                        : L.form == hwc::kFormE ? (four ? 6.1 : 10.0)
+                        : L.form == hwc::kFormG ? (four ? 9.4 : 14.1)
+                        : L.form == hwc::kFormF ? (four ? 11.0 : 15.2)
+                                                : 90.0;
+    ps += (double)L.nx * (2 * P->g + 2) * step;
   }
+  P->tile_cost = 10.0 + ps * 1e-3;
 }
 
 // Releases a plan's norm tables (deferred, as free_plan), leaving it to count by
@@ -1819,6 +1831,15 @@ struct BatchPlan {
 
 constexpr uint64_t kNoShift = ~0ull;
 
+// A batch's chunks hold at least this many nanoseconds of the chip's work (or an
+// entry for every wave): five pops of a queue or so, so that the queue of one job
+// alone does not bound its entries, and no more, as the waves of a workgroup that
+// popped more entries than it has idle waves keep others from them at the end.
+// 15 / 40 / 80 ns / an entry for every wave, us: 2^18 curves, g = 3, q = 31, 2611 /
+// 2607 / 2654 / 2884; g = 4, q = 13, 1619 / 1618 / 1623 / 1703; 4096, g = 3, q = 31,
+// 165 / 169 / 158 / 159; five mixed jobs of 4096 304 / 313 / 287 / 288.
+constexpr double kPopNs = 80.0;
+
 // Upper bound of a batch's descriptors: the jobs, their histograms and
 // bucketings, and the first job of each workgroup (at most 32 waves a CU, a
 // workgroup has at least four), each part padded to 16 bytes.
@@ -1944,7 +1965,10 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
                    [&](size_t a, size_t b) { return B.plans[a]->tile_cost > B.plans[b]->tile_cost; });
   const size_t nz = B.order.size();
   // tile parts: eight entries of about equal work for each of 16 waves a CU,
-  // where the jobs have the points
+  // where the jobs have the points.  128 entries a CU / 64 / 32 / 16, us: 65 536
+  // curves, g = 3, q = 49, 4097 / 4409 / 5888 / 5769; g = 3, q = 25, 416 / 414 / 482 /
+  // 715; 2^18, g = 3, q = 13, 358 / 336 / 345 / 389; 17 jobs of g = 3, 4096 each, 2032
+  // / 2181 / 2313 / 2722: light jobs lose a few per cent, heavy ones gain more
   double work = 0;
   auto job_tiles = [&](size_t r) { return (jobs[B.order[r]].n + hwc::kWave - 1) / hwc::kWave; };
   for (size_t r = 0; r < nz; ++r) work += B.plans[B.order[r]]->tile_cost * (double)job_tiles(r);
@@ -2049,7 +2073,9 @@ int run_batch(hwc_ctx* c, const hwc_job* jobs, size_t njobs, uint32_t flags, hip
     hj[r].g = J.g;
     hj[r].plog = B.plog[r];
     hj[r].norm = P->npath ? 1u : 0u;
-    hj[r].cost = (float)(P->tile_cost / (double)(1u << B.plog[r]));
+    const double entry = P->tile_cost / (double)(1u << B.plog[r]);   // ns
+    hj[r].cost = (float)entry;
+    hj[r].chunk = (uint32_t)std::max(1.0, std::ceil(kPopNs / entry));
     hj[r].acc = B.plog[r] ? static_cast<uint32_t*>(st.bacc.p) + B.aoff[r] : nullptr;
     hj[r].done = B.plog[r] ? hj[r].acc + J.n * J.g : nullptr;
     if (J.n <= B.bucket_max) {

@@ -1207,35 +1207,54 @@ __device__ __forceinline__ uint32_t next_job(const JobDesc* __restrict__ jobs, u
 // wave adds one and reads what was there.  Below the end it has an entry; exactly
 // one wave meets the end itself, fetches the next chunk and writes the word anew
 // (kJobDone once the queue is empty); those past the end wait for that.  A chunk is
-// an entry for every wave, or a quarter of a workgroup's share of what is left,
-// so late workgroups find work and the queue is popped a few hundred times.
+// the entries that a pop is worth (least, from the host; one for each wave at
+// most), or a quarter of a workgroup's share of what is left, so late workgroups
+// find work.  Up to kDirectPops entries the pops cost less than chunks that end in
+// a workgroup whose other waves are busy (4096 curves, chunks / pops, us: g = 3,
+// q = 11, 520 entries 115 / 108; g = 3, q = 17, 1040 entries 99 / 138): every wave
+// pops for itself, and the first to find the queue empty tells its workgroup.
 constexpr uint64_t kJobDone = 0xFFFFFFFFull << 32;
+constexpr uint32_t kDirectPops = 1024;
 
-__device__ __forceinline__ uint32_t next_job_entry(uint64_t* range, uint32_t* queue, uint32_t n) {
+__device__ __forceinline__ uint64_t load_range(const uint64_t* range) {
+  return __hip_atomic_load(range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void store_range(uint64_t* range, uint64_t v) {
+  __hip_atomic_store(range, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+__device__ __forceinline__ uint32_t next_job_entry(uint64_t* range, uint32_t* queue, uint32_t least, uint32_t n) {
   uint32_t e = n;
   if ((threadIdx.x & (kWave - 1)) == 0) {
-    for (;;) {
-      uint64_t v = __hip_atomic_fetch_add(range, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      const uint32_t end = (uint32_t)(v >> 32), at = (uint32_t)v;
-      if (end == 0xFFFFFFFFu) break;
-      if (at < end) {
-        e = at;
-        break;
+    if (n <= kDirectPops) {
+      if (load_range(range) != kJobDone) e = atomicAdd(queue, 1u);
+      if (e >= n) store_range(range, kJobDone);
+    } else {
+      for (;;) {
+        const uint64_t v = __hip_atomic_fetch_add(range, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        const uint32_t end = (uint32_t)(v >> 32), at = (uint32_t)v;
+        if (end == 0xFFFFFFFFu) break;
+        if (at < end) {
+          e = at;
+          break;
+        }
+        if (at == end) {
+          const uint32_t chunk = max(min(least, blockDim.x / kWave), (n - end) / (4u * gridDim.x));
+          const uint32_t got = end < n ? atomicAdd(queue, chunk) : n;
+          if (got < n) {
+            store_range(range, (uint64_t)(n - got < chunk ? n : got + chunk) << 32 | (got + 1u));
+            e = got;
+          } else {
+            store_range(range, kJobDone);
+          }
+          break;
+        }
+        uint64_t w;
+        do {   // the wave that met the end writes the word: it waits for nothing but its own atomic
+          __builtin_amdgcn_s_sleep(1);
+          w = load_range(range);
+        } while ((uint32_t)w > (uint32_t)(w >> 32));
       }
-      if (at == end) {
-        const uint32_t waves = blockDim.x / kWave, share = (n - end) / (4u * gridDim.x);
-        const uint32_t chunk = share > waves ? share : waves;
-        const uint32_t got = end < n ? atomicAdd(queue, chunk) : n;
-        const uint32_t stop = got < n ? (n - got < chunk ? n : got + chunk) : 0u;
-        __hip_atomic_store(range, got < n ? (uint64_t)stop << 32 | (got + 1u) : kJobDone, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (got < n) e = got;
-        break;
-      }
-      do {   // the wave that met the end writes the word: it waits for nothing but its own atomic
-        __builtin_amdgcn_s_sleep(1);
-        v = __hip_atomic_load(range, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-      } while ((uint32_t)v > (uint32_t)(v >> 32));
     }
   }
   return uniform(e);
@@ -1272,7 +1291,7 @@ __global__ __launch_bounds__(1024) void batch_kernel(const JobDesc* __restrict__
       staged = P;
     }
     for (;;) {
-      const uint32_t t = next_job_entry(range, J.queue, nt);
+      const uint32_t t = next_job_entry(range, J.queue, J.chunk, nt);
       if (t >= nt) break;
       process_job_tile<GMAX>(J, lb, t);
     }

@@ -255,7 +255,8 @@ struct JobDesc {
   // (counted in done) assembles N.  plog = 0: whole tiles.
   uint32_t plog;
   uint32_t norm;          // the plan has norm tables
-  float cost;             // relative work of one queue entry
+  float cost;             // work of one queue entry
+  uint32_t chunk;         // entries a workgroup takes at once, at least (at most one for each of its waves)
   uint32_t* acc;          // [n][g] packed level counts (zero before the launch)
   uint32_t* done;         // [tiles] parts finished (zero before the launch)
 };
