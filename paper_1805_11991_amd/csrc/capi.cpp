@@ -1524,10 +1524,14 @@ uint32_t part_log_single(const DevPlan* P, uint32_t flags, uint64_t n) {
 
 // Rows up to which one workgroup buckets a request alone (bucket_small.hip: 9 us
 // at 500 rows, 110 us at 8192, against about 22 us for the five launches of the
-// many-workgroup kernels), and jobs of up to kBucketSmallMax rows from which on
-// a batch buckets them all in one launch instead of five launches each.
+// many-workgroup kernels), and jobs of up to kBucketSmallMax rows from which on a
+// batch buckets them all in one launch instead of five launches each.  Whole
+// batch in separate launches / in one, us, two jobs and three: g = 3, q = 13, 4096
+// rows 122 / 102, 149 / 104; 8192 rows 140 / 144, 170 / 149; g = 2, q = 27, 8192 rows
+// 143 / 158, 172 / 161; g = 4, q = 7, 8192 rows 250 / 289, 301 / 305; g = 2, q = 101,
+// 8192 rows 172 / 150, 209 / 166; one job of 8192 rows 111 / 138 at g = 3, q = 13.
 constexpr uint32_t kBucketAlone = 1024;
-constexpr size_t kBucketTogether = 6;
+constexpr size_t kBucketTogether = 3;
 
 // The one-workgroup bucketing of n rows (out: their dense translates, or null).
 hwc::BucketJob bucket_job(const DevPlan* P, const void* codes, void* out, int cb, uint64_t n, uint32_t* perm,

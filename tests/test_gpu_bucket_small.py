@@ -1,8 +1,10 @@
-"""The one-workgroup bucketing (requests of up to 8192 rows): a request's counts
-equal the same rows' counts inside a larger request, which is bucketed by the
-many-workgroup kernels -- at the edges of its waves, of its passes over the
-rows and of its range; rows as given, translated by dot products (prime q) or
-by the step table (prime powers); int8 and int16; few and many patterns."""
+"""The one-workgroup bucketing (a request of up to 1024 rows alone, jobs of up to
+8192 rows in a batch of several): a request's counts equal the same rows' counts
+inside a larger request, which is bucketed by the many-workgroup kernels -- at
+the edges of its waves, of its passes over the rows and of its range; rows as
+given, translated by dot products (prime q) or by the step table (prime powers);
+int8 and int16; few and many patterns.  Single requests of 1025 rows and more
+take the many-workgroup kernels: the edge of the rule."""
 from __future__ import annotations
 
 import numpy as np
@@ -76,6 +78,30 @@ def test_batch_of_small_and_large(ctx, curvegen_mod):
         ctx.status()
         for j, w in zip(jobs, want):
             assert np.array_equal(j["d_out_N"].cpu().numpy(), w), (j["q"], j["g"], flags)
+
+
+@pytest.mark.parametrize("q,g,dtype", [(13, 3, np.int8), (31, 2, np.int16), (67, 2, np.int16), (27, 2, np.int8),
+                                       (9, 3, np.int16), (25, 2, np.int16), (3, 1, np.int8), (7, 4, np.int16)])
+def test_large_jobs_together(ctx, oracle_mod, curvegen_mod, q, g, dtype):
+    """More rows than one pass of the workgroup: every job of a batch of at least
+    three, at the edges of the passes and of the range."""
+    import torch
+    from paper_1805_11991_amd import hwcount as hw
+    rows = _rows(curvegen_mod, q, g, 9000, dtype)
+    want = _count(ctx, q, g, rows)                       # many-workgroup kernels
+    assert np.array_equal(want[:60], oracle_mod.count_curves(q, g, rows[:60]))
+    cuts = [(0, 1025), (500, 2048), (9000 - 4097, 4097), (7, 8191), (808, 8192), (0, 63), (0, 8193)]
+    jobs = [{"q": q, "g": g, "d_coeffs": torch.from_numpy(np.ascontiguousarray(rows[a:a + n])).cuda(),
+             "d_out_N": torch.full((n, g), -1, dtype=torch.int32, device="cuda")} for a, n in cuts]
+    for flags in (hw.HWC_NO_GRAPH, 0, 0):
+        for j in jobs:
+            j["d_out_N"].fill_(-1)
+        torch.cuda.synchronize()
+        print(q, g, dtype, flags, flush=True)
+        ctx.count_batch(jobs, flags=flags)
+        ctx.status()
+        for (a, n), j in zip(cuts, jobs):
+            assert np.array_equal(j["d_out_N"].cpu().numpy(), want[a:a + n]), (a, n, flags)
 
 
 @pytest.mark.parametrize("bad,code", [((0, 13), -4), ((0, -1), -4), (None, -5)])

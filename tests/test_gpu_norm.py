@@ -52,7 +52,7 @@ def _run(ctx, q, rows, flags):
     return N.cpu().numpy()
 
 
-@pytest.mark.parametrize("q", FIELDS)
+@pytest.mark.parametrize("q", FIELDS + [307])     # 307: the largest folded image
 def test_norm_count(ctx, oracle_mod, curvegen_mod, q):
     from paper_1805_11991_amd import hwcount as hw
     rows = _rows(curvegen_mod, q, 2000)
