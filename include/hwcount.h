@@ -274,14 +274,13 @@ int hwc_device_gather_rate(hwc_ctx* ctx, uint64_t table_entries, uint32_t chains
  * histogram of eq. (1.2)) in the persistent batched form, enqueued on
  * `stream`: the rows of every Zech-path job are bucketed, then in a persistent
  * multi-plan launch every workgroup starts at a job (workgroups in proportion
- * to the jobs' work), its waves pop the tiles of that job's queue, and it goes
+ * to the jobs' work), takes tiles from that job's queue for its waves, and goes
  * on to the job with the most work left (the LDS image restaged only when that
  * one has another plan; the tiles of expensive or small jobs are shared out
- * over several waves, whose counts are summed before N is assembled) -- the loops over the curves and fields of Algorithm 1 in one
- * launch, where
- * the paper launches once per curve and field (Sec. 3.3); jobs on the
- * opt-in matrix-product path follow as their own launches on the same
- * stream.
+ * over several waves, whose counts are summed before N is assembled) -- the
+ * loops over the curves and fields of Algorithm 1 in one launch, where the
+ * paper launches once per curve and field (Sec. 3.3); jobs on the opt-in
+ * matrix-product path follow as their own launches on the same stream.
  * Without HWC_NO_GRAPH the whole batch is captured once into a HIP graph
  * (keyed by the jobs' shapes and pointers) and replayed.  Errors as
  * hwc_count_curves_dev; a plan that cannot fit the HBM budget fails the
@@ -311,7 +310,7 @@ int hwc_ctx_profile_read(hwc_ctx* ctx, double* prep_ms, double* count_ms, double
 #define HWC_OPT_DEVICE_TABLES 4 /* bit mask over levels: bit j-1 set puts level j's Zech table in device
                                     memory (served by L2/MALL) instead of LDS; 0..15 */
 #define HWC_OPT_WAVES_PER_SIMD 5 /* count-kernel build that leaves registers for at least 6 or 8 waves per SIMD
-                                    (0 or 1: no constraint) */
+                                    (0 or 1: no constraint); genus 2 by norms (hwc_plan_info) takes its own */
 #define HWC_OPT_SPLIT_MIN_M 6     /* split only levels with at least this many nonzero elements (default 64):
                                     on small fields a wave meets vanishing bases too often */
 #define HWC_OPT_MFMA 8            /* 0 (default): Zech logarithms for every plan.  1 (opt-in): for prime
