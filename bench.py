@@ -57,7 +57,7 @@ COUNTER_SUMMARY = {"zech": os.path.join(PROFILES, "count_kernel_g3_q13_2p24_coun
                    "mfma": os.path.join(PROFILES, "vcount_kernel_g3_q13_2p24_counters.md")}
 KERNEL_SOURCES = {"zech": ("paper_1805_11991_amd/csrc/count_core.h", "paper_1805_11991_amd/csrc/count_impl.h",
                            "paper_1805_11991_amd/csrc/count_launch.h", "paper_1805_11991_amd/csrc/kernels.hip",
-                           "paper_1805_11991_amd/csrc/plan.h"),
+                           "paper_1805_11991_amd/csrc/parts.h", "paper_1805_11991_amd/csrc/plan.h"),
                   "mfma": ("paper_1805_11991_amd/csrc/vcount.hip", "paper_1805_11991_amd/csrc/plan.h")}
 
 
@@ -272,10 +272,10 @@ def main():
     ap.add_argument("--no-serving", action="store_true")
     ap.add_argument("--calib-copy", action="store_true",
                     help="also run a 1 GiB copy kernel (scale for the traffic counters)")
-    ap.add_argument("--profile-case", choices=("g2_q293_lds", "g2_q293_device", "g4_q13"),
-                    help="counter runs only: time this case alone (g=2 q=293, 2^20 curves, the top level's "
-                         "table as a half table in LDS or in device memory; g=4 q=13, 2^26 curves) and "
-                         "print its line")
+    ap.add_argument("--profile-case", choices=("g2_q293_norms", "g2_q293_device", "g2_fields", "g4_q13"),
+                    help="counter runs only: time this case alone (g=2 q=293, 2^20 curves, by norms or with the "
+                         "top level's table in device memory; the 71 fields of g=2, 2^16 curves each, in one "
+                         "batch; g=4 q=13, 2^26 curves) and print its line")
     args = ap.parse_args()
     if args.gpus != 1:
         print(f"bench.py measures one GPU only: the counter has no multi-GPU path (asked for --gpus {args.gpus})",
@@ -390,6 +390,27 @@ def main():
         }
 
     if args.profile_case:
+        def profile_line(t, curves, **more):
+            print(json.dumps({"metric": "curves/s", "value": round(curves / (t["ms_per_step"] * 1e-3), 1),
+                              "unit": "curves/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
+                              "ms_per_step": t["ms_per_step"], "higher_is_better": True, "scaling": "weak",
+                              "vs_baseline": None, "data": "synthetic", **more}))
+
+        if args.profile_case == "g2_fields":
+            from paper_1805_11991_amd.serving import odd_prime_power
+            jobs = []
+            for qq in (v for v in range(3, 300) if odd_prime_power(v)):
+                _, dj, Nj, hkj, hcj, hlj = setup(qq, 2, 1 << 16, curvegen.BASE_SEED + 2 + qq)
+                jobs.append(dict(q=qq, g=2, d_coeffs=dj, d_out_N=Nj, d_hist_keys=hkj, d_hist_counts=hcj,
+                                 d_hist_len=hlj))
+            tp = timed_steps(torch, stream, lambda: ctx.count_batch(jobs, stream=stream), args.steps, args.warmup)
+            ctx.status()
+            log(f"{args.profile_case}: {tp['ms_per_step']} ms/step")
+            profile_line(tp, len(jobs) << 16, config={"workload": "profile case g2_fields", "fields": len(jobs),
+                                                      "g": 2, "curves": len(jobs) << 16})
+            if args.calib_copy:
+                calibration_copy(torch, dev)
+            return
         qp, gp, npc = (13, 4, 1 << 26) if args.profile_case == "g4_q13" else (293, 2, 1 << 20)
         pctx = ctx
         if args.profile_case == "g2_q293_device":
@@ -400,18 +421,15 @@ def main():
         kp = kernel_ms(pctx, runner(pctx, qp, gp, pb, 0), 2)
         pctx.status()
         log(f"{args.profile_case}: {tp['ms_per_step']} ms/step, count kernel {kp['count_ms']:.3f} ms")
-        print(json.dumps({"metric": "curves/s", "value": round(npc / (tp["ms_per_step"] * 1e-3), 1),
-                          "unit": "curves/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
-                          "ms_per_step": tp["ms_per_step"], "higher_is_better": True, "scaling": "weak",
-                          "vs_baseline": None, "dtype": f"int{8 * pb[1].element_size()} codes, integer logs",
-                          "data": "synthetic",
-                          "config": {"workload": f"profile case {args.profile_case}", "q": qp, "g": gp,
-                                     "curves": npc},
-                          "count_kernel_ms": round(kp["count_ms"], 4),
-                          "levels": [{k: L[k] for k in ("M", "form", "nx", "msplit")} for L in pctx.plan_info(qp, gp)],
-                          "algorithmic_lookups_per_launch": algorithmic_lookups(pb[0], pctx.plan_info(qp, gp)),
-                          "performed_lookups_per_launch": lookups_per_batch(
-                              evaluated_rows(pctx, qp, gp, pb[1]), pctx.plan_info(qp, gp))[0]}))
+        levels = pctx.plan_info(qp, gp)
+        performed = (norm_lookups(qp, pb[0]) if args.profile_case == "g2_q293_norms"
+                     else lookups_per_batch(evaluated_rows(pctx, qp, gp, pb[1]), levels)[0])
+        profile_line(tp, npc, dtype=f"int{8 * pb[1].element_size()} codes, integer logs",
+                     config={"workload": f"profile case {args.profile_case}", "q": qp, "g": gp, "curves": npc},
+                     count_kernel_ms=round(kp["count_ms"], 4),
+                     levels=[{k: L[k] for k in ("M", "form", "nx", "msplit")} for L in levels],
+                     algorithmic_lookups_per_launch=algorithmic_lookups(pb[0], levels),
+                     performed_lookups_per_launch=performed)
         if args.calib_copy:
             calibration_copy(torch, dev)
         return

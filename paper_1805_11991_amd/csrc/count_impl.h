@@ -1270,8 +1270,9 @@ __device__ __forceinline__ uint32_t next_job_entry(uint64_t* range, uint32_t* qu
 // queue is empty, and it goes on to the open job with the most work left,
 // restaging its LDS image where that one has another plan.  (Taking the jobs
 // one after another with every workgroup, each image was staged 256 times and
-// every wave popped every queue: 71 jobs of 8192 curves took 5.6 ms, now 4.3;
-// 32 mixed jobs of up to 8192 curves, their tiles in more parts, 4.0 and 0.6.)  slot: byte
+// every wave popped every queue: 71 jobs of 8192 curves 5.6 -> 4.3 ms, 32 mixed jobs
+// of up to 8192 curves, their tiles in more parts, 4.0 -> 0.6; with level 2 in pairs
+// and entries in chunks 3.3 and 0.54.)  slot: byte
 // offset, past every image, of the word that broadcasts the next job and of the
 // chunk word (inside the dynamic block, so the kernel has no static LDS).
 template <int GMAX>
