@@ -1212,10 +1212,12 @@ __device__ __forceinline__ uint32_t next_job(const JobDesc* __restrict__ jobs, u
 // one wave meets the end itself, fetches the next chunk and writes the word anew
 // (kJobDone once the queue is empty); those past the end wait for that.  A chunk is
 // the entries that a pop is worth (least, from the host; one for each wave at
-// most), or a quarter of a workgroup's share of what is left, so late workgroups
-// find work.  Up to kDirectPops entries the pops cost less than chunks that end in
-// a workgroup whose other waves are busy (4096 curves, chunks / pops, us: g = 3,
-// q = 11, 520 entries 115 / 108; g = 3, q = 17, 1040 entries 99 / 138): every wave
+// most), or from its second one on a quarter of a workgroup's share of what is
+// left, so late workgroups find work and take no more of it than they should (a
+// first chunk by the whole job's share: 2^23 curves each at g = 4, q = 11 and 13,
+// 72.9 -> 81.4 ms).  Up to kDirectPops entries the pops cost less than chunks that
+// end in a workgroup whose other waves are busy (4096 curves, chunks / pops, us: g =
+// 3, q = 11, 520 entries 115 / 108; g = 3, q = 17, 1040 entries 99 / 138): every wave
 // pops for itself, and the first to find the queue empty tells its workgroup.
 constexpr uint64_t kJobDone = 0xFFFFFFFFull << 32;
 constexpr uint32_t kDirectPops = 1024;
@@ -1243,7 +1245,8 @@ __device__ __forceinline__ uint32_t next_job_entry(uint64_t* range, uint32_t* qu
           break;
         }
         if (at == end) {
-          const uint32_t chunk = max(min(least, blockDim.x / kWave), (n - end) / (4u * gridDim.x));
+          // a workgroup's first chunk of a job (end = 0) says how much is left
+          const uint32_t chunk = max(min(least, blockDim.x / kWave), end ? (n - end) / (4u * gridDim.x) : 0u);
           const uint32_t got = end < n ? atomicAdd(queue, chunk) : n;
           if (got < n) {
             store_range(range, (uint64_t)(n - got < chunk ? n : got + chunk) << 32 | (got + 1u));

@@ -30,6 +30,18 @@ def _job(curvegen_mod, q, g, n):
             "d_out_N": torch.full((n, g), -1, dtype=torch.int32, device="cuda")}
 
 
+def _best(ctx, call):
+    call()
+    ctx.status()
+    t = []
+    for _ in range(10):
+        t0 = time.perf_counter()
+        call()
+        ctx.status()
+        t.append(time.perf_counter() - t0)
+    return min(t)
+
+
 @pytest.mark.parametrize("sizes", [(1,), (65,), (70_001,), (0, 1, 64, 5000), (40_000, 3, 0, 9000, 20_000)])
 def test_every_entry_once(ctx, curvegen_mod, sizes):
     import torch
@@ -59,17 +71,21 @@ def test_one_job_is_not_bound_by_its_queue(ctx, curvegen_mod):
     import torch
     j = _job(curvegen_mod, 13, 3, 1 << 18)
 
-    def best(call):
-        call()
-        ctx.status()
-        t = []
-        for _ in range(10):
-            t0 = time.perf_counter()
-            call()
-            ctx.status()
-            t.append(time.perf_counter() - t0)
-        return min(t)
-
-    alone = best(lambda: ctx.count_curves_dev(13, 3, j["d_coeffs"], j["d_out_N"]))
-    batch = best(lambda: ctx.count_batch([j]))
+    alone = _best(ctx, lambda: ctx.count_curves_dev(13, 3, j["d_coeffs"], j["d_out_N"]))
+    batch = _best(ctx, lambda: ctx.count_batch([j]))
     assert batch < alone + 300e-6, (batch, alone)
+
+
+def test_late_workgroups_take_their_share(ctx, curvegen_mod):
+    """Two large jobs take about the sum of their times alone: a workgroup that comes
+    to the second one when little of it is left takes little (with a chunk by the
+    whole job's size the end cost an eighth)."""
+    import torch
+    jobs = []
+    for q in (11, 13):
+        j = _job(curvegen_mod, q, 4, 1 << 20)
+        jobs.append({**j, "d_coeffs": j["d_coeffs"].repeat(4, 1),
+                     "d_out_N": torch.empty((1 << 22, 4), dtype=torch.int32, device="cuda")})
+    alone = [_best(ctx, lambda j=j: ctx.count_batch([j])) for j in jobs]
+    both = _best(ctx, lambda: ctx.count_batch(jobs))
+    assert both < 1.06 * sum(alone), (both, alone)
