@@ -40,9 +40,11 @@
 // so a pair costs three steps for A, two for B and one read of a byte table for
 // both N(v) and N(-v): six reads for two points in place of six for one.  The
 // n_i are integers, some 50 more vector instructions a translate.  A pair is 16
-// vector instructions and 16.3 clocks of LDS.  Single points -> pairs, count
-// with its bucketing: q = 293, 2^18 curves 5.83 -> 3.46 ms; 101, 500 001 curves
-// 1.41 -> 1.01; 37, 2^18 curves 250 -> 236 us.
+// vector instructions and 16.3 clocks of LDS; with the translates 22.4 and 17.1 at
+// q = 293, in 21.6 CU-clocks: vector issue bounds it (1.04 instructions per CU and
+// clock, LDS active 79 %).  Single points -> pairs, count with its bucketing: q =
+// 293, 2^18 curves 5.83 -> 3.46 ms; 101, 500 001 curves 1.41 -> 1.01; 37, 2^18
+// curves 250 -> 236 us.
 //
 // The last step of the other fields needs the parity of log(1 - v O^2 / E^2) only:
 // w = log(-v) + 2 (log O - log E) mod M, so the sum d of the halves counts mod
