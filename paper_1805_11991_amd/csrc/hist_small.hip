@@ -223,15 +223,15 @@ bool hist_is_small(uint64_t n, uint32_t g, uint32_t q, bool lam) {
   if (n == 0 || n > kHistSmallMax) return false;
   const uint32_t codes = lam ? lam_code_list(g, nullptr) : 0u;
   uint32_t bits = lam ? 32u - (uint32_t)__builtin_clz(codes) : 0u;
-  double space = lam ? __builtin_log2((double)codes) : 0.0;
+  unsigned __int128 space = lam ? codes : 1u;
   uint64_t qk = 1;
   for (uint32_t k = 0; k < g; ++k) {
     qk *= q;
     if (qk > (1u << 24)) return false;
     bits += 32u - (uint32_t)__builtin_clz((uint32_t)(2 * qk + 2));
-    space += __builtin_log2((double)(2 * qk + 3));
+    space *= 2 * qk + 3;
   }
-  return bits <= 64 && space <= 63.0;
+  return bits <= 64 && space <= (unsigned __int128)1 << 63;
 }
 
 hipError_t launch_hist_small(const HistJob& J, const LamCodes* lc, uint32_t* err, hipStream_t s) {
